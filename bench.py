@@ -602,8 +602,8 @@ def cpu_baseline(wl, p_nr, p_rh, budget_s=12.0, max_steps=50, rows=None):
                 ms_per_step=round(t_tot / n * 1e3, 3))
 
 
-KERNEL_SYMBOLS = {"fwd_persist": ("lsd::k_fwd_persist<", "lsd::k_fwd_big<"), "step": ("lsd::k_step<",),
-                  "bwd_persist": ("lsd::k_bwd_persist<", "lsd::k_bwd_big"), "bwd": ("lsd::k_bwd<",),
+KERNEL_SYMBOLS = {"fwd_persist": ("lsd::k_fwd_persist<", "lsd::k_fwd_res<"), "step": ("lsd::k_step<",),
+                  "bwd_persist": ("lsd::k_bwd_persist<", "lsd::k_bwd_res<"), "bwd": ("lsd::k_bwd<",),
                   "wgrad": ("lsd::k_wgrad",),            # the row-sparse, the full and the large-batch kernel
                   "fx": ("lsd::k_fx<", "lsd::k_fx_big"), "dx": ("lsd::k_dx<", "lsd::k_dx_big"),
                   "mask_build": ("lsd::k_mask_build",), "transpose": ("lsd::k_trans",)}

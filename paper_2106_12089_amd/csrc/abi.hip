@@ -48,11 +48,26 @@ constexpr int KID_FWDP_ = 7;
 constexpr int KID_BWDP_ = 8;
 template <typename T>
 hipError_t launch_bwd_persist(PBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1);
-hipError_t launch_fwd_big(PFwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1);
-hipError_t launch_bwd_big(PBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_fwd_res(RFwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1);
+hipError_t launch_bwd_res(RBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1);
+double fwd_res_cost(int B, int H, int nslots);
+double bwd_res_cost(int B, int H, int nslots);
 bool wgrad_big_fits(int B);
 int kernel_timer_start(const char* name);
 int kernel_timer_stop(double* total_ms, int64_t* launches);
+
+// the persistent kernels of the fp32 path (bf16 runs with register-resident
+// weights, or per step where those do not fit the device)
+template <typename E>
+static hipError_t fwd_persist(PFwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1) {
+    if constexpr (std::is_same<E, float>::value) return launch_fwd_persist<float>(a, st, timer_on, e0, e1);
+    else return hipErrorInvalidValue;
+}
+template <typename E>
+static hipError_t bwd_persist(PBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1) {
+    if constexpr (std::is_same<E, float>::value) return launch_bwd_persist<float>(a, st, timer_on, e0, e1);
+    else return hipErrorInvalidValue;
+}
 
 static thread_local std::string g_err;
 
@@ -154,7 +169,6 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     q.w_dc = off;     off = align_up(off + D * B * H * 4, A);
     q.w_dhc = off;    off = align_up(off + D * B * H * 4, A);
     q.w_dxc = off;    off = align_up(off + 2 * T * B * (size_t)q.kin_max * 4, A);
-    q.w_part = off;   off = align_up(off + (size_t)((4 * q.H + 511) / 512) * B * H * 4, A);
     const size_t bwd = off;
     q.w_sync = align_up(fwd > bwd ? fwd : bwd, A);
     q.w_loss = q.w_sync + align_up(SYNC_BYTES, A);   // barrier counters and error flag
@@ -170,15 +184,14 @@ static bool use_stacked() {
     return !(v && v[0] == '0');
 }
 
-// LSTM_SD_FWD_WORKERS=0: a stacked forward without input-product workers
+// LSTM_SD_FWD_WORKERS=0: a stacked fp32 forward without input-product workers
 static bool use_fwd_workers() {
     const char* v = getenv("LSTM_SD_FWD_WORKERS");
     return !(v && v[0] == '0');
 }
 
-// The large-batch persistent kernels (bf16) run where the row-group tiling
-// does not fit.  LSTM_SD_BIG=0: never (per-step kernels there instead);
-// LSTM_SD_BIG=2: wherever they apply, one launch per layer (tests of their
+// The large-batch row-sparse weight gradient (bf16, LSTM_SD_WGRAD_GEMM=0) runs
+// from 128 rows.  LSTM_SD_BIG=0: never; LSTM_SD_BIG=2: from 64 rows (tests of its
 // tiling on ragged shapes).
 static int big_mode() {
     const char* v = getenv("LSTM_SD_BIG");
@@ -197,6 +210,18 @@ static bool use_wgrad_big() {
 static bool use_gemm_big() {
     const char* v = getenv("LSTM_SD_GEMM_BIG");
     return !(v && v[0] == '0');
+}
+
+// Whether a stack runs as one pipeline (T + 2(L-1) steps of all its slots, cs ns
+// each) rather than layer by layer (c1 ns a step): its estimated time is below
+// that of the layers one after the other, each launch with about 20 us of its own
+// (weights into registers), and the products between them at about 300 TFLOP/s.  A
+// large batch fills the chip with one layer's row groups, and a wide layer's
+// backward is faster in the narrow tiles of a launch of its own.
+static bool res_stack_pays(const Plan& P, double cs, double c1) {
+    const double product = 5000.0 + 2.0 * P.T * P.B * (double)P.G * P.H / 300e3;
+    return 20000.0 + (P.T + 2.0 * (P.L - 1)) * cs + 10000.0 * (P.L - 1) <=
+           P.L * (20000.0 + P.T * c1) + (P.L - 1) * product;
 }
 
 static bool use_persistent() {
@@ -409,38 +434,87 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
         }
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool timed = timer_pair(KID_FWDP_, &e0, &e1);
-        if (launch_fwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) return true;
+        if (fwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) return true;
         (void)hipGetLastError();              // does not fit
         if (timed) timer_unpair();
         return false;
     };
-    const bool big_first = std::is_same<E, bf16>::value && big_mode() == 2;
+    // The recurrences with register-resident weights (bf16, hidden size up to
+    // 1536): layers l0 .. l0+nl-1, a stack's with a worker slot between layers.
+    auto res_launch = [&](int l0, int nl) -> bool {
+        RFwdArgs ra;
+        memset(&ra, 0, sizeof(ra));
+        ra.lengths = lengths;
+        ra.bar = (unsigned*)(W + P.w_sync);
+        ra.err = (int*)(W + P.w_sync + SYNC_ERR_OFS);
+        ra.timeout = barrier_timeout_ticks();
+        ra.B = B; ra.H = H; ra.T = T; ra.BP = BP; ra.ldy = D * H; ra.kmax = P.kmax; ra.mtiles = P.mtiles;
+        int n = 0;
+        for (int l = l0; l < l0 + nl; ++l) {
+            int wk = -1;
+            if (l > l0) {                     // (a stack: D == 1) the worker of layer l: slot n, the layer below n - 1
+                RFwdSlot& x = ra.d[n];
+                wk = n++;
+                x.role = 1; x.dep = wk - 1; x.dir = 0; x.s = P.s_nr[l];
+                x.U = w->W[l]; x.bias = w->b[l];
+                x.xin = W + P.w_xx + (size_t)(l - 1) * T * P.xxs * es;
+                x.gxp = (float*)(W + P.w_gxs) + (size_t)(l - 1) * T * B * G;
+            }
+            for (int d = 0; d < D; ++d) {
+                const int k = l * D + d;
+                char* rd = R + P.rdir(l, d);
+                RFwdSlot& x = ra.d[n++];
+                x.role = 0; x.dep = wk; x.dir = d; x.s = P.s_rh[l];
+                x.U = w->U[k];
+                x.gx = (const float*)(W + P.w_gx) + (size_t)d * T * B * G;
+                if (wk >= 0) x.gxp = ra.d[wk].gxp;
+                x.h0 = (const char*)h0 + (size_t)k * B * H * es;
+                x.c0 = c0 + (size_t)k * B * H;
+                x.rmask = site_view(P, mbuf, P.site_rh(l, d)).mask;
+                x.hx = W + P.w_hx + (size_t)(nl > 1 ? l : d) * 2 * P.hxs * es;
+                if (l + 1 < l0 + nl) {
+                    x.umask = site_view(P, mbuf, P.site_nr(l + 1)).mask;
+                    x.xout = W + P.w_xx + (size_t)l * T * P.xxs * es;
+                }
+                x.gates = (float*)(rd + P.r_gates);
+                x.cres = (float*)(rd + P.r_c);
+                x.hrecT = rd + P.r_hrecT;
+                x.hT = hT + (size_t)k * B * H;
+                x.cT = cT + (size_t)k * B * H;
+                if (l == L - 1) {
+                    x.y = y + d * H;
+                } else {
+                    x.ybuf = R + P.rybuf(l) + (size_t)d * H * es;
+                    x.ybufT = R + P.rybufT(l) + (size_t)d * H * BP * es;
+                }
+            }
+        }
+        ra.nslots = n;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        const bool timed = timer_pair(KID_FWDP_, &e0, &e1);
+        if (launch_fwd_res(ra, st, timed, e0, e1) == hipSuccess) return true;
+        (void)hipGetLastError();              // does not fit
+        if (timed) timer_unpair();
+        return false;
+    };
     bool fx0_done = false;
-    if (use_persistent() && use_stacked() && !big_first && D == 1 && L > 1 && L <= 4) {
+    const bool res = std::is_same<E, bf16>::value && use_persistent() && fwd_res_cost(B, H, D) > 0.0;
+    if (res && use_stacked() && D == 1 && L > 1 && L <= 4) {
+        const double cs = fwd_res_cost(B, H, 2 * L - 1), c1 = fwd_res_cost(B, H, 1);
+        if (cs > 0.0 && res_stack_pays(P, cs, c1)) {
+            launch_fx_layer(0);
+            if (res_launch(0, L)) return hip_check("forward launch");
+            fx0_done = true;
+        }
+    }
+    if (!std::is_same<E, bf16>::value && use_persistent() && use_stacked() && D == 1 && L > 1 && L <= 4) {
         launch_fx_layer(0);
         if ((use_fwd_workers() && stacked(true)) || stacked(false)) return hip_check("forward launch");
         fx0_done = true;                      // neither fits: one layer at a time below
     }
     for (int l = 0; l < L; ++l) {
-        const int kin = P.kin(l);
-        const void* X = l == 0 ? x : (const void*)(R + P.rybuf(l - 1));
-        for (int d = 0; d < D && !(l == 0 && fx0_done); ++d) {
-            FxArgs f;
-            memset(&f, 0, sizeof(f));
-            f.X = X; f.ldx = kin;
-            f.W = w->W[l * D + d];
-            f.bias = w->b[l * D + d];
-            f.site = site_view(P, mbuf, P.site_nr(l));
-            f.Gx = (float*)(W + P.w_gx) + (size_t)d * T * B * G;
-            f.K = kin; f.B = B; f.G = G; f.T = T; f.dense = !P.compact; f.s = P.s_nr[l];
-            if (gemm_big) {
-                f.XT = l == 0 ? (const void*)(R + P.r_xT) : (const void*)(R + P.rybufT(l - 1));
-                f.xt_tstride = (long)kin * BP;
-                f.xt_ld = BP;
-            }
-            attach_tr(f);
-            launch_fx<E>(f, st);
-        }
+        if (!(l == 0 && fx0_done)) launch_fx_layer(l);
+        if (res && res_launch(l, 1)) continue;
         if (use_persistent()) {
             PFwdArgs pa;
             common_args(pa);
@@ -451,13 +525,8 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
             }
             hipEvent_t e0 = nullptr, e1 = nullptr;
             const bool timed = timer_pair(KID_FWDP_, &e0, &e1);
-            if (big_first && launch_fwd_big(pa, st, timed, e0, e1) == hipSuccess) continue;
-            (void)hipGetLastError();
-            if (launch_fwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) continue;
-            (void)hipGetLastError();          // does not fit: the large-batch kernel (bf16), else per step
-            if (std::is_same<E, bf16>::value && use_big() && launch_fwd_big(pa, st, timed, e0, e1) == hipSuccess)
-                continue;
-            (void)hipGetLastError();
+            if (fwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) continue;
+            (void)hipGetLastError();          // does not fit: per step
             if (timed) timer_unpair();
         }
         for (int s = 0; s < T; ++s) {
@@ -543,6 +612,60 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
         pd.s_rh = P.s_rh[l];
         pd.above = -1;
     };
+    // The recurrences with register-resident weights, as in the forward:
+    // layers l1 down to l0 (a stack's with a worker slot between layers).  An
+    // inner layer that starts a launch reads its input gradient full width.
+    bool res = std::is_same<E, bf16>::value && use_persistent() && bwd_res_cost(B, H, D) > 0.0;
+    auto res_launch = [&](int l1, int l0, const float* dy_above, int lddy) -> bool {
+        RBwdArgs ra;
+        memset(&ra, 0, sizeof(ra));
+        ra.lengths = lengths;
+        ra.bar = sync_bar;
+        ra.err = sync_err;
+        ra.timeout = barrier_timeout_ticks();
+        ra.B = B; ra.H = H; ra.T = T; ra.BP = BP; ra.kmax = P.kmax; ra.mtiles = P.mtiles;
+        int n = 0;
+        for (int l = l1; l >= l0; --l) {
+            const int reg = l1 > l0 ? l : 0;  // DA regions: per layer of a stack, or per direction
+            int wk = -1;
+            if (l < l1) {                     // (a stack) the worker forming dx of layer l+1: slot n, that layer n - 1
+                RBwdSlot& x = ra.d[n];
+                wk = n++;
+                x.role = 1; x.dep = wk - 1; x.dir = 0; x.s = P.s_nr[l + 1];
+                x.U = w->W[l + 1];
+                x.mask = site_view(P, mbuf, P.site_nr(l + 1)).mask;
+                x.dxw = (float*)(W + P.w_dxw) + (size_t)l * T * B * H;
+                x.da = da_of(l + 1);
+            }
+            for (int d = 0; d < D; ++d) {
+                const int k = l * D + d;
+                const char* rd = R + P.rdir(l, d);
+                RBwdSlot& x = ra.d[n++];
+                x.role = 0; x.dep = wk; x.dir = d; x.s = P.s_rh[l];
+                x.U = w->U[k];
+                x.mask = site_view(P, mbuf, P.site_rh(l, d)).mask;
+                x.gates = (const float*)(rd + P.r_gates);
+                x.cres = (const float*)(rd + P.r_c);
+                x.c0 = c0 + (size_t)k * B * H;
+                x.dy = dy_above + d * H;
+                x.lddy = lddy;
+                if (wk >= 0) x.dxw = ra.d[wk].dxw;
+                x.dhT = dhT ? dhT + (size_t)k * B * H : nullptr;
+                x.dcT = dcT ? dcT + (size_t)k * B * H : nullptr;
+                x.da = da_of(reg + d);
+                x.daT = daT_of(reg + d);
+                x.dh0 = dh0 + (size_t)k * B * H;
+                x.dc0 = dc0 + (size_t)k * B * H;
+            }
+        }
+        ra.nslots = n;
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        const bool timed = timer_pair(KID_BWDP_, &e0, &e1);
+        if (launch_bwd_res(ra, st, timed, e0, e1) == hipSuccess) return true;
+        (void)hipGetLastError();              // does not fit
+        if (timed) timer_unpair();
+        return false;
+    };
     // input gradient of layer l for the layer below (and the caller's dx)
     auto layer_dx = [&](int l, int reg0, float* dxc_here) {
         const int kin = P.kin(l);
@@ -553,8 +676,9 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
             a.da[d] = da_of(reg0 + d);
             a.W[d] = w->W[l * D + d];
         }
-        // layer 0 writes the caller's full-width dx directly
-        a.site = nv; a.out = l == 0 ? dx : dxc_here; a.scatter = l == 0; a.D = D; a.B = B; a.G = G; a.ldo = kin;
+        // layer 0 writes the caller's full-width dx directly; full width too
+        // where the layer below reads it by unit
+        a.site = nv; a.out = l == 0 ? dx : dxc_here; a.scatter = l == 0 || res; a.D = D; a.B = B; a.G = G; a.ldo = kin;
         a.T = T; a.K = kin; a.tps = ((kin + 7) / 8 + 15) / 16; a.mtiles = P.mtiles;
         a.dense = !P.compact; a.s = P.s_nr[l];
         a.status = sync_status;
@@ -613,8 +737,21 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
 
     // Unidirectional stack: every layer's BPTT in one persistent launch, with
     // a worker between layers l+1 and l forming dx of layer l+1 per step.
-    const bool big_first = std::is_same<E, bf16>::value && big_mode() == 2;
-    if (use_persistent() && use_stacked() && !big_first && D == 1 && L > 1 && 2 * L - 1 <= 8) {
+    if (res && use_stacked() && D == 1 && L > 1 && L <= 4) {
+        // (as the forward's rule; DA of every layer is kept, one region each)
+        const double cs = bwd_res_cost(B, H, 2 * L - 1), c1 = bwd_res_cost(B, H, 1);
+        if (cs > 0.0 && res_stack_pays(P, cs, c1)) {
+            launch_bwd_init(nullptr, nullptr, nullptr, nullptr, 0, W + P.w_da, (int)es, G, P.mtiles, (long)L * T,
+                            (long)P.das, sync_bar, sync_err, st);
+            if (res_launch(L - 1, 0, dy, D * H)) {
+                if (dx) layer_dx(0, 0, (float*)(W + P.w_dxc));
+                for (int l = L - 1; l >= 0; --l) layer_wgrad(l, l);
+                flush_wgrad();
+                return hip_check("backward launch");
+            }
+        }
+    }
+    if (!std::is_same<E, bf16>::value && use_persistent() && use_stacked() && D == 1 && L > 1 && 2 * L - 1 <= 8) {
         launch_bwd_init(nullptr, nullptr, nullptr, nullptr, 0, W + P.w_da, (int)es, G, P.mtiles, (long)L * T,
                         (long)P.das, sync_bar, sync_err, st);
         PBwdArgs pa;
@@ -643,7 +780,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
         }
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool timed = timer_pair(KID_BWDP_, &e0, &e1);
-        if (launch_bwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) {
+        if (bwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) {
             if (dx) layer_dx(0, 0, (float*)(W + P.w_dxc));
             for (int l = L - 1; l >= 0; --l) layer_wgrad(l, l);
             flush_wgrad();
@@ -656,38 +793,22 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
     for (int l = L - 1; l >= 0; --l) {
         float* dhc = (float*)(W + P.w_dhc);
         float* dcs = (float*)(W + P.w_dc);
-        launch_bwd_init(dhT ? dhT + (size_t)l * D * B * H : nullptr, dcT ? dcT + (size_t)l * D * B * H : nullptr,
+        // (the register-resident recurrences hold their carries: only the first
+        // layer's call has anything to clear)
+        if (!res || l == L - 1)
+            launch_bwd_init(dhT ? dhT + (size_t)l * D * B * H : nullptr, dcT ? dcT + (size_t)l * D * B * H : nullptr,
                         dhc, dcs, (long)D * B * H, l == L - 1 ? (void*)(W + P.w_da) : nullptr, (int)es, G,
                         P.mtiles, (long)D * T, (long)P.das, sync_bar, sync_err, st);
         float* dxc_above = (float*)(W + P.w_dxc) + (size_t)((l + 1) & 1) * T * B * P.kin_max;
         float* dxc_here = (float*)(W + P.w_dxc) + (size_t)(l & 1) * T * B * P.kin_max;
         bool persistent_done = false;
-        // the large-batch kernel, one launch per direction
-        auto big = [&]() -> bool {
-            if (!std::is_same<E, bf16>::value || !use_big()) return false;
-            for (int d = 0; d < D; ++d) {
-                PBwdArgs pa;
-                common_args(pa);
-                pa.nslots = 1;
-                pa.lddx = l + 1 < L ? P.kin(l + 1) : 0;
-                pa.part = (float*)(W + P.w_part);
-                PBwdDir& pd = pa.d[0];
-                fill_layer(pd, l, d, d);
-                if (l < L - 1) {
-                    pd.dxc = dxc_above;
-                    pd.dxpos = site_view(P, mbuf, P.site_nr(l + 1)).pos + d * H;
-                }
-                hipEvent_t e0 = nullptr, e1 = nullptr;
-                const bool timed = timer_pair(KID_BWDP_, &e0, &e1);
-                if (launch_bwd_big(pa, st, timed, e0, e1) != hipSuccess) {
-                    (void)hipGetLastError();
-                    if (timed) timer_unpair();
-                    return false;             // (the first direction: nothing was launched)
-                }
+        if (res) {
+            persistent_done = res_launch(l, l, l == L - 1 ? dy : dxc_above, l == L - 1 ? D * H : P.kin(l + 1));
+            if (!persistent_done) {
+                if (l < L - 1) return fail(LSTM_SD_EHIP, "backward launch: a layer's recurrence does not fit");
+                res = false;                  // (decided at the first layer, for all of them)
             }
-            return true;
-        };
-        if (use_persistent() && big_first) persistent_done = big();
+        }
         if (use_persistent() && !persistent_done) {
             PBwdArgs pa;
             common_args(pa);
@@ -703,12 +824,11 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
             }
             hipEvent_t e0 = nullptr, e1 = nullptr;
             const bool timed = timer_pair(KID_BWDP_, &e0, &e1);
-            if (launch_bwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) {
+            if (bwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) {
                 persistent_done = true;
             } else {
-                (void)hipGetLastError();      // does not fit: the large-batch kernel, else per step
+                (void)hipGetLastError();      // does not fit: per step
                 if (timed) timer_unpair();
-                persistent_done = big();
             }
         }
         // T pointwise steps plus one final pass (recurrent gradient of h0)

@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(512) k_dx_big(DxArgs a) {
                 const int ck = 2 * c + (blk >> 4), mt = mt0 + (blk & 15);
                 const bool ok = mt < a.mtiles && 32 * ck < G;
                 ra[set][i] = __builtin_amdgcn_raw_buffer_load_b128(
-                    dr, ok ? (uint32_t)(frag_lane_off(ck, mt, l, a.mtiles) * 2) : OOB_OFF, 0, 0);
+                    dr, ok ? (uint32_t)(frag_lane_off(ck, mt, l, (G + 31) / 32) * 2) : OOB_OFF, 0, 0);
             }
 #pragma unroll
             for (int i = 0; i < 2; ++i) {

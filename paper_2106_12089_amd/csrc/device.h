@@ -54,18 +54,21 @@ __device__ __forceinline__ void mma_16x16x32(const Frag<float>& a, const Frag<fl
 }
 
 // Fragment-major layout of a [rows][cols] matrix whose rows are the M side
-// of an MFMA product: 32-column chunks x 16-row tiles x 64 lanes x 8
-// elements.  Element (row, col) of a matrix with `mtiles` 16-row tiles sits
-// at frag_off(row, col, mtiles); the A fragment of (chunk c, tile mt) is the
-// 16 bytes of lane l at frag_lane_off(c, mt, l, mtiles), and a wave reads it
-// as one contiguous 1 KB block.  A buffer holds ceil(cols/32)*mtiles*512
+// of an MFMA product: 16-row tiles x 32-column chunks x 64 lanes x 8
+// elements.  Element (row, col) of a matrix with `nch` 32-column chunks sits
+// at frag_off(row, col, nch); the A fragment of (chunk c, tile mt) is the
+// 16 bytes of lane l at frag_lane_off(c, mt, l, nch), and a wave reads it
+// as one contiguous 1 KB block.  Row tiles are outermost: what a row group of
+// a recurrence reads at every step is then one contiguous range, spread over
+// all L2 channels (with chunks outermost a group read 1 of every 2 KB at batch
+// 20, or 2 of every 16 KB at batch 256: half of the channels).  A buffer holds ceil(cols/32)*mtiles*512
 // elements.
-__device__ __forceinline__ size_t frag_lane_off(int c, int mt, int lane, int mtiles) {
-    return (((size_t)c * mtiles + mt) * 64 + lane) << 3;
+__device__ __forceinline__ size_t frag_lane_off(int c, int mt, int lane, int nch) {
+    return (((size_t)mt * nch + c) * 64 + lane) << 3;
 }
-__device__ __forceinline__ size_t frag_off(int row, int col, int mtiles) {
+__device__ __forceinline__ size_t frag_off(int row, int col, int nch) {
     const int k = col & 31;
-    return frag_lane_off(col >> 5, row >> 4, (k >> 3) * 16 + (row & 15), mtiles) + (k & 7);
+    return frag_lane_off(col >> 5, row >> 4, (k >> 3) * 16 + (row & 15), nch) + (k & 7);
 }
 
 // 8 consecutive elements (16-byte aligned bf16, 32-byte aligned f32)

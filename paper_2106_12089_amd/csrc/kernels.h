@@ -256,6 +256,76 @@ struct PFwdArgs {
     size_t xxs;                         // elements per xin/xout slot
 };
 
+// Persistent recurrences with register-resident weights (bf16).  Their barrier
+// counters share the region of the others: RB_GROUPS groups (slot, row group)
+// of RB_LINES lines of RB_PITCH words.
+constexpr int RB_PITCH = 32, RB_LINES = 8, RB_GROUPS = 32;
+static_assert(RB_PITCH * RB_LINES * RB_GROUPS <= BAR_PITCH * BAR_LINES * BAR_EXIT, "groups end before the exit counter");
+
+struct RFwdSlot {
+    int role;                           // 0: a layer (direction); 1: an input-product worker
+    int dep;                            // worker: slot of the layer below; layer: slot of its worker; or -1
+    int dir;                            // 0: t = 0 .. T-1;  1: t = T-1 .. 0
+    float s;                            // dropout scale of the product (layer: RH; worker: NR of the layer's input)
+    const void* U;                      // [H][4H]: layer U; worker W of the layer
+    const float* gx;                    // layer without a worker: [T][B][4H] input product incl. bias
+    float* gxp;                         // worker's output / fed layer's input product: [T][B][H][4]
+    const float* bias;                  // worker: [4H]
+    const void* xin;                    // worker: [T] exchange slots of the layer below's masked output
+    const void* h0;                     // [B][H]
+    const float* c0;                    // [B][H]
+    const uint8_t* rmask;               // RH mask rows
+    const uint8_t* umask;               // NR mask rows of the layer above (with xout)
+    void* hx;                           // [2] exchange slots of the masked h_t
+    void* xout;                         // [T] exchange slots of the masked output for the layer above, or null
+    float* gates;                       // [T][B][H][4]
+    float* cres;                        // [T][B][H]
+    void* hrecT;                        // [T][H][BP]
+    float* hT;                          // [B][H]
+    float* cT;                          // [B][H]
+    float* y;                           // top layer: y + d*H (rows ld ldy), or null
+    void* ybuf;                         // inner layer: ybuf + d*H, or null
+    void* ybufT;
+};
+struct RFwdArgs {
+    RFwdSlot d[8];
+    const int32_t* lengths;
+    unsigned* bar;
+    int* err;
+    long long timeout;
+    int B, H, T, BP, ldy, kmax, mtiles, nslots;
+    int ntiles, mgroups, mg0, rg, gpx;  // (set by the launcher) unit tiles; row groups of the launch, the first one, their rows; groups per XCD
+};
+struct RBwdSlot {
+    int role;                           // 0: a layer (direction); 1: an input-gradient worker
+    int dep;                            // worker: slot of the layer whose DA it reads; layer: slot of its worker; or -1
+    int dir;                            // 0: t = T-1 .. 0;  1: t = 0 .. T-1
+    float s;                            // layer: RH scale; worker: NR scale of the layer above
+    const void* U;                      // [H][4H]: layer U; worker W of the layer above
+    const uint8_t* mask;                // layer: RH mask rows; worker: NR mask rows of the layer above
+    const float* gates;                 // [T][B][H][4]
+    const float* cres;                  // [T][B][H]
+    const float* c0;                    // [B][H]
+    const float* dy;                    // layer without a worker: dh input, row (t, b) at (t*B + b)*lddy
+    int lddy;
+    const float* dhT;                   // [B][H] or null
+    const float* dcT;
+    float* dxw;                         // [T][B][H]: a worker's output, a fed layer's input
+    void* da;                           // [T] x fragment-major [B][4H] (worker: of the layer above)
+    void* daT;                          // [T][4H][BP]
+    float* dh0;
+    float* dc0;
+};
+struct RBwdArgs {
+    RBwdSlot d[8];
+    const int32_t* lengths;
+    unsigned* bar;
+    int* err;
+    long long timeout;
+    int B, H, T, BP, kmax, mtiles, nslots;
+    int ntiles, mgroups, mg0, rg, gpx;
+};
+
 // Persistent BPTT of one layer (both directions): one launch
 // runs all T backward steps and the final pass that forms dh0/dc0.
 struct PBwdDir {
@@ -293,8 +363,6 @@ struct PBwdArgs {
     int* err;
     long long timeout;                  // wall-clock ticks (<= 0: every wait fails at once)
     int B, H, T, BP, ldy, lddx, kmax, dense, ntiles, mgroups, mtiles, nslots;
-    float* part;                        // large-batch kernel: [ngk][B][H] partial recurrent gradients
-    int ngu, ngk;                       // large-batch kernel: unit groups and gate-column groups
 };
 
 }  // namespace lsd

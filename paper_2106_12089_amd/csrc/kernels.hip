@@ -148,6 +148,13 @@ __global__ void __launch_bounds__(256) k_mask_build(MaskArgs a) {
     }
 }
 
+// every barrier counter and flag of the persistent kernels <- 0 (one workgroup)
+__device__ __forceinline__ void clear_counters(unsigned* bar) {
+    constexpr int N = BAR_PITCH * BAR_LINES * BAR_EXIT;
+    for (int i = threadIdx.x; i < N / 4; i += blockDim.x) ((uint4*)bar)[i] = make_uint4(0u, 0u, 0u, 0u);
+    if (threadIdx.x == 0) bar[N] = 0u;
+}
+
 // ---------------------------------------------------------------------------
 // src [N][B][K] -> dst [N][K][BP], zero rows b in [B, BP); two such jobs
 // (matrices z < n1 from the first, the others from the second) in one grid,
@@ -161,7 +168,7 @@ __device__ __forceinline__ void transpose_block(const TransArgs& a, int N, int b
     if (bz == N) {
         const long nb = (long)gx * gy, bi = (long)by * gx + bx;
         if (bi == 0) {
-            for (int i = tid; i <= BAR_LINES * BAR_EXIT; i += 256) a.bar[BAR_PITCH * i] = 0u;
+            clear_counters(a.bar);
             if (tid == 0) {
                 *a.err = 0;
                 *(int*)((char*)a.err + (SYNC_STATUS_OFS - SYNC_ERR_OFS)) = 0;   // a new step's status
@@ -505,8 +512,8 @@ __global__ void __launch_bounds__(1024) k_bwd(BwdArgs a) {
                     const int row = m0 + mt * 16 + (lane & 15);
                     Frag<T> fa;
                     // fragment-major DA: entries past B or 4H are never written
-                    ld4(DA + frag_lane_off(nc >> 5, (m0 >> 4) + mt, lane, a.mtiles), fa.v);
-                    ld4(DA + frag_lane_off(nc >> 5, (m0 >> 4) + mt, lane, a.mtiles) + 4, fa.v + 4);
+                    ld4(DA + frag_lane_off(nc >> 5, (m0 >> 4) + mt, lane, (G + 31) / 32), fa.v);
+                    ld4(DA + frag_lane_off(nc >> 5, (m0 >> 4) + mt, lane, (G + 31) / 32) + 4, fa.v + 4);
 #pragma unroll
                     for (int e = 0; e < 8; ++e)
                         if (row >= B || nc + g8 + e >= G) fa.v[e] = zero_val<T>();
@@ -568,7 +575,7 @@ __global__ void __launch_bounds__(1024) k_bwd(BwdArgs a) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const T v = from_f32<T>(da4[g]);
-                ((T*)D.da)[frag_off(b, g * H + u, a.mtiles)] = v;
+                ((T*)D.da)[frag_off(b, g * H + u, (G + 31) / 32)] = v;
                 dat[(size_t)(g * H + u) * a.BP + b] = v;
             }
         }
@@ -638,7 +645,7 @@ __global__ void __launch_bounds__(256) k_dx(DxArgs a) {
                 raw_load(fb[u], wr, woff + nc * ES);
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    raw_load(fa[u][mt], dr, m0 + 16 * mt + cl < a.B ? (uint32_t)(frag_lane_off(nc >> 5, (m0 >> 4) + mt, lane, a.mtiles) * ES) : OOB_OFF);
+                    raw_load(fa[u][mt], dr, m0 + 16 * mt + cl < a.B ? (uint32_t)(frag_lane_off(nc >> 5, (m0 >> 4) + mt, lane, (a.G + 31) / 32) * ES) : OOB_OFF);
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -1584,7 +1591,7 @@ __global__ void __launch_bounds__(WFS_FS_THREADS) __attribute__((amdgpu_waves_pe
 // the persistent kernels' barrier counters and error flag <- 0
 __device__ __forceinline__ void clear_sync(unsigned* bar, int* err) {
     if (blockIdx.x == 0) {
-        for (int i = threadIdx.x; i <= BAR_LINES * BAR_EXIT; i += blockDim.x) bar[BAR_PITCH * i] = 0u;
+        clear_counters(bar);
         if (threadIdx.x == 0) *err = 0;
     }
 }
@@ -1605,7 +1612,7 @@ __global__ void k_bwd_init(const float* dhT, const float* dcT, float* dhc, float
     const long np = da ? nblk * rows * padc : 0;
     for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < np; i += (long)gridDim.x * blockDim.x) {
         const long blk = i / (rows * padc), rem = i % (rows * padc);
-        const size_t off = (size_t)blk * das + frag_off((int)(rem / padc), G + (int)(rem % padc), mtiles);
+        const size_t off = (size_t)blk * das + frag_off((int)(rem / padc), G + (int)(rem % padc), (G + 31) / 32);
         if (es == 2) ((uint16_t*)da)[off] = 0;
         else ((uint32_t*)da)[off] = 0u;
     }
@@ -1946,7 +1953,7 @@ __global__ void __launch_bounds__(256) k_ce_grad(const float* z, const int32_t* 
                 float o[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) o[e] = tile[r][k0 + e];
-                st8(dat + frag_lane_off(c, mt, lane, mtiles), o);
+                st8(dat + frag_lane_off(c, mt, lane, nchunk), o);
             }
         }
         __syncthreads();

@@ -1,5 +1,5 @@
-// Persistent recurrent kernels (gfx950): one launch runs every
-// time step of a layer.  Each workgroup keeps its slice of the recurrent
+// Persistent recurrent kernels of the fp32 path (gfx950; bf16 runs with its weights
+// in registers, elsewhere): one launch runs every time step of a layer.  Each workgroup keeps its slice of the recurrent
 // weight U in LDS and its part of the cell state in registers for the whole
 // sequence; the workgroups meet at a grid barrier once per step.
 //
@@ -36,15 +36,10 @@ namespace lsd {
 // loads before its first MFMA) and reduced in LDS.
 // Dynamic LDS: the weight slice, U for a layer, W for a worker, with HP =
 // fwd_hp(H) (or KP) rows: rows of the weight rounded up to 32, plus 8, zero
-// past the end.  bf16 slices are K-major, [HP][16*NT + 4]: the B fragment of
-// a 16-column tile over 32 kept neurons is two transposing 8-byte LDS reads
-// per lane, whose addresses are the kept rows of the keep list, so a
-// gathered fragment costs what a contiguous one does.  f32 slices are
-// column-major, [16*NT][HP], a fragment one 32-byte read (identity keep
-// list) or 8 gathered elements.  Then keep lists [H+32] and [kin_max+32]
+// past the end; column-major, [16*NT][HP], a fragment one 32-byte read
+// (identity keep list) or 8 gathered elements.  Then keep lists [H+32] and [kin_max+32]
 // (int16) and the reduction area [8][MG][16*NT] (float).
 constexpr int PF_NW = 8;
-__host__ __device__ constexpr int fwd_ncp(int NT) { return 16 * NT + 4; }
 
 template <typename T, int NT, int MG>
 __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
@@ -52,8 +47,6 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
     constexpr int NTH = 64 * NW;
     constexpr int PPT = (MG * UPW + NTH - 1) / NTH;
     constexpr int MAXC = MT <= 2 ? 3 : 2;       // chunks per wave per round (registers)
-    constexpr bool KM = sizeof(T) == 2;          // K-major weight slices (transposing reads)
-    constexpr int NCP = fwd_ncp(NT);             // their row pitch (elements)
     extern __shared__ __align__(16) char smem[];
     const int H = a.H, G = 4 * H, B = a.B, T_ = a.T;
     const int HP = fwd_hp(H), KP = a.KP;
@@ -108,7 +101,7 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
                     if (i < total) {
                         const int k = i / NC, c = i % NC;
                         const int u = u0 + 4 * (c >> 4) + ((c & 15) >> 2);
-                        dst[KM ? k * NCP + c : c * pitch + k] = (u < H && k < rows) ? v[j] : zero_val<T>();
+                        dst[c * pitch + k] = (u < H && k < rows) ? v[j] : zero_val<T>();
                     }
                 }
             }
@@ -216,16 +209,16 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
     // round (slots past the keep count have a zeroed A side and read B rows at
     // offset 0: no branch lets the compiler sink the loads into the products).
     auto issue = [&](const T* src, size_t slot_elems, int n, int c0, Raw8<T> (&fa)[MAXC][MT]) {
-        // the resource ends after the chunks the count uses: loads of the
-        // chunk slots past it return 0 and move no data
-        const size_t used = (size_t)((n + 31) / 32) * a.mtiles * 512;
-        const __amdgpu_buffer_rsrc_t hr = buf_rsrc(src, (uint32_t)((used < slot_elems ? used : slot_elems) * sizeof(T)));
+        // loads of the chunk slots past those the count uses return 0 and move
+        // no data
+        const int used = (n + 31) / 32;
+        const __amdgpu_buffer_rsrc_t hr = buf_rsrc(src, (uint32_t)(slot_elems * sizeof(T)));
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
             const int c = c0 + w + NW * i;
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-                raw_load<T, CPOL_SC1>(fa[i][mt], hr, m0 + 16 * mt + (lane & 15) < B ? (uint32_t)(frag_lane_off(c, m0 / 16 + mt, lane, a.mtiles) * sizeof(T)) : OOB_OFF);
+                raw_load<T, CPOL_SC1>(fa[i][mt], hr, c < used && m0 + 16 * mt + (lane & 15) < B ? (uint32_t)(frag_lane_off(c, m0 / 16 + mt, lane, (H + 31) / 32) * sizeof(T)) : OOB_OFF);
         }
     };
     // B fragments of the 32-neuron chunk at kc: rows kid[kc..kc+31] of the
@@ -234,18 +227,7 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
     // of the first chunk (their A side is zero).
     auto load_b = [&](int kc, int n, const int16_t* kid, const T* Bt, int bp, int kfull, Raw8<T> (&fb)[NT]) {
         const int kb = kc < n ? kc : 0;
-        if constexpr (KM) {
-            // lanes 4e..4e+3 of group g address kept row kb + 8g + e (read 0)
-            // and kb + 8g + 4 + e (read 1), at columns 0, 4, 8, 12 of a tile
-            const int j = kb + g8 + ((lane & 15) >> 2);
-            const T* p0 = Bt + (int)kid[j] * NCP + 4 * (lane & 3);
-            const T* p1 = Bt + (int)kid[j + 4] * NCP + 4 * (lane & 3);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const uint2 lo = lds_tr4((const bf16*)(p0 + 16 * nt)), hi = lds_tr4((const bf16*)(p1 + 16 * nt));
-                fb[nt].w[0] = lo.x; fb[nt].w[1] = lo.y; fb[nt].w[2] = hi.x; fb[nt].w[3] = hi.y;
-            }
-        } else if (n == kfull) {                // identity keep list: contiguous rows
+        if (n == kfull) {                       // identity keep list: contiguous rows
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) raw_lds(fb[nt], Bt + (size_t)(nt * 16 + (lane & 15)) * bp + kb + g8);
         } else {
@@ -399,7 +381,7 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
             if (pb[q] < B && pu[q] < H) {
                 const int pp = pos[pu[q]];
                 if (pp >= 0)
-                    xstore(hx0 + frag_off(pb[q], pp, a.mtiles),
+                    xstore(hx0 + frag_off(pb[q], pp, (H + 31) / 32),
                            (a.dense && !msk[pu[q]]) ? zero_val<T>() : from_f32<T>(hreg[q]));
             }
         }
@@ -473,10 +455,10 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
             const T hv = from_f32<T>(vq ? hnv[q] : hreg[q]);
             // (coherent buffer stores at 32-bit offsets, as xstore)
             if (pn[q] >= 0)
-                store_coherent(hxn, hxs, (uint32_t)frag_off(b, pn[q], a.mtiles), (a.dense && !mnr[q]) ? zero_val<T>() : hv);
+                store_coherent(hxn, hxs, (uint32_t)frag_off(b, pn[q], (H + 31) / 32), (a.dense && !mnr[q]) ? zero_val<T>() : hv);
             if (D.xout && pup[q] >= 0) {
                 const T yv = (vq && !(a.dense && !mup[q])) ? from_f32<T>(hnv[q]) : zero_val<T>();
-                store_coherent((T*)D.xout + (size_t)t * a.xxs, a.xxs, (uint32_t)frag_off(b, pup[q], a.mtiles), yv);
+                store_coherent((T*)D.xout + (size_t)t * a.xxs, a.xxs, (uint32_t)frag_off(b, pup[q], (H + 31) / 32), yv);
             }
         }
         grid_arrive(bar);
@@ -655,11 +637,11 @@ __global__ void __launch_bounds__(1024) k_bwd_persist(PBwdArgs a) {
         const int ul = lane & 15;
         // byte offset of this lane's fragment of tile mt in chunk 0 (out of
         // range for rows past B); chunk c adds c * cbytes
-        const uint32_t cbytes = (uint32_t)(a.mtiles * 512 * sizeof(T));
+        const uint32_t cbytes = (uint32_t)(512 * sizeof(T));
         uint32_t lofs[MT];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            lofs[mt] = m0 + 16 * mt + ul < B ? (uint32_t)(frag_lane_off(0, m0 / 16 + mt, lane, a.mtiles) * sizeof(T)) : OOB_OFF;
+            lofs[mt] = m0 + 16 * mt + ul < B ? (uint32_t)(frag_lane_off(0, m0 / 16 + mt, lane, nch) * sizeof(T)) : OOB_OFF;
         for (int c0 = 0; c0 < nch; c0 += NW * MAXC) {
             Raw8<T> fa[MAXC][MT];
 #pragma unroll
@@ -782,7 +764,7 @@ __global__ void __launch_bounds__(1024) k_bwd_persist(PBwdArgs a) {
             const __amdgpu_buffer_rsrc_t dw = buf_rsrc((const T*)D.da + (size_t)t * das, (uint32_t)(das * sizeof(T)));
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
-                const uint32_t o = (uint32_t)frag_off(b, g * H + u, a.mtiles) * (uint32_t)sizeof(T);
+                const uint32_t o = (uint32_t)frag_off(b, g * H + u, (G + 31) / 32) * (uint32_t)sizeof(T);
                 if constexpr (sizeof(T) == 2)
                     __builtin_amdgcn_raw_buffer_store_b16(from_f32<T>(da4[q][g]), dw, o, 0, CPOL_SC1);
                 else
@@ -833,565 +815,11 @@ __global__ void __launch_bounds__(1024) k_bwd_persist(PBwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Persistent forward recurrence for large batches (Eq. 1-6), one layer (its
-// directions as slots).  At a batch where the row-group tiling of
-// k_fwd_persist does not fit the device at once (each of its workgroups
-// holds a U slice in LDS for every 64 rows), this kernel holds the U slice
-// in registers instead and gives LDS to the reduction:
-//   workgroup = (slot, 16 hidden units = 64 gate columns, 64 batch rows),
-//   512 threads = 8 waves.  Wave w owns the recurrent neurons
-//   [32*KC*w, 32*KC*(w+1)) of the contraction: its B fragments (U rows of
-//   those neurons, the 64 columns of the tile: KC chunks x 4 column tiles)
-//   are loaded once and stay in registers for the whole sequence.  Per step
-//   each wave loads the A fragments of its neuron range for the 64 rows
-//   (every element of h_{t-1} the workgroup needs is loaded by exactly one
-//   wave), forms a 64 x 64 partial product, and the eight partials are
-//   summed through LDS by the threads of the gate pointwise (two
-//   (row, unit) pairs each).
-// h_{t-1} is exchanged uncompacted and multiplied by the step's RH mask at
-// the producer (a dropped neuron contributes an exact zero), so the same
-// kernel serves both modes; rows and neurons past the shape read as zero.
-constexpr int BG_NW = 8, BG_MG = 64, BG_UT = 16, BG_NC = 4 * BG_UT, BG_RP = BG_NC + 4;
-
-template <int KC>
-__global__ void __launch_bounds__(512) k_fwd_big(PFwdArgs a) {
-    constexpr int MT = BG_MG / 16, NTL = BG_NC / 16, NTH = 64 * BG_NW;
-    constexpr int PPT = BG_MG * BG_UT / NTH;   // (row, unit) pairs per thread
-    extern __shared__ __align__(16) char smem[];
-    float* red = (float*)smem;                 // [8 waves][64 rows][BG_RP]
-    const int H = a.H, G = 4 * H, B = a.B, T_ = a.T;
-    const int nslot = a.ntiles * a.mgroups;
-    const int d = blockIdx.x / nslot, rem = blockIdx.x % nslot;
-    const int tile = rem / a.mgroups, mg = rem % a.mgroups;
-    const PFwdDir& D = a.d[d];
-    const int u0 = tile * BG_UT, m0 = mg * BG_MG;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g8 = 8 * (lane >> 4);
-    unsigned* bar = slot_bar(a.bar, d);
-    const int nch = (H + 31) / 32;             // 32-neuron chunks of the contraction
-
-    // B fragments: U rows of this wave's neurons, the tile's 64 columns
-    // (column c of tile j is gate (c&15)>>2 of unit u0 + 4j + (c&3))
-    bf16x8_t ub[KC][NTL];
-    {
-        const bf16* U = (const bf16*)D.U;
-#pragma unroll
-        for (int j = 0; j < NTL; ++j) {
-            const int cl = lane & 15;
-            const int unit = u0 + 4 * j + (cl & 3);
-            const int gcol = (cl >> 2) * H + min(unit, H - 1);
-#pragma unroll
-            for (int c = 0; c < KC; ++c) {
-                const int kb = 32 * (w * KC + c) + g8;
-                s16x8_t f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int k = kb + e;
-                    const bf16 v = U[(size_t)min(k, H - 1) * G + gcol];
-                    f[e] = (short)((k < H && unit < H) ? v : (bf16)0);
-                }
-                ub[c][j] = __builtin_bit_cast(bf16x8_t, f);
-            }
-        }
-    }
-    // this thread's (row, unit) pairs, their state and per-step inputs
-    float creg[PPT], hreg[PPT], gxr[PPT][4];
-    int pb[PPT], pu[PPT], lenr[PPT], mnx[PPT];
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int p = tid + NTH * q;
-        pb[q] = m0 + p / BG_UT;
-        pu[q] = u0 + p % BG_UT;
-        const bool ok = pb[q] < B && pu[q] < H;
-        creg[q] = ok ? D.c0[(size_t)pb[q] * H + pu[q]] : 0.f;
-        hreg[q] = ok ? bf2f(((const bf16*)D.h0)[(size_t)pb[q] * H + pu[q]]) : 0.f;
-        lenr[q] = a.lengths ? a.lengths[min(pb[q], B - 1)] : T_;
-    }
-    auto step_t = [&](int s) { return D.dir == 0 ? s : T_ - 1 - s; };
-    // inputs of step s (clamped, valid addresses): the input product and the
-    // RH mask of the step that consumes h_t
-    auto prefetch = [&](int s) {
-        const int sc = min(s, T_ - 1);
-        const int t = step_t(sc);
-        const int tn = step_t(min(sc + 1, T_ - 1));
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-            const int bc = min(pb[q], B - 1), uc = min(pu[q], H - 1);
-            const float* gp = D.gx + ((size_t)t * B + bc) * G + uc;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) gxr[q][g] = gp[g * H];
-            mnx[q] = D.rh.mask[(size_t)tn * D.rh.kmax + uc];
-        }
-    };
-    const size_t hxs = (size_t)nch * a.mtiles * 512;       // elements per h slot
-    // this lane's A offset in chunk 0 of the wave and row tile 0 of the group
-    const uint32_t a_base = (uint32_t)(frag_lane_off(w * KC, m0 / 16, lane, a.mtiles) * sizeof(bf16));
-    // Rows past the batch inside its last 16-row tile are never written and
-    // only reach outputs of rows past the batch (not stored).  Neurons past H
-    // in the last chunk are never written either and meet zero U rows, so
-    // they are cleared here, in both slots, before the first barrier (a
-    // stale NaN times zero would not vanish): the last unit tile's
-    // workgroups clear them for their rows.
-    if (tile == a.ntiles - 1 && H % 32) {
-        const int npad = 32 * nch - H;
-        for (int i = tid; i < 2 * BG_MG * npad; i += NTH) {
-            const int sl = i / (BG_MG * npad), r = (i / npad) % BG_MG, k = H + i % npad;
-            if (m0 + r < 16 * a.mtiles)
-                xstore((bf16*)D.hx + (size_t)sl * hxs + frag_off(m0 + r, k, a.mtiles), (bf16)0);
-        }
-    }
-    // prologue: h0 times the first step's RH mask into slot 0
-    {
-        const int t0 = step_t(0);
-        bf16* hx0 = (bf16*)D.hx;
-#pragma unroll
-        for (int q = 0; q < PPT; ++q)
-            if (pb[q] < B && pu[q] < H)
-                xstore(hx0 + frag_off(pb[q], pu[q], a.mtiles),
-                       D.rh.mask[(size_t)t0 * D.rh.kmax + pu[q]] ? f2bf(hreg[q]) : (bf16)0);
-    }
-    prefetch(0);
-    grid_arrive(bar);
-
-    for (int s = 0; s < T_; ++s) {
-        const int t = step_t(s);
-        if (!grid_wait(bar, d, nslot, (unsigned)(s + 1), a.err, a.timeout, STATUS_FWD)) break;
-        // ---- h~_{t-1} (this wave's neurons, the tile's rows) times the U slice
-        // A fragments two chunks deep (registers): chunk c+2 is issued as
-        // soon as chunk c has been multiplied.  Offsets: one base register
-        // (copied inside the loop, so the compiler keeps one register rather
-        // than hoisting a register per fragment) plus the chunk; the row tile
-        // is the instruction's immediate (tiles are 1 KB apart).  Chunks past
-        // the last one and row tiles past the last one of the batch read
-        // past the slot (zero) or rows past the batch (whose outputs are not
-        // stored).
-        const __amdgpu_buffer_rsrc_t hr = buf_rsrc((const bf16*)D.hx + (size_t)(s & 1) * hxs,
-                                                   (uint32_t)(hxs * sizeof(bf16)));
-        uint32_t vb;
-        asm volatile("v_mov_b32 %0, %1" : "=v"(vb) : "v"(a_base));
-        auto issue = [&](int c, u32x4_t (&f)[MT]) {
-            const uint32_t vo = vb + (uint32_t)(c * a.mtiles * 1024);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) f[mt] = __builtin_amdgcn_raw_buffer_load_b128(hr, vo + mt * 1024, 0, CPOL_SC1);
-        };
-        u32x4_t fa[2][MT];
-        issue(0, fa[0]);
-        if (KC > 1) issue(1, fa[1]);
-        f32x4_t acc[MT][NTL];
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NTL; ++j) acc[i][j] = f32x4_t{0, 0, 0, 0};
-#pragma unroll
-        for (int c = 0; c < KC; ++c) {
-            u32x4_t (&f)[MT] = fa[c & 1];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const bf16x8_t av = __builtin_bit_cast(bf16x8_t, f[mt]);
-#pragma unroll
-                for (int j = 0; j < NTL; ++j)
-                    acc[mt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, ub[c][j], acc[mt][j], 0, 0, 0);
-            }
-            if (c + 2 < KC) issue(c + 2, f);
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int j = 0; j < NTL; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    red[(w * BG_MG + mt * 16 + acc_row(lane, r)) * BG_RP + j * 16 + (lane & 15)] = acc[mt][j][r];
-        __syncthreads();
-        // ---- pointwise (Eq. 1-6); h_t goes out first, masked for the next step
-        bf16* hxn = (bf16*)D.hx + (size_t)((s + 1) & 1) * hxs;
-        float og4[PPT][4], cnv[PPT], hnv[PPT];
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-            const int p = tid + NTH * q;
-            const int rr = p / BG_UT, uu = p % BG_UT;
-            const int cb = (uu >> 2) * 16 + (uu & 3);
-            float pre[4];
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                float v = 0.f;
-#pragma unroll
-                for (int i = 0; i < BG_NW; ++i) v += red[(i * BG_MG + rr) * BG_RP + cb + 4 * g];
-                pre[g] = D.s_rh * v + gxr[q][g];
-            }
-            og4[q][0] = sigmoid_fast(pre[0]);
-            og4[q][1] = sigmoid_fast(pre[1]);
-            og4[q][2] = tanh_fast(pre[2]);
-            og4[q][3] = sigmoid_fast(pre[3]);
-            cnv[q] = og4[q][1] * creg[q] + og4[q][0] * og4[q][2];
-            hnv[q] = og4[q][3] * tanh_fast(cnv[q]);
-            if (pb[q] < B && pu[q] < H && s + 1 < T_) {
-                const bool vq = t < lenr[q];
-                xstore(hxn + frag_off(pb[q], pu[q], a.mtiles), mnx[q] ? f2bf(vq ? hnv[q] : hreg[q]) : (bf16)0);
-            }
-        }
-        grid_arrive(bar);
-        // outputs only later kernels read, and the next step's inputs
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-            const int b = pb[q], u = pu[q];
-            if (b >= B || u >= H) continue;
-            const bool vq = t < lenr[q];
-            const float cn = vq ? cnv[q] : creg[q], hn = hnv[q];
-            const bf16 hv = f2bf(vq ? hn : hreg[q]);
-            *(float4*)(D.gates + ((size_t)t * B + b) * G + 4 * u) = make_float4(og4[q][0], og4[q][1], og4[q][2], og4[q][3]);
-            D.cres[((size_t)t * B + b) * H + u] = cn;
-            if (vq) { creg[q] = cnv[q]; hreg[q] = hn; }
-            ((bf16*)D.hrecT)[((size_t)t * H + u) * a.BP + b] = hv;
-            if (D.y) D.y[((size_t)t * B + b) * a.ldy + u] = vq ? hn : 0.0f;
-            if (D.ybuf) {
-                const bf16 yv = vq ? f2bf(hn) : (bf16)0;
-                ((bf16*)D.ybuf)[((size_t)t * B + b) * a.ldy + u] = yv;
-                ((bf16*)D.ybufT)[((size_t)t * a.ldy + u) * a.BP + b] = yv;
-            }
-        }
-        prefetch(s + 1);
-    }
-    // ---- final state (NaN if a barrier wait timed out, and then every step of y)
-    const bool failed = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        if (pb[q] < B && pu[q] < H) {
-            D.hT[(size_t)pb[q] * H + pu[q]] = failed ? __builtin_nanf("") : hreg[q];
-            D.cT[(size_t)pb[q] * H + pu[q]] = failed ? __builtin_nanf("") : creg[q];
-            if (failed && D.y)
-                for (int t = 0; t < T_; ++t) D.y[((size_t)t * B + pb[q]) * a.ldy + pu[q]] = __builtin_nanf("");
-        }
-    }
-    grid_exit(a.bar, a.nslots, a.err);
-}
-
-// ---------------------------------------------------------------------------
-// Persistent BPTT for large batches (Eq. 7-10), one layer.  The recurrent
-// gradient of a step, dh_{t-1} = (DA_t U^T) * m * s, is a product over the
-// 4H gate columns; at a large batch it runs split over the gate columns so
-// that every workgroup keeps a 128-unit x 512-column block of U in
-// registers:
-//   phase A (pointwise, Eq. 7-9): workgroup = (16 units, 64 rows); sums the
-//     partial gradients of the step before over the column groups, forms
-//     DA_t of its tile and publishes it;
-//   phase B (product, Eq. 10): workgroup = (64 rows, unit group of 128,
-//     column group of 512); each wave multiplies 4 of the group's 16
-//     column chunks for 64 of its units, the four column quarters are
-//     summed through LDS and the group's partial [B][H] is published.
-// Two grid barriers per step; partial sums are added in a fixed order.
-constexpr int BB_NW = 8, BB_MG = 64, BB_UT = 16, BB_UG = 128, BB_KG = 512, BB_RP = BB_UG + 4;
-
-__global__ void __launch_bounds__(512) k_bwd_big(PBwdArgs a) {
-    constexpr int MT = BB_MG / 16, NTH = 64 * BB_NW, KC = 4, NTL = 4;
-    constexpr int PPT = BB_MG * BB_UT / NTH;   // (row, unit) pairs per thread in phase A
-    extern __shared__ __align__(16) char smem[];
-    float* red = (float*)smem;                 // phase B: [4 column quarters][64 rows][BB_RP]
-    const int H = a.H, G = 4 * H, B = a.B, T_ = a.T;
-    const int nslot = gridDim.x;               // one slot (one direction per launch)
-    const PBwdDir& D = a.d[0];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int g8 = 8 * (lane >> 4);
-    unsigned* bar = slot_bar(a.bar, 0);
-    const size_t das = (size_t)((G + 31) / 32) * a.mtiles * 512;   // fragment-major DA block per step
-    const int nchG = (G + 31) / 32;
-
-    // ---- phase A role: (unit tile, row group)
-    const int nA = a.ntiles * a.mgroups;
-    const bool roleA = (int)blockIdx.x < nA;
-    const int tA = blockIdx.x / a.mgroups, mA = blockIdx.x % a.mgroups;
-    const int u0 = tA * BB_UT, mA0 = mA * BB_MG;
-    // ---- phase B role: (row group, unit group, column group)
-    const int nB = a.mgroups * a.ngu * a.ngk;
-    const bool roleB = (int)blockIdx.x < nB;
-    const int rgB = blockIdx.x % a.mgroups, ugB = (blockIdx.x / a.mgroups) % a.ngu,
-              kgB = blockIdx.x / (a.mgroups * a.ngu);
-    const int mB0 = rgB * BB_MG;
-    const int kq = w >> 1, ch = w & 1;         // this wave's column quarter and unit half
-
-    // U block in registers: B fragment (chunk c, unit tile j) of this wave:
-    // contraction = gate columns, output columns = units
-    bf16x8_t ub[KC][NTL];
-    {
-        const bf16* U = (const bf16*)D.U;
-#pragma unroll
-        for (int j = 0; j < NTL; ++j) {
-            const int u = BB_UG * ugB + 16 * (NTL * ch + j) + (lane & 15);
-#pragma unroll
-            for (int c = 0; c < KC; ++c) {
-                const int n0 = BB_KG * kgB + 32 * (KC * kq + c) + g8;
-                s16x8_t f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int n = n0 + e;
-                    const bf16 v = U[(size_t)min(u, H - 1) * G + min(n, G - 1)];
-                    f[e] = (short)((roleB && u < H && n < G) ? v : (bf16)0);
-                }
-                ub[c][j] = __builtin_bit_cast(bf16x8_t, f);
-            }
-        }
-    }
-    // phase A pairs and their carries: pair p = tid + 512q is row p/16 of
-    // the group, unit p%16 of the tile (16 lanes on 16 adjacent units)
-    float dcs[PPT], dhc[PPT];
-    int pb[PPT], pu[PPT], lenr[PPT];
-#pragma unroll
-    for (int q = 0; q < PPT; ++q) {
-        const int p = tid + NTH * q;
-        pb[q] = roleA ? mA0 + p / BB_UT : B;
-        pu[q] = u0 + p % BB_UT;
-        const bool ok = pb[q] < B && pu[q] < H;
-        dhc[q] = (ok && D.dhT) ? D.dhT[(size_t)pb[q] * H + pu[q]] : 0.f;
-        dcs[q] = (ok && D.dcT) ? D.dcT[(size_t)pb[q] * H + pu[q]] : 0.f;
-        lenr[q] = a.lengths ? a.lengths[min(pb[q], B - 1)] : T_;
-    }
-    auto step_t = [&](int s) { return D.dir == 0 ? T_ - 1 - s : s; };
-    // per-step inputs of phase A (clamped addresses), one step ahead
-    float gt4[PPT][4], ctv[PPT], cpv[PPT], dyv[PPT];
-    int mkr[PPT];
-    auto prefetch = [&](int s) {
-        const int t = step_t(min(s, T_ - 1));
-        const int tp = D.dir == 0 ? t - 1 : t + 1;        // forward predecessor of t
-        const int tn = step_t(max(s - 1, 0));              // the step processed before
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-            const int bc = min(pb[q], B - 1), uc = min(pu[q], H - 1);
-            const float4 gr = *(const float4*)(D.gates + ((size_t)t * B + bc) * G + 4 * uc);
-            gt4[q][0] = gr.x; gt4[q][1] = gr.y; gt4[q][2] = gr.z; gt4[q][3] = gr.w;
-            ctv[q] = D.cres[((size_t)t * B + bc) * H + uc];
-            cpv[q] = *(s >= T_ - 1 ? D.c0 + (size_t)bc * H + uc : D.cres + ((size_t)tp * B + bc) * H + uc);
-            if (D.dy) {
-                dyv[q] = D.dy[((size_t)t * B + bc) * a.ldy + uc];
-            } else if (D.dxc) {
-                const int dp = D.dxpos[(size_t)t * a.kmax + uc];
-                dyv[q] = dp >= 0 ? D.dxc[((size_t)t * B + bc) * a.lddx + dp] : 0.0f;
-            } else {
-                dyv[q] = 0.0f;
-            }
-            mkr[q] = D.rh.mask[(size_t)tn * a.kmax + uc];
-        }
-    };
-    // this lane's A offset in the wave's first chunk and the group's first
-    // row tile (chunks past 4H read past the block: zero)
-    const uint32_t a_base = (uint32_t)(frag_lane_off((BB_KG / 32) * kgB + KC * kq, mB0 / 16, lane, a.mtiles) *
-                                       sizeof(bf16));
-
-    prefetch(0);
-    bool ok = true;
-    // hidden sizes in multiples of 8: DA goes out as whole 16-byte pieces
-    const bool wide = (H & 7) == 0;
-    for (int s = 0; s <= T_; ++s) {
-        const bool final_pass = s == T_;
-        const int t = final_pass ? -1 : step_t(s);
-        // ---- phase A: the partial recurrent gradients of the step before
-        // (phase B of iteration s-1) are complete after 2s arrivals
-        if (s > 0 && !(ok = grid_wait(bar, 0, nslot, (unsigned)(2 * s), a.err, a.timeout, STATUS_BWD))) break;
-        // the recurrent gradients of the thread's pairs: the partial sums of
-        // the column groups, 8 groups' loads of both pairs in flight at once
-        // (absent groups read group 0; clamped addresses: the results of
-        // pairs outside the batch or the layer are not used), added in group
-        // order
-        float rg[PPT] = {0.f, 0.f};
-        if (s > 0) {
-            for (int k0 = 0; k0 < a.ngk; k0 += 8) {
-                float pv[PPT][8];
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const float* pk = a.part + (size_t)(k0 + k < a.ngk ? k0 + k : 0) * B * H;
-#pragma unroll
-                    for (int q = 0; q < PPT; ++q)
-                        pv[q][k] = xload1(pk + (size_t)min(pb[q], B - 1) * H + min(pu[q], H - 1));
-                }
-#pragma unroll
-                for (int k = 0; k < 8; ++k)
-#pragma unroll
-                    for (int q = 0; q < PPT; ++q)
-                        if (k0 + k < a.ngk) rg[q] += pv[q][k];
-            }
-        }
-        float da4[PPT][4];
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) da4[q][g] = 0.f;
-            // (copies the compiler cannot hoist: the addresses derived from
-            // them are recomputed per step instead of occupying registers)
-            int b = pb[q], u = pu[q];
-            asm volatile("" : "+v"(b), "+v"(u));
-            if (b >= B || u >= H) continue;
-            float dh = dhc[q];
-            // units dropped at the step before get no recurrent gradient (Eq. 10)
-            if (s > 0 && mkr[q]) dh += D.s_rh * rg[q];
-            if (final_pass) {
-                D.dh0[(size_t)b * H + u] = dh;
-                D.dc0[(size_t)b * H + u] = dcs[q];
-                continue;
-            }
-            if (t < lenr[q]) {
-                dh += dyv[q];
-                const float ig = gt4[q][0], fg = gt4[q][1], gg = gt4[q][2], og = gt4[q][3];
-                const float tc = tanh_fast(ctv[q]);
-                const float dout = dh * tc;                            // Eq. 7
-                const float dc = dh * og * (1.0f - tc * tc) + dcs[q];  // Eq. 7
-                da4[q][0] = dc * gg * ig * (1.0f - ig);                // Eq. 9, sigmoid'
-                da4[q][1] = dc * cpv[q] * fg * (1.0f - fg);            // Eq. 8, sigmoid'
-                da4[q][2] = dc * ig * (1.0f - gg * gg);                // Eq. 9, tanh'
-                da4[q][3] = dout * og * (1.0f - og);                   // Eq. 7, sigmoid'
-                dcs[q] = dc * fg;                                      // Eq. 8
-                dhc[q] = 0.0f;
-            } else {
-                dhc[q] = dh;                                           // frozen row: pass through
-            }
-            if (!wide) {
-                bf16* dar = (bf16*)D.da + (size_t)t * das;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) xstore(dar + frag_off(b, g * H + u, a.mtiles), f2bf(da4[q][g]));
-            }
-        }
-        if (final_pass) break;
-        if (wide && roleA) {
-            // DA_t of the tile through LDS ([64 rows][4 gates x 16 units]),
-            // published as 16-byte pieces: 8 adjacent units of one gate and
-            // row are one piece of the fragment-major block
-            bf16* st = (bf16*)red;
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-                const int p = tid + NTH * q;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) st[(p / BB_UT) * 64 + g * BB_UT + p % BB_UT] = f2bf(da4[q][g]);
-            }
-            __syncthreads();
-            const int rr = tid >> 3, g = (tid >> 1) & 3, h = tid & 1;
-            const int b = mA0 + rr, uh = u0 + 8 * h;
-            if (b < B && uh < H) {
-                const __amdgpu_buffer_rsrc_t dw = buf_rsrc((const bf16*)D.da + (size_t)t * das, (uint32_t)(das * 2));
-                const u32x4_t v = *(const u32x4_t*)(st + rr * 64 + g * BB_UT + 8 * h);
-                __builtin_amdgcn_raw_buffer_store_b128(v, dw, (uint32_t)(frag_off(b, g * H + uh, a.mtiles) * 2), 0, CPOL_SC1);
-            }
-        }
-        grid_arrive(bar);                                  // DA_t is published (arrival 2s+1)
-        // DA^T (the weight gradients' operand) through LDS: the tile's
-        // [4 gates x 16 units][64 rows] block, written as 16-byte row pieces
-        if (roleA) {
-            bf16* st = (bf16*)red;
-#pragma unroll
-            for (int q = 0; q < PPT; ++q) {
-                const int p = tid + NTH * q;
-                const bool okp = pb[q] < B && pu[q] < H;
-#pragma unroll
-                for (int g = 0; g < 4; ++g) st[(g * BB_UT + p % BB_UT) * BB_MG + p / BB_UT] = f2bf(okp ? da4[q][g] : 0.f);
-            }
-            __syncthreads();
-            constexpr int PPR = BB_MG * 2 / 16;            // 16-byte pieces of a staged row
-            bf16* dat = (bf16*)D.daT + (size_t)t * G * a.BP;
-            for (int i = tid; i < 4 * BB_UT * PPR; i += NTH) {
-                const int r = i / PPR, pc = i % PPR;
-                const int u = u0 + r % BB_UT, col = mA0 + pc * 8;
-                if (u < H && col < a.BP)
-                    *(uint4*)(dat + (size_t)((r / BB_UT) * H + u) * a.BP + col) = *(const uint4*)(st + r * BB_MG + pc * 8);
-            }
-        }
-        // ---- phase B: every DA_t tile is published after 2s+1 arrivals
-        if (!(ok = grid_wait(bar, 0, nslot, (unsigned)(2 * s + 1), a.err, a.timeout, STATUS_BWD))) break;
-        if (roleB) {
-            // A fragments (DA_t rows of the group, this wave's column quarter)
-            // two chunks deep; offsets as in the large-batch forward
-            const __amdgpu_buffer_rsrc_t dr = buf_rsrc((const bf16*)D.da + (size_t)t * das,
-                                                       (uint32_t)(das * sizeof(bf16)));
-            uint32_t vb;
-            asm volatile("v_mov_b32 %0, %1" : "=v"(vb) : "v"(a_base));
-            auto issue = [&](int c, u32x4_t (&f)[MT]) {
-                const uint32_t vo = vb + (uint32_t)(c * a.mtiles * 1024);
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    f[mt] = __builtin_amdgcn_raw_buffer_load_b128(dr, vo + mt * 1024, 0, CPOL_SC1);
-            };
-            u32x4_t fa[2][MT];
-            issue(0, fa[0]);
-            issue(1, fa[1]);
-            f32x4_t acc[MT][NTL];
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int j = 0; j < NTL; ++j) acc[i][j] = f32x4_t{0, 0, 0, 0};
-#pragma unroll
-            for (int c = 0; c < KC; ++c) {
-                u32x4_t (&f)[MT] = fa[c & 1];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const bf16x8_t av = __builtin_bit_cast(bf16x8_t, f[mt]);
-#pragma unroll
-                    for (int j = 0; j < NTL; ++j)
-                        acc[mt][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, ub[c][j], acc[mt][j], 0, 0, 0);
-                }
-                if (c + 2 < KC) issue(c + 2, f);
-            }
-            // (the DA^T staging of phase A is done with the LDS area: every
-            // thread passed the barrier wait above after its stores)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int j = 0; j < NTL; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        red[(kq * BB_MG + mt * 16 + acc_row(lane, r)) * BB_RP + 64 * ch + 16 * j + (lane & 15)] =
-                            acc[mt][j][r];
-            __syncthreads();
-            float* pk = a.part + (size_t)kgB * B * H;
-            if ((H & 3) == 0) {                // four adjacent units, one 16-byte coherent store
-                const __amdgpu_buffer_rsrc_t pr = buf_rsrc(pk, (uint32_t)((size_t)B * H * 4));
-                for (int i = tid; i < BB_MG * BB_UG / 4; i += NTH) {
-                    const int rr = i / (BB_UG / 4), uu = 4 * (i % (BB_UG / 4));
-                    const int b = mB0 + rr, u = BB_UG * ugB + uu;
-                    if (b < B && u < H) {
-                        float4 v = *(const float4*)(red + (size_t)rr * BB_RP + uu);
-#pragma unroll
-                        for (int k = 1; k < 4; ++k) {
-                            const float4 x = *(const float4*)(red + (size_t)(k * BB_MG + rr) * BB_RP + uu);
-                            v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
-                        }
-                        const u32x4_t o = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z),
-                                           __float_as_uint(v.w)};
-                        __builtin_amdgcn_raw_buffer_store_b128(o, pr, (uint32_t)(((size_t)b * H + u) * 4), 0, CPOL_SC1);
-                    }
-                }
-            } else {
-                for (int i = tid; i < BB_MG * BB_UG; i += NTH) {
-                    const int rr = i / BB_UG, uu = i % BB_UG;
-                    const int b = mB0 + rr, u = BB_UG * ugB + uu;
-                    if (b < B && u < H) {
-                        float v = 0.f;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) v += red[(k * BB_MG + rr) * BB_RP + uu];
-                        xstore(pk + (size_t)b * H + u, v);
-                    }
-                }
-            }
-        }
-        grid_arrive(bar);                                  // the partials are published (arrival 2s+2)
-        prefetch(s + 1);                                   // (in flight during the next wait)
-    }
-    // a timed-out barrier, here or in the forward pass of the step, poisons
-    // the input-state gradients
-    if (!ok || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-        __hip_atomic_load(sync_status(a.err), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-#pragma unroll
-        for (int q = 0; q < PPT; ++q)
-            if (pb[q] < B && pu[q] < H) {
-                D.dh0[(size_t)pb[q] * H + pu[q]] = __builtin_nanf("");
-                D.dc0[(size_t)pb[q] * H + pu[q]] = __builtin_nanf("");
-            }
-    }
-    grid_exit(a.bar, 1, a.err);
-}
-
-// ---------------------------------------------------------------------------
 // Host side.
 
 // Checks (once per device, kernel and LDS size) that nwg workgroups of the
 // kernel can be resident at once; sets the dynamic LDS limit on first use.
-static hipError_t resident_limit(const void* fn, int threads, size_t lds, int nwg) {
+hipError_t resident_limit(const void* fn, int threads, size_t lds, int nwg) {
     struct Entry { int dev; const void* fn; size_t lds; int max_wg; };
     static std::vector<Entry> cache;
     static std::mutex mu;
@@ -1424,7 +852,7 @@ static hipError_t resident_limit(const void* fn, int threads, size_t lds, int nw
 // products); keep lists at kofs; then the reduction area.  Returns the size.
 size_t fwd_persist_lds(int H, int NT, int MG, int esize, int KP, int kin_max, bool w_beside_u, size_t* wofs,
                        size_t* kofs) {
-    const size_t cols = esize == 2 ? (size_t)fwd_ncp(NT) : (size_t)16 * NT;   // bf16: K-major, padded rows
+    const size_t cols = (size_t)16 * NT;
     const size_t us = (cols * fwd_hp(H) * esize + 15) & ~(size_t)15;
     const size_t ws = (cols * KP * esize + 15) & ~(size_t)15;
     *wofs = w_beside_u ? us : 0;
@@ -1460,27 +888,6 @@ hipError_t launch_fwd_persist(PFwdArgs& a, hipStream_t st, int kid_timer_on, hip
 }
 
 template hipError_t launch_fwd_persist<float>(PFwdArgs&, hipStream_t, int, hipEvent_t, hipEvent_t);
-template hipError_t launch_fwd_persist<bf16>(PFwdArgs&, hipStream_t, int, hipEvent_t, hipEvent_t);
-
-// The large-batch forward (bf16): returns an error before anything is
-// enqueued when the shape is outside its register budget or the grid does
-// not fit the device at once.
-hipError_t launch_fwd_big(PFwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1) {
-    const int KC = a.H <= 512 ? 2 : a.H <= 1024 ? 4 : 0;
-    if (!KC || a.nslots > 2) return hipErrorInvalidValue;
-    a.ntiles = (a.H + BG_UT - 1) / BG_UT;
-    a.mgroups = (a.B + BG_MG - 1) / BG_MG;
-    const int nwg = a.nslots * a.ntiles * a.mgroups;
-    const size_t lds = (size_t)BG_NW * BG_MG * BG_RP * sizeof(float);
-    void (*fn)(PFwdArgs) = KC == 2 ? k_fwd_big<2> : k_fwd_big<4>;
-    hipError_t e = resident_limit((const void*)fn, 64 * BG_NW, lds, nwg);
-    if (e != hipSuccess) return e;
-    if (timer_on) (void)hipEventRecord(e0, st);
-    hipLaunchKernelGGL(fn, dim3(nwg), dim3(64 * BG_NW), lds, st, a);
-    e = hipGetLastError();
-    if (timer_on && e == hipSuccess) (void)hipEventRecord(e1, st);
-    return e;
-}
 
 size_t bwd_persist_lds(int H, int UB, int MG, int esize) {
     const size_t G = 4 * (size_t)H, GP = (G + 31) / 32 * 32 + 8;
@@ -1510,53 +917,17 @@ hipError_t launch_bwd_persist(PBwdArgs& a, hipStream_t st, int timer_on, hipEven
     const int nwg = a.nslots * a.ntiles * a.mgroups;
     if (a.nslots > 8) return hipErrorInvalidValue;
     if (timer_on) (void)hipEventRecord(e0, st);
-    // chunks per wave per round: 128 VGPRs at 1024 threads hold 6 bf16
-    // rounds of 32-row fragments (3 f32), 2 of 64-row ones (1 f32)
-    const int nch = (4 * a.H + 31) / 32, per_wave = (nch + PB_NW - 1) / PB_NW;
+    // chunks per wave per round: 128 VGPRs at 1024 threads hold 3 of 32-row
+    // fragments, 1 of 64-row ones
     hipError_t e;
-    if constexpr (sizeof(T) == 4) {
-        if (UB == 16) e = MG == 32 ? launch_bwd_persist_t<T, 16, 32, 3>(a, nwg, lds, st)
-                                   : launch_bwd_persist_t<T, 16, 64, 1>(a, nwg, lds, st);
-        else e = MG == 32 ? launch_bwd_persist_t<T, 8, 32, 3>(a, nwg, lds, st)
-                          : launch_bwd_persist_t<T, 8, 64, 1>(a, nwg, lds, st);
-    } else if (MG == 64) {
-        e = UB == 16 ? launch_bwd_persist_t<T, 16, 64, 2>(a, nwg, lds, st)
-                     : launch_bwd_persist_t<T, 8, 64, 2>(a, nwg, lds, st);
-    } else if (per_wave <= 2) {
-        e = UB == 16 ? launch_bwd_persist_t<T, 16, 32, 2>(a, nwg, lds, st)
-                     : launch_bwd_persist_t<T, 8, 32, 2>(a, nwg, lds, st);
-    } else if (per_wave <= 4) {
-        e = UB == 16 ? launch_bwd_persist_t<T, 16, 32, 4>(a, nwg, lds, st)
-                     : launch_bwd_persist_t<T, 8, 32, 4>(a, nwg, lds, st);
-    } else {
-        e = UB == 16 ? launch_bwd_persist_t<T, 16, 32, 6>(a, nwg, lds, st)
-                     : launch_bwd_persist_t<T, 8, 32, 6>(a, nwg, lds, st);
-    }
+    if (UB == 16) e = MG == 32 ? launch_bwd_persist_t<T, 16, 32, 3>(a, nwg, lds, st)
+                               : launch_bwd_persist_t<T, 16, 64, 1>(a, nwg, lds, st);
+    else e = MG == 32 ? launch_bwd_persist_t<T, 8, 32, 3>(a, nwg, lds, st)
+                      : launch_bwd_persist_t<T, 8, 64, 1>(a, nwg, lds, st);
     if (timer_on && e == hipSuccess) (void)hipEventRecord(e1, st);
     return e;
 }
 
 template hipError_t launch_bwd_persist<float>(PBwdArgs&, hipStream_t, int, hipEvent_t, hipEvent_t);
-template hipError_t launch_bwd_persist<bf16>(PBwdArgs&, hipStream_t, int, hipEvent_t, hipEvent_t);
-
-// The large-batch backward (bf16, one direction per launch): returns an
-// error before anything is enqueued when the grid does not fit the device.
-hipError_t launch_bwd_big(PBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1) {
-    if (a.nslots != 1) return hipErrorInvalidValue;
-    a.ntiles = (a.H + BB_UT - 1) / BB_UT;
-    a.mgroups = (a.B + BB_MG - 1) / BB_MG;
-    a.ngu = (a.H + BB_UG - 1) / BB_UG;
-    a.ngk = (4 * a.H + BB_KG - 1) / BB_KG;
-    const int nA = a.ntiles * a.mgroups, nB = a.mgroups * a.ngu * a.ngk;
-    const int nwg = nA > nB ? nA : nB;
-    const size_t lds = (size_t)4 * BB_MG * BB_RP * sizeof(float);
-    hipError_t e = resident_limit((const void*)k_bwd_big, 64 * BB_NW, lds, nwg);
-    if (e != hipSuccess) return e;
-    if (timer_on) (void)hipEventRecord(e0, st);
-    hipLaunchKernelGGL(k_bwd_big, dim3(nwg), dim3(64 * BB_NW), lds, st, a);
-    e = hipGetLastError();
-    if (timer_on && e == hipSuccess) (void)hipEventRecord(e1, st);
-    return e;
-}
 
 }  // namespace lsd
