@@ -25,13 +25,14 @@ template <typename T> void launch_step(const StepArgs& a, int D, hipStream_t st)
 template <typename T> void launch_bwd(const BwdArgs& a, int D, hipStream_t st);
 template <typename T> void launch_dx(const DxArgs& a, int K, hipStream_t st);
 template <typename T> void launch_wgrad(const WgBatch& b, hipStream_t st);
+void launch_wgrad_bf16(WrBatch& b, hipStream_t st);
 void launch_bwd_init(const float*, const float*, float*, float*, long, void*, int, int, int, long, long, unsigned*, int*,
                      hipStream_t);
 void launch_emb_grad(const int32_t*, int, int, int, const float*, const SiteView&, int, float*, hipStream_t);
 void launch_case1_drop(int, int, const void*, void*, uint8_t*, int, int, int, uint64_t, uint64_t, uint64_t, uint64_t,
                        float, hipStream_t);
 void launch_case1_undrop(const float*, const uint8_t*, float*, long, float, hipStream_t);
-template <typename T> void launch_head_prep(const float*, void*, void*, int, int, int, int, hipStream_t);
+template <typename T> void launch_head_prep(const float*, void*, void*, const SiteView&, int, int, int, int, int, hipStream_t);
 void launch_ce_loss(const float*, const int32_t*, const int32_t*, int, int, int, float*, float*, float*, float*, float*,
                     hipStream_t);
 template <typename T>
@@ -52,7 +53,6 @@ hipError_t launch_fwd_res(RFwdArgs& a, hipStream_t st, int timer_on, hipEvent_t 
 hipError_t launch_bwd_res(RBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1);
 double fwd_res_cost(int B, int H, int nslots);
 double bwd_res_cost(int B, int H, int nslots);
-bool wgrad_big_fits(int B);
 int kernel_timer_start(const char* name);
 int kernel_timer_stop(double* total_ms, int64_t* launches);
 
@@ -123,7 +123,8 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     q.das = (size_t)((q.G + 31) / 32) * q.mtiles * 512;   // DA block per step: fragment-major [B][4H]
     q.hxs = (size_t)((q.H + 31) / 32) * q.mtiles * 512;
     q.xxs = (size_t)((q.D * q.H + 31) / 32) * q.mtiles * 512;
-    q.MGc = (q.B + 63) / 64;
+    q.IP = (q.I + 7) / 8 * 8;
+    q.DHP = (q.D * q.H + 7) / 8 * 8;
     q.sites = q.L + q.L * q.D;
     q.kin_max = q.L > 1 ? (q.I > q.D * q.H ? q.I : q.D * q.H) : q.I;
     q.kmax = q.kin_max > q.H ? q.kin_max : q.H;
@@ -144,14 +145,16 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     off = 0;
     q.r_gates = off; off = align_up(off + T * B * G * 4, A);
     q.r_c = off;     off = align_up(off + T * B * H * 4, A);
-    q.r_hrecT = off; off = align_up(off + T * H * BP * es, A);
+    const bool b16 = es == 2, xt = !b16 || B >= 64;   // (bf16: transposed inputs feed the large-batch products only)
+    q.r_hrecT = off; off = align_up(off + (b16 ? T * B * (size_t)q.HP : T * H * BP) * es, A);
     q.r_dir_bytes = off;
     off = (size_t)q.L * D * q.r_dir_bytes;
-    q.r_xT = off;    off = align_up(off + T * (size_t)q.I * BP * es, A);
-    q.r_h0T = off;   off = align_up(off + (size_t)q.L * D * H * BP * es, A);
+    q.r_xT = off;    off = align_up(off + (xt ? T * (size_t)q.I * BP * es : 0), A);
+    q.r_xm = off;    off = align_up(off + (b16 ? T * B * (size_t)q.IP * es : 0), A);
+    q.r_h0T = off;   off = align_up(off + (b16 ? 0 : (size_t)q.L * D * H * BP * es), A);
     q.r_ybuf_base = off;
-    q.r_ybufT_off = align_up(T * B * D * H * es, A);
-    q.r_ybuf_bytes = q.r_ybufT_off + align_up(T * D * H * BP * es, A);
+    q.r_ybufT_off = align_up(T * B * (b16 ? (size_t)q.DHP : D * H) * es, A);
+    q.r_ybuf_bytes = q.r_ybufT_off + align_up(xt ? T * D * H * BP * es : 0, A);
     q.r_total = q.r_ybuf_base + (size_t)(q.L - 1) * q.r_ybuf_bytes;
 
     off = 0;
@@ -163,8 +166,12 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     const size_t fwd = off;
     off = 0;
     const size_t NR = D > (size_t)q.L ? D : (size_t)q.L;   // DA regions: per direction, or per layer of a stack
-    q.w_da = off;     off = align_up(off + NR * T * (size_t)q.das * es, A);
-    q.w_daT = off;    off = align_up(off + NR * T * G * BP * es, A);
+    // bf16: a region per (layer, direction) (one weight-gradient launch per
+    // pass) where that takes no more than a region per direction or stacked
+    // layer and its transpose, as fp32 has them
+    q.da_regs = b16 && (size_t)q.L * D * q.das <= NR * (q.das + G * BP) ? q.L * (int)D : (int)NR;
+    q.w_da = off;     off = align_up(off + (size_t)q.da_regs * T * (size_t)q.das * es, A);
+    q.w_daT = off;    off = align_up(off + (b16 ? 0 : NR * T * G * BP * es), A);
     q.w_dxw = off;    off = align_up(off + (size_t)(q.L - 1) * T * B * H * 4, A);
     q.w_dc = off;     off = align_up(off + D * B * H * 4, A);
     q.w_dhc = off;    off = align_up(off + D * B * H * 4, A);
@@ -187,21 +194,6 @@ static bool use_stacked() {
 // LSTM_SD_FWD_WORKERS=0: a stacked fp32 forward without input-product workers
 static bool use_fwd_workers() {
     const char* v = getenv("LSTM_SD_FWD_WORKERS");
-    return !(v && v[0] == '0');
-}
-
-// The large-batch row-sparse weight gradient (bf16, LSTM_SD_WGRAD_GEMM=0) runs
-// from 128 rows.  LSTM_SD_BIG=0: never; LSTM_SD_BIG=2: from 64 rows (tests of its
-// tiling on ragged shapes).
-static int big_mode() {
-    const char* v = getenv("LSTM_SD_BIG");
-    return (v && v[0] == '0') ? 0 : (v && v[0] == '2') ? 2 : 1;
-}
-static bool use_big() { return big_mode() != 0; }
-// LSTM_SD_WGRAD_BIG=0: the weight gradients of a large batch on the
-// small-batch kernel
-static bool use_wgrad_big() {
-    const char* v = getenv("LSTM_SD_WGRAD_BIG");
     return !(v && v[0] == '0');
 }
 
@@ -316,18 +308,28 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
     const size_t es = P.esize;
     char* R = (char*)reserve;
     char* W = (char*)ws;
-    // x (T matrices) and h0 (L*D matrices) transposed, and the pass
-    // initialised (hT, cT, barrier counters): these ride on the first input
+    // x (T matrices) and h0 (L*D matrices) as the weight gradients read them
+    // (fp32: transposed; bf16: masked), and the pass initialised (hT, cT, barrier counters): these ride on the first input
     // product launch (independent work, one launch less)
     TransArgs tr;
     memset(&tr, 0, sizeof(tr));
     tr.src = x; tr.dst = R + P.r_xT; tr.B = B; tr.K = P.I; tr.BP = BP; tr.n1 = T;
     tr.src2 = h0; tr.dst2 = R + P.r_h0T; tr.K2 = H;
+    const bool b16 = std::is_same<E, bf16>::value;
+    // large batches (bf16): the input products read the transposed inputs
+    const bool gemm_big = b16 && B >= 64 && use_gemm_big();
+    if (b16) {
+        if (!gemm_big) tr.dst = nullptr;
+        tr.dst2 = nullptr;
+        tr.xm = R + P.r_xm; tr.ldm = P.IP;
+        tr.mask = site_view(P, mbuf, P.site_nr(0)).mask;
+        tr.hm = R + P.rdir(0, 0) + P.r_hrecT; tr.hm_stride = P.r_dir_bytes; tr.ldh = P.HP; tr.D = D;
+        tr.mask2 = site_view(P, mbuf, P.site_rh(0, 0)).mask;
+        tr.kmax = P.kmax;
+    }
     tr.h0 = h0; tr.c0 = c0; tr.hT = hT; tr.cT = cT; tr.n_init = (long)L * D * B * H;
     tr.bar = (unsigned*)(W + P.w_sync); tr.err = (int*)(W + P.w_sync + SYNC_ERR_OFS);
     bool tr_pending = true;
-    // large batches (bf16): the input products read the transposed inputs
-    const bool gemm_big = std::is_same<E, bf16>::value && B >= 64 && use_gemm_big();
     auto attach_tr = [&](FxArgs& f) {
         if (!tr_pending) return;
         f.tr = tr;
@@ -381,7 +383,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
         for (int d = 0; d < D; ++d) {
             FxArgs f;
             memset(&f, 0, sizeof(f));
-            f.X = X; f.ldx = kin;
+            f.X = X; f.ldx = b16 && l > 0 ? P.DHP : kin;
             f.W = w->W[l * D + d];
             f.bias = w->b[l * D + d];
             f.site = site_view(P, mbuf, P.site_nr(l));
@@ -448,7 +450,8 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
         ra.bar = (unsigned*)(W + P.w_sync);
         ra.err = (int*)(W + P.w_sync + SYNC_ERR_OFS);
         ra.timeout = barrier_timeout_ticks();
-        ra.B = B; ra.H = H; ra.T = T; ra.BP = BP; ra.ldy = D * H; ra.kmax = P.kmax; ra.mtiles = P.mtiles;
+        ra.B = B; ra.H = H; ra.T = T; ra.BP = BP; ra.ldy = D * H; ra.ldyb = P.DHP; ra.ldh = P.HP; ra.kmax = P.kmax;
+        ra.mtiles = P.mtiles;
         int n = 0;
         for (int l = l0; l < l0 + nl; ++l) {
             int wk = -1;
@@ -472,20 +475,20 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
                 x.c0 = c0 + (size_t)k * B * H;
                 x.rmask = site_view(P, mbuf, P.site_rh(l, d)).mask;
                 x.hx = W + P.w_hx + (size_t)(nl > 1 ? l : d) * 2 * P.hxs * es;
+                if (l + 1 < L) x.umask = site_view(P, mbuf, P.site_nr(l + 1)).mask + d * H;
                 if (l + 1 < l0 + nl) {
-                    x.umask = site_view(P, mbuf, P.site_nr(l + 1)).mask;
                     x.xout = W + P.w_xx + (size_t)l * T * P.xxs * es;
                 }
                 x.gates = (float*)(rd + P.r_gates);
                 x.cres = (float*)(rd + P.r_c);
-                x.hrecT = rd + P.r_hrecT;
+                x.hm = rd + P.r_hrecT;
                 x.hT = hT + (size_t)k * B * H;
                 x.cT = cT + (size_t)k * B * H;
                 if (l == L - 1) {
                     x.y = y + d * H;
                 } else {
                     x.ybuf = R + P.rybuf(l) + (size_t)d * H * es;
-                    x.ybufT = R + P.rybufT(l) + (size_t)d * H * BP * es;
+                    if (gemm_big && l + 1 == l0 + nl) x.ybufT = R + P.rybufT(l) + (size_t)d * H * BP * es;
                 }
             }
         }
@@ -533,6 +536,8 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
             StepArgs a;
             memset(&a, 0, sizeof(a));
             a.lengths = lengths; a.B = B; a.H = H; a.ldy = D * H; a.BP = BP; a.dense = !P.compact; a.s = P.s_rh[l];
+            a.ldyb = b16 ? P.DHP : D * H;
+            a.ldh = P.HP;
             for (int d = 0; d < D; ++d) {
                 const int k = l * D + d;
                 const int t = d == 0 ? s : T - 1 - s;
@@ -543,7 +548,16 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
                 sd.hprev = s == 0 ? (const void*)((const char*)h0 + (size_t)k * B * H * es)
                                   : (const void*)(hrec2 + (size_t)((s - 1) & 1) * B * P.HP * es);
                 sd.hrec = hrec2 + (size_t)(s & 1) * B * P.HP * es;
-                sd.hrecT = rd + P.r_hrecT + (size_t)t * H * BP * es;
+                if (b16) {
+                    const int tn = d == 0 ? t + 1 : t - 1;
+                    if (s + 1 < T) {
+                        sd.hm = rd + P.r_hrecT + (size_t)tn * B * P.HP * es;
+                        sd.hmask = site_view(P, mbuf, P.site_rh(l, d)).mask + (size_t)tn * P.kmax;
+                    }
+                    if (l + 1 < L) sd.ymask = site_view(P, mbuf, P.site_nr(l + 1)).mask + (size_t)t * P.kmax + d * H;
+                } else {
+                    sd.hrecT = rd + P.r_hrecT + (size_t)t * H * BP * es;
+                }
                 sd.U = w->U[k];
                 sd.gx = (const float*)(W + P.w_gx) + ((size_t)d * T + t) * B * G;
                 const SiteView sv = site_view(P, mbuf, P.site_rh(l, d));
@@ -557,8 +571,8 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
                 if (l == L - 1) {
                     sd.y = y + (size_t)t * B * D * H + d * H;
                 } else {
-                    sd.ybuf = R + P.rybuf(l) + ((size_t)t * B * D * H + d * H) * es;
-                    sd.ybufT = R + P.rybufT(l) + ((size_t)t * D * H + d * H) * BP * es;
+                    sd.ybuf = R + P.rybuf(l) + ((size_t)t * B * a.ldyb + d * H) * es;
+                    if (!b16 || gemm_big) sd.ybufT = R + P.rybufT(l) + ((size_t)t * D * H + d * H) * BP * es;
                 }
             }
             launch_step<E>(a, D, st);
@@ -583,7 +597,11 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
     // DA and DA^T regions: one per direction, or one per layer when a
     // unidirectional stack runs in one launch
     auto da_of = [&](int reg) { return W + P.w_da + (size_t)reg * T * P.das * es; };
-    auto daT_of = [&](int reg) { return W + P.w_daT + (size_t)reg * T * G * BP * es; };
+    auto daT_of = [&](int reg) { return W + P.w_daT + (size_t)reg * T * G * BP * es; };   // (f32)
+    constexpr bool b16 = std::is_same<E, bf16>::value;
+    // (bf16) every (layer, direction) has a region of its own: its reg0
+    const bool all_da = b16 && P.da_regs == L * D;
+    auto reg_of = [&](int l) { return all_da ? l * D : 0; };
     auto common_args = [&](PBwdArgs& pa) {
         memset(&pa, 0, sizeof(pa));
         pa.lengths = lengths;
@@ -623,10 +641,10 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
         ra.bar = sync_bar;
         ra.err = sync_err;
         ra.timeout = barrier_timeout_ticks();
-        ra.B = B; ra.H = H; ra.T = T; ra.BP = BP; ra.kmax = P.kmax; ra.mtiles = P.mtiles;
+        ra.B = B; ra.H = H; ra.T = T; ra.kmax = P.kmax; ra.mtiles = P.mtiles;
         int n = 0;
         for (int l = l1; l >= l0; --l) {
-            const int reg = l1 > l0 ? l : 0;  // DA regions: per layer of a stack, or per direction
+            const int reg = l1 > l0 ? l : reg_of(l);   // DA regions: per layer of a stack, or as planned
             int wk = -1;
             if (l < l1) {                     // (a stack) the worker forming dx of layer l+1: slot n, that layer n - 1
                 RBwdSlot& x = ra.d[n];
@@ -653,7 +671,6 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
                 x.dhT = dhT ? dhT + (size_t)k * B * H : nullptr;
                 x.dcT = dcT ? dcT + (size_t)k * B * H : nullptr;
                 x.da = da_of(reg + d);
-                x.daT = daT_of(reg + d);
                 x.dh0 = dh0 + (size_t)k * B * H;
                 x.dc0 = dc0 + (size_t)k * B * H;
             }
@@ -687,20 +704,45 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
     };
     // weight and bias gradients (Eq. 11) of layer l: its problems join one
     // batch (row-sparse and full problems alike), one launch per batch
-    WgBatch b;
+    WgBatch b;                                // (fp32)
     b.np = 0;
     b.status = sync_status;
-    b.big = std::is_same<E, bf16>::value && wgrad_big_fits(B) && use_big() && (B >= 128 || big_mode() == 2) &&
-            use_wgrad_big();
+    WrBatch wr;
+    wr.np = 0;
+    wr.status = sync_status;
+    wr.B = B; wr.T = T; wr.R = T * B; wr.G = G; wr.das = (long)P.das;
+    auto flush_wgrad = [&]() {
+        if constexpr (b16) launch_wgrad_bf16(wr, st);
+        else launch_wgrad<E>(b, st);
+        wr.np = b.np = 0;
+    };
     auto add_wgrad = [&](const WgArgs& a) {
-        if (b.np == WG_MAXP) {                 // full: launch it (its DA is complete)
-            launch_wgrad<E>(b, st);
-            b.np = 0;
-        }
+        if (b.np == WG_MAXP) flush_wgrad();    // full: launch it (its DA is complete)
         b.p[b.np++] = a;
     };
     auto layer_wgrad = [&](int l, int reg0) {
         const int kin = P.kin(l);
+        if constexpr (b16) {
+            for (int d = 0; d < D; ++d) {
+                const int k = l * D + d;
+                if (wr.np + 2 > WR_MAXP) flush_wgrad();
+                WrProblem& a = wr.p[wr.np++];
+                a.A = l == 0 ? (const void*)(R + P.r_xm) : (const void*)(R + P.rybuf(l - 1));
+                a.lda = l == 0 ? P.IP : P.DHP;
+                a.da = da_of(reg0 + d);
+                a.out = g->dW[k];
+                a.db = g->db[k];              // the bias gradient rides on the input-weight product
+                a.K = kin; a.s = P.s_nr[l];
+                WrProblem& u = wr.p[wr.np++];
+                u.A = R + P.rdir(l, d) + P.r_hrecT;
+                u.lda = P.HP;
+                u.da = a.da;
+                u.out = g->dU[k];
+                u.db = nullptr;
+                u.K = H; u.s = P.s_rh[l];
+            }
+            return;
+        }
         const SiteView nv = site_view(P, mbuf, P.site_nr(l));
         const void* XT = l == 0 ? (const void*)(R + P.r_xT) : (const void*)(R + P.rybufT(l - 1));
         for (int d = 0; d < D; ++d) {
@@ -729,10 +771,6 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
             u.full = P.p_rh[l] == 0.0 || !P.compact;
             add_wgrad(u);
         }
-    };
-    auto flush_wgrad = [&]() {
-        launch_wgrad<E>(b, st);
-        b.np = 0;
     };
 
     // Unidirectional stack: every layer's BPTT in one persistent launch, with
@@ -798,7 +836,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
         if (!res || l == L - 1)
             launch_bwd_init(dhT ? dhT + (size_t)l * D * B * H : nullptr, dcT ? dcT + (size_t)l * D * B * H : nullptr,
                         dhc, dcs, (long)D * B * H, l == L - 1 ? (void*)(W + P.w_da) : nullptr, (int)es, G,
-                        P.mtiles, (long)D * T, (long)P.das, sync_bar, sync_err, st);
+                        P.mtiles, (long)(all_da ? L * D : D) * T, (long)P.das, sync_bar, sync_err, st);
         float* dxc_above = (float*)(W + P.w_dxc) + (size_t)((l + 1) & 1) * T * B * P.kin_max;
         float* dxc_here = (float*)(W + P.w_dxc) + (size_t)(l & 1) * T * B * P.kin_max;
         bool persistent_done = false;
@@ -852,7 +890,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
                 bd.dhc = dhc + (size_t)d * B * H;
                 bd.dcs = dcs + (size_t)d * B * H;
                 if (s > 0) {
-                    bd.da_next = (char*)da_of(d) + (size_t)tn * P.das * es;
+                    bd.da_next = (char*)da_of(reg_of(l) + d) + (size_t)tn * P.das * es;
                     bd.nmask = rv.mask + (size_t)tn * P.kmax;
                     bd.nkeep = rv.keep + (size_t)tn * P.kmax;
                     bd.ncount = rv.count + tn;
@@ -876,14 +914,14 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
                     bd.dxc = dxc_above + (size_t)t * B * a.lddx;
                     bd.dxpos = sv.pos + (size_t)t * P.kmax + d * H;
                 }
-                bd.da = (char*)da_of(d) + (size_t)t * P.das * es;
-                bd.daT = (char*)daT_of(d) + (size_t)t * G * BP * es;
+                bd.da = (char*)da_of(reg_of(l) + d) + (size_t)t * P.das * es;
+                if (!b16) bd.daT = (char*)daT_of(d) + (size_t)t * G * BP * es;
             }
             launch_bwd<E>(a, D, st);
         }
-        if (l > 0 || dx) layer_dx(l, 0, dxc_here);
-        layer_wgrad(l, 0);
-        flush_wgrad();                        // before the next layer reuses the DA regions
+        if (l > 0 || dx) layer_dx(l, reg_of(l), dxc_here);
+        layer_wgrad(l, reg_of(l));
+        if (!all_da || l == 0) flush_wgrad(); // (else before the next layer reuses the DA regions)
     }
     return hip_check("backward launch");
 }
@@ -895,7 +933,7 @@ using namespace lsd;
 // ---------------------------------------------------------------------------
 // Output head (pre-FC output dropout, FC layer, softmax cross-entropy).
 struct HeadPlan {
-    int F, V, B, T, dtype, compact, sid, BP, mtiles;
+    int F, FP, V, B, T, dtype, compact, sid, BP, mtiles;   // FP: row pitch of yb
     double p;
     float s;
     size_t esize, das;
@@ -929,6 +967,7 @@ static int make_head_plan(const lstm_sd_head_dims* d, HeadPlan* p, const char** 
     q.F = d->features; q.V = d->vocab; q.B = d->batch; q.T = d->seq_len; q.dtype = d->dtype;
     q.compact = d->compact; q.sid = d->stream_id; q.p = d->p_out; q.s = inv_keep(d->p_out);
     q.esize = es;
+    q.FP = es == 2 ? (q.F + 7) / 8 * 8 : q.F;
     q.BP = (q.B + 31) / 32 * 32;
     q.mtiles = (q.B + 15) / 16;
     q.das = (size_t)((q.V + 31) / 32) * q.mtiles * 512;
@@ -944,10 +983,10 @@ static int make_head_plan(const lstm_sd_head_dims* d, HeadPlan* p, const char** 
     q.m_dseg = off;   off = align_up(off + T * 17 * 4, A);
     q.m_total = off;
     off = 0;
-    q.w_yb = off;      off = align_up(off + T * B * F * es, A);
-    q.w_ybT = off;     off = align_up(off + T * F * BP * es, A);
+    q.w_yb = off;      off = align_up(off + T * B * (size_t)q.FP * es, A);
+    q.w_ybT = off;     off = align_up(off + (es == 4 ? T * F * BP * es : 0), A);
     q.w_da = off;      off = align_up(off + T * q.das * es, A);
-    q.w_daT = off;     off = align_up(off + T * V * BP * es, A);
+    q.w_daT = off;     off = align_up(off + (es == 4 ? T * V * BP * es : 0), A);
     q.w_lse = off;     off = align_up(off + T * B * 4, A);
     q.w_rowloss = off; off = align_up(off + T * B * 4, A);
     q.w_rowok = off;   off = align_up(off + T * B * 4, A);
@@ -988,6 +1027,16 @@ static void head_backward_impl(const HeadPlan& P, const void* W_fc, const int32_
     a.T = P.T; a.K = P.F; a.tps = ((P.F + 7) / 8 + 15) / 16; a.mtiles = P.mtiles;
     a.dense = !P.compact; a.s = P.s;
     launch_dx<E>(a, P.F, st);
+    if constexpr (std::is_same<E, bf16>::value) {
+        WrBatch wr;
+        memset(&wr, 0, sizeof(wr));
+        wr.np = 1; wr.B = P.B; wr.T = P.T; wr.R = P.T * P.B; wr.G = P.V; wr.das = (long)P.das;
+        WrProblem& g = wr.p[0];
+        g.A = W + P.w_yb; g.lda = P.FP; g.da = W + P.w_da;
+        g.out = dW; g.db = db; g.K = P.F; g.s = P.s;
+        launch_wgrad_bf16(wr, st);
+        return;
+    }
     WgBatch b;
     memset(&b, 0, sizeof(b));
     b.np = 1;
@@ -998,7 +1047,7 @@ static void head_backward_impl(const HeadPlan& P, const void* W_fc, const int32_
     g.dense = !P.compact; g.s = P.s;
     g.out = dW; g.db = db;
     g.full = P.p == 0.0 || !P.compact;
-    launch_wgrad<E>(b, st);
+    launch_wgrad<float>(b, st);
 }
 
 extern "C" {
@@ -1194,13 +1243,13 @@ int lstm_sd_head_forward(const lstm_sd_head_dims* hd, const void* W_fc, const fl
     char* W = (char*)workspace;
     FxArgs f;
     memset(&f, 0, sizeof(f));
-    f.X = W + P.w_yb; f.ldx = P.F; f.W = W_fc; f.K = P.F; f.bias = b_fc; f.site = head_site(P, mask_buf);
+    f.X = W + P.w_yb; f.ldx = P.FP; f.W = W_fc; f.K = P.F; f.bias = b_fc; f.site = head_site(P, mask_buf);
     f.Gx = logits; f.B = P.B; f.G = P.V; f.T = P.T; f.dense = !P.compact; f.s = P.s;
     if (P.dtype == LSTM_SD_DTYPE_BF16) {
-        launch_head_prep<bf16>(y, W + P.w_yb, W + P.w_ybT, P.T, P.B, P.F, P.BP, st);
+        launch_head_prep<bf16>(y, W + P.w_yb, nullptr, f.site, P.T, P.B, P.F, P.BP, P.FP, st);
         launch_fx<bf16>(f, st);
     } else {
-        launch_head_prep<float>(y, W + P.w_yb, W + P.w_ybT, P.T, P.B, P.F, P.BP, st);
+        launch_head_prep<float>(y, W + P.w_yb, W + P.w_ybT, f.site, P.T, P.B, P.F, P.BP, P.FP, st);
         launch_fx<float>(f, st);
     }
     return hip_check("head forward launch");

@@ -8,7 +8,10 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <stdlib.h>
+
 #include <algorithm>
+#include <type_traits>
 
 #include "device.h"
 #include "kernels.h"
@@ -16,234 +19,6 @@
 
 namespace lsd {
 
-
-// ---------------------------------------------------------------------------
-// Weight gradient for large batches, Eq. 11:
-//   dW[k][n] = s * sum_t sum_{b} act_t[b][k] da_t[b][n]
-// over the steps t at which row k is kept (row-sparse), or every step with
-// the mask as a multiplier (the dense comparison mode); rows never kept are
-// 0.  grid (row slices of 128 x column blocks of 128, 1, problems), 512
-// threads (8 waves); workgroup i runs on XCD i % 8, which takes the column
-// blocks x, x+8, ... with every row slice, so one XCD's L2 holds its
-// columns' DA^T of a step once for all of its slices.
-// At each step the kept rows of the slice are listed in ascending order (a
-// ballot over the mask bytes), and the contraction over the batch runs in
-// chunks of 64 batch rows: the chunk of the listed rows of act_t^T ([K][BP])
-// and of the block's 128 columns of DA_t^T ([G][BP]) are staged in LDS as
-// [row][64+8] tiles (whole 16-byte pieces of each row), double buffered,
-// with the loads issued two chunks ahead across step boundaries.  The
-// step's product (listed rows x 128 columns) is tiled in 16x16 MFMA tiles:
-// wave w takes the columns 32*(w%4) .. +31 and the row tiles w/4, w/4+2,
-// .. (those past the listed count are skipped), and at the end of the step
-// adds its tiles into the slice's rows of an LDS accumulator (the rows of
-// one step are distinct; the positions past the count go to a spare row).
-// Slice 0 also sums the bias gradient.  One launch covers every problem of
-// a pass.
-constexpr int WL_R = 128, WL_C = 128, WL_KC = 64, WL_P = WL_KC + 8, WL_LDC = WL_C + 4;
-constexpr size_t WL_LDS = (size_t)(WL_R + 1) * WL_LDC * 4 + (size_t)2 * (WL_R + WL_C) * WL_P * 2 +
-                          (size_t)4 * 2 * WL_R * 4 + 64;
-
-__global__ void __launch_bounds__(512) k_wgrad_big(WgBatch bt) {
-    extern __shared__ __align__(16) char smem[];
-    const WgArgs& a = bt.p[blockIdx.z];
-    const int nrs = (a.K + WL_R - 1) / WL_R, ncb = (a.G + WL_C - 1) / WL_C;
-    const int xcd = blockIdx.x % 8, k8 = blockIdx.x / 8;
-    const int rs = k8 % nrs, cb = xcd + 8 * (k8 / nrs);
-    if (cb >= ncb) return;
-    const int r0 = rs * WL_R, nrow = min(WL_R, a.K - r0), n0 = cb * WL_C;
-    float* acc_lds = (float*)smem;                                        // [WL_R + 1][WL_LDC]
-    bf16* As = (bf16*)(smem + (size_t)(WL_R + 1) * WL_LDC * 4);           // [2][WL_R][WL_P]
-    bf16* Bs = As + 2 * WL_R * WL_P;                                      // [2][WL_C][WL_P]
-    int* lrow = (int*)(Bs + 2 * WL_C * WL_P);                             // [4][WL_R] rows to load (-1: zero)
-    int* trow = lrow + 4 * WL_R;                                          // [4][WL_R] accumulator rows
-    int* lcount = trow + 4 * WL_R;                                        // [4]
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int B = a.B, G = a.G, T_ = a.T;
-    const int nb = (B + WL_KC - 1) / WL_KC, nq = T_ * nb;               // chunks per step, in all
-    const bool failed = bt.status && *bt.status != 0;
-    for (int i = tid; i < (WL_R + 1) * WL_LDC; i += 512) acc_lds[i] = 0.0f;
-
-    // the row list of step t into ring slot t % 4 (wave 0; mask bytes of
-    // the step in mk0 / mk1): compact mode lists the kept rows of the slice
-    // in ascending order, then -1 (loaded as zero, added into the spare
-    // row); dense mode lists every row, a dropped one loaded as zero
-    auto mask_load = [&](int t, uint32_t& mk0, uint32_t& mk1) {
-        const uint8_t* mrow = a.site.mask + (size_t)min(t, T_ - 1) * a.site.kmax + r0;
-        mk0 = mrow[min(lane, nrow - 1)];
-        mk1 = mrow[min(lane + 64, nrow - 1)];
-    };
-    auto build = [&](int t, uint32_t mk0, uint32_t mk1) {
-        int* lr = lrow + (t & 3) * WL_R;
-        int* tr = trow + (t & 3) * WL_R;
-        const bool k0 = t < T_ && lane < nrow && mk0 != 0;
-        const bool k1 = t < T_ && lane + 64 < nrow && mk1 != 0;
-        if (a.dense) {
-            lr[lane] = k0 ? r0 + lane : -1;
-            lr[lane + 64] = k1 ? r0 + 64 + lane : -1;
-            tr[lane] = lane < nrow ? lane : WL_R;
-            tr[lane + 64] = lane + 64 < nrow ? lane + 64 : WL_R;
-            if (lane == 0) lcount[t & 3] = t < T_ ? nrow : 0;
-            return;
-        }
-        const uint64_t b0 = __builtin_amdgcn_ballot_w64(k0), b1 = __builtin_amdgcn_ballot_w64(k1);
-        const int c0 = __popcll(b0), n = c0 + __popcll(b1);
-        const int i0 = __builtin_amdgcn_mbcnt_hi((uint32_t)(b0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b0, 0));
-        const int i1 = c0 + __builtin_amdgcn_mbcnt_hi((uint32_t)(b1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)b1, 0));
-        if (k0) { lr[i0] = r0 + lane; tr[i0] = lane; }
-        if (k1) { lr[i1] = r0 + 64 + lane; tr[i1] = 64 + lane; }
-        if (n + lane < WL_R) { lr[n + lane] = -1; tr[n + lane] = WL_R; }
-        if (n + 64 + lane < WL_R) { lr[n + 64 + lane] = -1; tr[n + 64 + lane] = WL_R; }
-        if (lane == 0) lcount[t & 3] = n;
-    };
-    auto act_ptr = [&](int t) {
-        return (a.actT_first && t == a.t_first) ? (const bf16*)a.actT_first
-                                                : (const bf16*)a.actT + (long)(t + a.shift) * a.tstride;
-    };
-    // lists are built three steps ahead: with one chunk per step the loads
-    // of step t+2 go out during step t, before its list would otherwise be
-    // built
-    uint32_t mk0 = 0, mk1 = 0;
-    if (w == 0) {
-        for (int t = 0; t < 3; ++t) {
-            mask_load(t, mk0, mk1);
-            build(t, mk0, mk1);
-        }
-        mask_load(3, mk0, mk1);                                           // (step 3's, built at step 0)
-    }
-    __syncthreads();
-
-    // staging of chunk q = t * nb + c: thread -> (row slot tid/8 + 64i,
-    // 16-byte piece tid%8) of A and of B; batch entries past B are zeroed
-    const int sr = tid >> 3, sp = tid & 7;
-    u32x4_t ra[2][2], rb[2][2];
-    float dbacc[2] = {0.0f, 0.0f};
-    const bool dbw = a.db && rs == 0;
-    auto fetch = [&](int set, int q) {
-        const bool live = q < nq;
-        const int t = live ? q / nb : T_ - 1, c = live ? q % nb : 0;
-        const int bq = WL_KC * c + 8 * sp;                                // first batch entry of the piece
-        const __amdgpu_buffer_rsrc_t ar = buf_rsrc(act_ptr(t), (uint32_t)((size_t)a.K * a.BP * 2));
-        const __amdgpu_buffer_rsrc_t br = buf_rsrc((const bf16*)a.daT + (size_t)t * G * a.BP,
-                                                   (uint32_t)((size_t)G * a.BP * 2));
-        const int* lr = lrow + (t & 3) * WL_R;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r = lr[sr + 64 * i];
-            const uint32_t oa = (live && r >= 0 && bq < B) ? (uint32_t)((size_t)r * a.BP + bq) * 2 : OOB_OFF;
-            ra[set][i] = __builtin_amdgcn_raw_buffer_load_b128(ar, oa, 0, 0);
-            const int n = n0 + sr + 64 * i;
-            const uint32_t ob = (live && n < G && bq < B) ? (uint32_t)((size_t)n * a.BP + bq) * 2 : OOB_OFF;
-            rb[set][i] = __builtin_amdgcn_raw_buffer_load_b128(br, ob, 0, 0);
-        }
-    };
-    auto commit = [&](int set, int buf, int q) {
-        const int c = q % nb;
-        const int bq = WL_KC * c + 8 * sp;
-        uint32_t m[4];
-        pad_mask<bf16>(bq, B, m);                                         // (batch entries past B)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            u32x4_t x = ra[set][i], y = rb[set][i];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { x[e] &= m[e]; y[e] &= m[e]; }
-            *(u32x4_t*)(As + ((size_t)buf * WL_R + sr + 64 * i) * WL_P + 8 * sp) = x;
-            *(u32x4_t*)(Bs + ((size_t)buf * WL_C + sr + 64 * i) * WL_P + 8 * sp) = y;
-            if (dbw && q < nq) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) dbacc[i] += __uint_as_float(y[e] << 16) + __uint_as_float(y[e] & 0xffff0000u);
-            }
-        }
-    };
-
-    f32x4_t acc[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x4_t{0, 0, 0, 0};
-    const int mw = w >> 2, cw = 32 * (w & 3);
-    const int cl = lane & 15, g8 = 8 * (lane >> 4);
-    int cnt = lcount[0];                                                  // rows of the current step
-    fetch(0, 0);
-    fetch(1, 1);
-    commit(0, 0, 0);
-    __syncthreads();
-    // chunk q (LDS buffer cur = q % 2): the loads of q+2 go out, then the
-    // products; at the first chunk of a step wave 0 lists the rows of step
-    // t+3 (ring slot (t+3) % 4, whose step t-1 is done), at the last the
-    // step's tiles go into the accumulator
-    auto chunk = [&](int q, int cur) {
-        fetch(cur, q + 2);
-        __builtin_amdgcn_sched_barrier(0);     // (the loads go out before anything waits)
-        const int t = q / nb, c = q % nb;
-        if (c == 0 && w == 0) {
-            build(t + 3, mk0, mk1);
-            mask_load(t + 4, mk0, mk1);
-        }
-        const bf16* Ab = As + (size_t)cur * WL_R * WL_P;
-        const bf16* Bb = Bs + (size_t)cur * WL_C * WL_P;
-#pragma unroll
-        for (int ks = 0; ks < WL_KC / 32; ++ks) {
-            Raw8<bf16> fb[2];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) raw_lds(fb[j], Bb + (size_t)(cw + 16 * j + cl) * WL_P + 32 * ks + g8);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int mt = mw + 2 * i;
-                if (16 * mt >= cnt) break;                                // (uniform) row tiles past the list
-                Raw8<bf16> fa;
-                raw_lds(fa, Ab + (size_t)(16 * mt + cl) * WL_P + 32 * ks + g8);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) raw_mma(fa, fb[j], acc[i][j]);
-            }
-        }
-        if (c == nb - 1) {
-            // the step's tiles into their rows: every wave's additions of
-            // the step before are complete (a barrier ends every chunk)
-            const int* tr = trow + (t & 3) * WL_R;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int mt = mw + 2 * i;
-                if (16 * mt >= cnt) break;
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        float* d = acc_lds + (size_t)tr[16 * mt + acc_row(lane, r)] * WL_LDC + cw + 16 * j + cl;
-                        *d += a.s * acc[i][j][r];
-                    }
-                    acc[i][j] = f32x4_t{0, 0, 0, 0};
-                }
-            }
-        }
-        commit(cur ^ 1, cur ^ 1, q + 1);
-        __syncthreads();
-        if (c == nb - 1) cnt = lcount[(t + 1) & 3];
-    };
-    int q = 0;
-    for (; q + 1 < nq; q += 2) {
-        chunk(q, 0);
-        chunk(q + 1, 1);
-    }
-    if (q < nq) chunk(q, 0);
-    __syncthreads();
-    const float nan = __builtin_nanf("");
-    for (int i = tid; i < nrow * WL_C; i += 512) {
-        const int r = i / WL_C, c = i % WL_C;
-        if (n0 + c < G) a.out[(size_t)(r0 + r) * G + n0 + c] = failed ? nan : acc_lds[r * WL_LDC + c];
-    }
-    if (dbw) {
-        // the 8 threads of a column slot hold its partial sums over their pieces
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            float v = dbacc[i];
-            v += __shfl_xor(v, 1);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 4);
-            const int n = n0 + sr + 64 * i;
-            if (sp == 0 && n < G) a.db[n] = failed ? nan : v;
-        }
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Forward input product for large batches (Eq. 1-4 input term; Sec. 3.2 FP
@@ -540,237 +315,246 @@ void launch_dx_big(const DxArgs& a, hipStream_t st, hipEvent_t e0, hipEvent_t e1
     else k_dx_big<<<grid, blk, DB_LDS, st>>>(a);
 }
 
-size_t wgrad_big_lds() { return WL_LDS; }
+// ---------------------------------------------------------------------------
+// Weight gradients (bf16), Eq. 11, every problem of a pass in one launch: a plain
+// matrix product per problem over the T*B (step, batch) rows,
+//   out[k][n] = s * sum_r A[r][k] da[r][n],
+// with A row-major and already masked by its producer (a dropped neuron's column
+// is zero at that step, so the row sparsity of Eq. 11 holds: never-kept rows are
+// exact zeros) and da the published fragment-major DA blocks, read where the
+// recurrence left them.  Both operands are staged with the contraction (rows)
+// outermost and their fragments come from transposing LDS reads, so no transposed
+// copy of either is ever written: those copies cost the backward recurrence 2.4 us
+// of a 7.7 us step at batch 256, padded every step's contraction to 32 rows, and
+// took a pass over the input of their own.  Rows of successive steps share a
+// 32-row chunk.
+// A workgroup of WM x WN waves computes a TM x TN tile (a wave MI x NI MFMA
+// tiles) with its accumulators in registers over all rows.  Two LDS buffers; the
+// loads of a chunk go out two chunks before it is staged, and the one barrier per
+// chunk waits for LDS only.  Tiles of 256 x 256 (one workgroup per CU) read the
+// fewest bytes per product; 128 x 128 and 64 x 128 fill the chip when a pass has
+// few of those.  Against the kernels before (a step's rows padded to 32, transposed
+// operands, 128 x 256 tiles): batch 256 x hidden 1024 826 -> 565 us, AWD 277 -> 116,
+// LM-large 151 -> 83, LM-medium 38 -> 27, vocabulary head at batch 64 189 -> 105 us.  Workgroup i runs on XCD i % 8, which takes a contiguous range of
+// (problem, column block, row block): an XCD's L2 holds its columns' DA for all
+// their row blocks.
+template <int WM, int WN, int MI, int NI>
+struct WrShape {
+    static constexpr int NW = WM * WN, NTH = 64 * NW, TM = WM * MI * 16, TN = WN * NI * 16;
+    static constexpr int AP = TM + 16, BP = TN + 16;                 // row pitches (32 bytes past a whole bank row)
+    static constexpr size_t LDS = (size_t)2 * 32 * (AP + BP) * 2;
+};
 
-// The large-batch weight gradient takes any batch (its loads run two
-// 64-row groups ahead); it pays off from a few groups per step on.
-bool wgrad_big_fits(int B) { return B >= 64; }
-
-// Weight gradient for large batches as one GEMM per problem, Eq. 11 with
-// every row multiplied by its mask byte (a dropped row contributes an exact
-// zero; identity keep lists need no mask):
-//   dW[k][n] = s * sum over (t, b) of m_t[k] act_t[b][k] da_t[b][n]
-// The contraction runs over all T*B (step, batch) pairs, so each
-// workgroup's accumulators stay in registers for the whole pass: no per-step
-// read-modify-write of an LDS accumulator (the row-sparse kernel above pays
-// one for every kept row at every step, and at 256 rows per step that,
-// with its per-step chain, holds it to about 10% of MFMA peak).
-// grid (8 x row blocks x ceil(column blocks / 8), 1, problems), 512 threads;
-// workgroup = 128 rows x 256 columns; workgroup i runs on XCD i % 8, which
-// takes the column blocks i % 8 + 8j with every row block, so an XCD's L2
-// holds its columns' DA^T for all of its row blocks.  Wave w owns rows
-// 64 (w / 4) .. +63 and columns 64 (w % 4) .. +63 of the tile (4 x 4 MFMA
-// tiles).  The contraction goes in chunks of 32 batch rows of one step: the
-// chunk's 128 activation rows and 256 DA^T columns are loaded once (one or
-// two 16-byte pieces per thread), stored fragment-major in LDS and read by
-// the waves that need them.  Loads run up to five chunks ahead (register
-// ring), three stage buffers rotate (a chunk is staged two chunks before it
-// is multiplied), and each wave reads the fragments of the next chunk from
-// LDS while it multiplies the current one; one barrier per chunk.  The workgroups of the
-// last row block also sum the bias gradient.
-constexpr int WM_R = 128, WM_C = 256, WM_KC = 32, WM_RING = 3;
-constexpr size_t WM_STAGE = (size_t)(WM_R + WM_C) * WM_KC * 2;    // one stage buffer: 24 KB
-constexpr size_t WM_LDS = 3 * WM_STAGE;
-
-__global__ void __launch_bounds__(512) k_wgrad_gemm(WgBatch bt) {
+template <int WM, int WN, int MI, int NI>
+__global__ void __launch_bounds__(64 * WM * WN, 2) k_wgrad_rows(WrBatch bt) {
+    using S = WrShape<WM, WN, MI, NI>;
+    constexpr int NTH = S::NTH, NW = S::NW, TM = S::TM, TN = S::TN, AP = S::AP, BPITCH = S::BP;
+    constexpr int PA = TM * 4 / NTH, NBLK = TN / 16, PB = NBLK / NW;  // pieces: A per thread; 16x32 blocks of da per wave
+    static_assert(PA * NTH == TM * 4 && PB * NW == NBLK, "whole pieces");
     extern __shared__ __align__(16) char smem[];
-    const WgArgs& a = bt.p[blockIdx.z];
-    const int nrb = (a.K + WM_R - 1) / WM_R, ncb = (a.G + WM_C - 1) / WM_C;
-    const int xcd = blockIdx.x % 8, k8 = blockIdx.x / 8;
-    const int rb = k8 % nrb, cb = xcd + 8 * (k8 / nrb);
-    if (cb >= ncb) return;
-    const int r0 = rb * WM_R, n0 = cb * WM_C;
+    bf16* As = (bf16*)smem;                                          // [2][32][AP]
+    bf16* Bs = As + 2 * 32 * AP;                                     // [2][32][BPITCH]
+    int pos = (int)(blockIdx.x % 8) * bt.per + (int)(blockIdx.x / 8), pi = 0;
+    if (pos >= bt.total) return;
+    while (pos >= bt.p[pi].tiles) pos -= bt.p[pi++].tiles;
+    const WrProblem& a = bt.p[pi];
+    const int cb = pos / a.nrb, rb = pos % a.nrb;
+    const int r0 = rb * TM, n0 = cb * TN, G = bt.G, B = bt.B, R = bt.R;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = w >> 2, wc = w & 3;
-    const bool dbw = a.db && rb == nrb - 1;
+    const int wm = w / WN, wn = w % WN;
+    const bool dbw = a.db && rb == a.nrb - 1;
     if (bt.status && *bt.status != 0) {        // the step's recurrence timed out: NaN in every output
         const float nan = __builtin_nanf("");
-        for (int i = tid; i < WM_R * WM_C; i += 512) {
-            const int r = r0 + i / WM_C, n = n0 + i % WM_C;
-            if (r < a.K && n < a.G) a.out[(size_t)r * a.G + n] = nan;
+        for (int i = tid; i < TM * TN; i += NTH) {
+            const int r = r0 + i / TN, n = n0 + i % TN;
+            if (r < a.K && n < G) a.out[(size_t)r * G + n] = nan;
         }
         if (dbw)
-            for (int n = n0 + tid; n < min(n0 + WM_C, a.G); n += 512) a.db[n] = nan;
+            for (int n = n0 + tid; n < min(n0 + TN, G); n += NTH) a.db[n] = nan;
         return;
     }
-    const bool masked = a.dense || !a.full;    // rows times the mask byte
-    const int nb = (a.B + WM_KC - 1) / WM_KC, nq = a.T * nb;
-    const uint32_t abytes = (uint32_t)a.K * a.BP * 2, bbytes = (uint32_t)a.G * a.BP * 2;
-    // staging pieces of this thread: activation row j, DA^T columns j and
-    // j + 128, batch entries 8 q4 .. +7 of the chunk
-    // (lane l of a wave takes fragment position l of a 16-row tile, so a
-    // wave's LDS stores are one contiguous 1 KB block: no bank conflicts)
-    const int j = (tid & 15) + 16 * (tid >> 6), q4 = (tid >> 4) & 3;
-    const int frag = ((j & 15) + 16 * q4) * 16 + (j >> 4) * 1024;   // fragment-major offset in a 16-row tile
-    const bool rok = r0 + j < a.K;
-    auto act_rsrc = [&](int t) {
-        const bf16* act = (a.actT_first && t == a.t_first) ? (const bf16*)a.actT_first
-                                                           : (const bf16*)a.actT + (long)(t + a.shift) * a.tstride;
-        return buf_rsrc(act, abytes);
-    };
-    // per-thread byte offsets of the pieces within a step's blocks (chunk 0);
-    // chunk c of the step adds 64 c bytes (out-of-range offsets stay so)
-    const uint32_t aoff = rok ? (uint32_t)((r0 + j) * a.BP + 8 * q4) * 2 : OOB_OFF;
-    const uint32_t boff0 = n0 + j < a.G ? (uint32_t)((n0 + j) * a.BP + 8 * q4) * 2 : OOB_OFF;
-    const uint32_t boff1 = n0 + 128 + j < a.G ? (uint32_t)((n0 + 128 + j) * a.BP + 8 * q4) * 2 : OOB_OFF;
-    const uint32_t moff = masked && rok ? (uint32_t)(r0 + j) : OOB_OFF;
-    const bool padb = (a.B & (WM_KC - 1)) != 0;   // the last chunk of a step holds padding rows
-    auto dat_rsrc = [&](int t) { return buf_rsrc((const bf16*)a.daT + (size_t)t * a.G * a.BP, bbytes); };
-    auto msk_rsrc = [&](int t) { return buf_rsrc(a.site.mask + (size_t)t * a.site.kmax, (uint32_t)a.site.kmax); };
-    // the next chunk to load (chunks go out in order): its step, its index
-    // in the step, its index, and the step's resources; past the last chunk
-    // the last one is loaded again
-    int it = 0, ic = 0, iq = 0;
-    __amdgpu_buffer_rsrc_t ar = act_rsrc(0), br = dat_rsrc(0), mr = msk_rsrc(0);
-    u32x4_t ra[WM_RING], rb0[WM_RING], rb1[WM_RING];
-    int mk[WM_RING], bq[WM_RING];
+    const int nch = (G + 31) / 32, nq = (R + 31) / 32;
+    // A: piece i of this thread is row ar + i * (rows per pass), 8 columns at ac;
+    // da: block w + NW*i: 16 rows (br: this lane's) x 32 columns.  Both through
+    // resources that begin at the chunk's first row (first step) and end after the
+    // last row (step): constant or small 32-bit offsets, rows past the last are
+    // zeros.
+    constexpr int APR = TM / 8;                                      // pieces per A row
+    const int ar = tid / APR, ac = min(r0 + 8 * (tid % APR), a.lda - 8);
+    const uint32_t aofs = (uint32_t)(ar * a.lda + ac) * 2, apass = (uint32_t)(NTH / APR * a.lda) * 2;
+    const int br = lane & 15, bk = lane >> 4;
+    const uint32_t dasb = (uint32_t)(bt.das * 2);
+    const uint32_t msmall = 65536u / (uint32_t)B + 1u;               // (B < 32: r / B = r * msmall >> 16 for r < 64)
+    uint32_t bofs[PB];                                               // column block, and this lane's column piece
+#pragma unroll
+    for (int i = 0; i < PB; ++i) bofs[i] = (uint32_t)min((n0 >> 5) + ((w + NW * i) >> 1), nch - 1) * 1024u + (uint32_t)bk * 256u;
+    int it = 0, ib = 0;                                              // step and batch row of the next chunk's first row
+    int ir = 0;                                                      // that row
+    u32x4_t ra[2][PA], rbv[2][PB];
     auto issue = [&](int sl) {
-        const uint32_t co = 64u * ic;
-        bq[sl] = WM_KC * ic + 8 * q4;
-        ra[sl] = __builtin_amdgcn_raw_buffer_load_b128(ar, aoff + co, 0, 0);
-        rb0[sl] = __builtin_amdgcn_raw_buffer_load_b128(br, boff0 + co, 0, 0);
-        rb1[sl] = __builtin_amdgcn_raw_buffer_load_b128(br, boff1 + co, 0, 0);
-        // (always issued, past the resource when not masked or past the rows)
-        mk[sl] = (int)__builtin_amdgcn_raw_buffer_load_b8(mr, moff, 0, 0);
-        if (iq + 1 < nq) {
-            ++iq;
-            if (++ic == nb) {
-                ic = 0;
-                ++it;
-                ar = act_rsrc(it);
-                br = dat_rsrc(it);
-                mr = msk_rsrc(it);
-            }
+        const __amdgpu_buffer_rsrc_t arc =
+            buf_rsrc((const bf16*)a.A + (size_t)ir * a.lda, (uint32_t)max(min(R - ir, 32), 0) * (uint32_t)a.lda * 2u);
+        const size_t left = (size_t)max(bt.T - it, 0) * dasb;
+        const __amdgpu_buffer_rsrc_t brc =
+            buf_rsrc((const bf16*)a.da + (size_t)it * bt.das, left < 0x7fffffffu ? (uint32_t)left : 0x7fffffffu);
+#pragma unroll
+        for (int i = 0; i < PA; ++i) ra[sl][i] = __builtin_amdgcn_raw_buffer_load_b128(arc, aofs + i * apass, 0, 0);
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+            const int r = ib + 16 * ((w + NW * i) & 1) + br;
+            const int dt = B >= 32 ? (r >= B ? 1 : 0) : (int)(((uint32_t)r * msmall) >> 16);
+            const int b = r - dt * B;
+            rbv[sl][i] = __builtin_amdgcn_raw_buffer_load_b128(
+                brc, (uint32_t)dt * dasb + (uint32_t)((b >> 4) * nch) * 1024u + (uint32_t)(b & 15) * 16u + bofs[i], 0, 0);
+        }
+        ir += 32;
+        if (B >= 32) {
+            ib += 32;
+            if (ib >= B) { ib -= B; ++it; }
+        } else {
+            ib += 32;
+            const int dt = (int)(((uint32_t)ib * msmall) >> 16);
+            it += dt;
+            ib -= dt * B;
         }
     };
     auto stage = [&](int buf, int sl) {
-        uint32_t pm[4] = {~0u, ~0u, ~0u, ~0u};
-        if (padb) pad_mask<bf16>(bq[sl], a.B, pm);
-        char* sb = smem + buf * WM_STAGE;
-        const bool keep = !masked || mk[sl] != 0;
-        const uint4 va = keep ? make_uint4(ra[sl][0] & pm[0], ra[sl][1] & pm[1], ra[sl][2] & pm[2], ra[sl][3] & pm[3])
-                              : make_uint4(0u, 0u, 0u, 0u);
-        *(uint4*)(sb + frag) = va;
-        *(uint4*)(sb + WM_R * WM_KC * 2 + frag) =
-            make_uint4(rb0[sl][0] & pm[0], rb0[sl][1] & pm[1], rb0[sl][2] & pm[2], rb0[sl][3] & pm[3]);
-        *(uint4*)(sb + WM_R * WM_KC * 2 + 8 * 1024 + frag) =
-            make_uint4(rb1[sl][0] & pm[0], rb1[sl][1] & pm[1], rb1[sl][2] & pm[2], rb1[sl][3] & pm[3]);
+        bf16* Ab = As + buf * 32 * AP;
+        bf16* Bb = Bs + buf * 32 * BPITCH;
+#pragma unroll
+        for (int i = 0; i < PA; ++i) *(u32x4_t*)(Ab + (ar + i * (NTH / APR)) * AP + 8 * (tid % APR)) = ra[sl][i];
+#pragma unroll
+        for (int i = 0; i < PB; ++i) {
+            const int blk = w + NW * i;
+            *(u32x4_t*)(Bb + (16 * (blk & 1) + br) * BPITCH + 32 * (blk >> 1) + 8 * bk) = rbv[sl][i];
+        }
     };
-    f32x4_t acc[4][4];
+    f32x4_t acc[MI][NI], dbacc[NI];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < NI; ++j) {
+        dbacc[j] = f32x4_t{0, 0, 0, 0};
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[i][c] = f32x4_t{0, 0, 0, 0};
-    // the bias gradient (the last row block's waves 0-3): each DA^T fragment
-    // times a fragment of ones, i.e. its column sums over the chunk's batch
-    // entries, on the matrix cores (unpacking and adding the bf16 pairs took
-    // 64 vector instructions per chunk, and those workgroups set the
-    // kernel's time)
-    f32x4_t dbacc[4];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) dbacc[c] = f32x4_t{0, 0, 0, 0};
-    Raw8<bf16> ones;
-#pragma unroll
-    for (int q = 0; q < Raw8<bf16>::NW; ++q) ones.w[q] = 0x3f803f80u;     // bf16 1.0, twice
-    // fragments of two chunks in registers: those of chunk q+1 are read
-    // from LDS while chunk q is multiplied
-    Raw8<bf16> fa[2][4], fb[2][4];
-    auto frags = [&](int buf, int fs) {
-        const char* sb = smem + buf * WM_STAGE;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) raw_lds(fb[fs][c], (const bf16*)(sb + WM_R * WM_KC * 2 + (4 * wc + c) * 1024 + lane * 16));
-#pragma unroll
-        for (int i = 0; i < 4; ++i) raw_lds(fa[fs][i], (const bf16*)(sb + (4 * wr + i) * 1024 + lane * 16));
-    };
-    auto multiply = [&](int fs) {
-        if (dbw && wr == 0)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) raw_mma(fb[fs][c], ones, dbacc[c]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) raw_mma(fb[fs][c], fa[fs][i], acc[i][c]);
-    };
-    // chunk q: stage q+2 (its loads went out two chunks earlier) into the
-    // third buffer, read the fragments of q+1, multiply q, then the slot of
-    // q+2 takes the loads of q+2+WM_RING
-    // (sl = q % WM_RING and fs = q % 2, passed as constants of the unrolled loop)
-    auto iter = [&](int q, int sl, int fs) {
-        stage((q + 2) % 3, (sl + 2) % WM_RING);
-        frags((q + 1) % 3, fs ^ 1);
-        if (q < nq) multiply(fs);
-        issue((sl + 2) % WM_RING);               // (chunk q + 2 + WM_RING)
-        __syncthreads();
-    };
-#pragma unroll
-    for (int i = 0; i < WM_RING; ++i) issue(i);
-    stage(0, 0);
-    stage(1, 1);
-    issue(0);
-    issue(1);
-    __syncthreads();
-    frags(0, 0);
-    for (int q = 0; q < nq; q += 2 * WM_RING) {
-#pragma unroll
-        for (int i = 0; i < 2 * WM_RING; ++i) iter(q + i, i % WM_RING, i & 1);
+        for (int i = 0; i < MI; ++i) acc[i][j] = f32x4_t{0, 0, 0, 0};
     }
+    Raw8<bf16> ones;                           // the bias gradient: da fragments times ones
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ones.w[q] = 0x3f803f80u;
+    const int trow = 8 * (lane >> 4) + ((lane & 15) >> 2), tcol = 4 * (lane & 3);
+    auto frag = [&](Raw8<bf16>& f, const bf16* p, int pitch) {
+        const uint2 lo = lds_tr4(p), hi = lds_tr4(p + 4 * pitch);
+        f.w[0] = lo.x; f.w[1] = lo.y; f.w[2] = hi.x; f.w[3] = hi.y;
+    };
+    auto barrier = [&]() {                     // LDS only: the loads stay in flight
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // (two builds of the loop: a branch around the bias products inside it makes
+    // the compiler copy every accumulator at every chunk)
+    auto run = [&](auto with_db) {
+        auto multiply = [&](int buf) {
+            const bf16* Ab = As + buf * 32 * AP + trow * AP + wm * MI * 16 + tcol;
+            const bf16* Bb = Bs + buf * 32 * BPITCH + trow * BPITCH + wn * NI * 16 + tcol;
+            Raw8<bf16> fb[NI];
+#pragma unroll
+            for (int j = 0; j < NI; ++j) frag(fb[j], Bb + 16 * j, BPITCH);
+            if constexpr (decltype(with_db)::value)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) raw_mma(fb[j], ones, dbacc[j]);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                Raw8<bf16> fa;
+                frag(fa, Ab + 16 * i, AP);
+#pragma unroll
+                for (int j = 0; j < NI; ++j) raw_mma(fb[j], fa, acc[i][j]);
+            }
+        };
+        issue(0);
+        issue(1);
+        stage(0, 0);
+        issue(0);
+        barrier();
+        // chunks in pairs (an odd last one multiplies zeros): stage q+1 (loaded two
+        // chunks ago), its registers take the loads of q+3, multiply q
+        for (int q = 0; q < nq; q += 2) {
+            stage(1, 1);
+            issue(1);
+            multiply(0);
+            barrier();
+            stage(0, 0);
+            issue(0);
+            multiply(1);
+            barrier();
+        }
+    };
+    if (dbw && wm == 0) run(std::true_type());
+    else run(std::false_type());
     // (transposed products) output r of this lane is gradient column
     // 4*(lane/16)+r of the column tile, in the lane's own row
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = r0 + 64 * wr + 16 * i + (lane & 15);
+    for (int i = 0; i < MI; ++i) {
+        const int row = r0 + (wm * MI + i) * 16 + (lane & 15);
         if (row >= a.K) continue;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int nq4 = n0 + 64 * wc + 16 * c + 4 * (lane >> 4);
-            float* o = a.out + (size_t)row * a.G + nq4;
-            if (nq4 + 3 < a.G) {
-                *(float4*)o = make_float4(a.s * acc[i][c][0], a.s * acc[i][c][1], a.s * acc[i][c][2], a.s * acc[i][c][3]);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (nq4 + r < a.G) o[r] = a.s * acc[i][c][r];
-            }
+        for (int j = 0; j < NI; ++j) {
+            const int n = n0 + (wn * NI + j) * 16 + 4 * (lane >> 4);     // (G is a multiple of 4)
+            if (n < G)
+                *(float4*)(a.out + (size_t)row * G + n) =
+                    make_float4(a.s * acc[i][j][0], a.s * acc[i][j][1], a.s * acc[i][j][2], a.s * acc[i][j][3]);
         }
     }
-    if (dbw && wr == 0 && (lane & 15) == 0) {  // (every output column holds the same sums) output r of
-#pragma unroll                                 // lane 16j is the sum of tile column 4j+r
-        for (int c = 0; c < 4; ++c)
+    if (dbw && wm == 0 && (lane & 15) == 0) {
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int n = n0 + 64 * wc + 16 * c + 4 * (lane >> 4) + r;
-                if (n < a.G) a.db[n] = dbacc[c][r];
+                const int n = n0 + (wn * NI + j) * 16 + 4 * (lane >> 4) + r;
+                if (n < G) a.db[n] = dbacc[j][r];
             }
     }
 }
 
-void launch_wgrad_gemm(const WgBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-    int nx = 0;                                // 8 x (row blocks) x ceil(column blocks / 8)
-    for (int i = 0; i < b.np; ++i)
-        nx = std::max(nx, 8 * ((b.p[i].K + WM_R - 1) / WM_R) * (((b.p[i].G + WM_C - 1) / WM_C + 7) / 8));
-    const dim3 grid(nx, 1, b.np), blk(512);
-    if (e0 && e1) hipExtLaunchKernelGGL(k_wgrad_gemm, grid, blk, (uint32_t)WM_LDS, st, e0, e1, 0, b);
-    else k_wgrad_gemm<<<grid, blk, WM_LDS, st>>>(b);
-}
-
-void launch_wgrad_big(const WgBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
-    int nx = 0;                                // 8 x (row slices) x ceil(column blocks / 8)
-    for (int i = 0; i < b.np; ++i)
-        nx = std::max(nx, 8 * ((b.p[i].K + WL_R - 1) / WL_R) * (((b.p[i].G + WL_C - 1) / WL_C + 7) / 8));
-    const dim3 grid(nx, 1, b.np), blk(512);
-    if (e0 && e1) hipExtLaunchKernelGGL(k_wgrad_big, grid, blk, (uint32_t)wgrad_big_lds(), st, e0, e1, 0, b);
-    else k_wgrad_big<<<grid, blk, wgrad_big_lds(), st>>>(b);
+// The tile of a pass.  256 x 256 (973 TFLOP/s at hidden 1024, batch 256, 64 steps:
+// 565 us a pass against 733 with 128 x 128) needs a long contraction to pay for its
+// one workgroup per CU and a count that fills the chip; at 22 to 44 chunks 128 x 128
+// is as fast or faster (hidden 1500: 83 against 100 us); below a workgroup of those
+// per CU, 64 x 128 (tagger 27 against 31 us).
+void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+    if (b.np == 0) return;
+    auto fill = [&](int TM, int TN) {
+        b.total = 0;
+        for (int i = 0; i < b.np; ++i) {
+            b.p[i].nrb = (b.p[i].K + TM - 1) / TM;
+            b.p[i].tiles = b.p[i].nrb * ((b.G + TN - 1) / TN);
+            b.total += b.p[i].tiles;
+        }
+        b.per = (b.total + 7) / 8;
+        return b.total;
+    };
+    auto go = [&](auto kern, int nth, size_t lds) {
+        const dim3 grid(8 * b.per), blk(nth);
+        if (e0 && e1) hipExtLaunchKernelGGL(kern, grid, blk, (uint32_t)lds, st, e0, e1, 0, b);
+        else kern<<<grid, blk, lds, st>>>(b);
+    };
+    int big = b.R >= 4096 ? 200 : 1 << 30, mid = 256;
+#ifdef LSD_TUNE
+    if (const char* v = getenv("LSD_TUNE_W")) { big = v[0] == '2' ? 0 : 1 << 30; mid = v[0] == '1' ? 0 : 1 << 30; }
+#endif
+    if (fill(256, 256) >= big) go(k_wgrad_rows<2, 4, 8, 4>, 512, WrShape<2, 4, 8, 4>::LDS);
+    else if (fill(128, 128) >= mid) go(k_wgrad_rows<2, 2, 4, 4>, 256, WrShape<2, 2, 4, 4>::LDS);
+    else {
+        fill(64, 128);
+        go(k_wgrad_rows<1, 4, 4, 2>, 256, WrShape<1, 4, 4, 2>::LDS);
+    }
 }
 
 int setup_big_attributes() {
-    bool ok = hipFuncSetAttribute((const void*)k_wgrad_big, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)wgrad_big_lds()) == hipSuccess;
+    bool ok = hipFuncSetAttribute((const void*)k_wgrad_rows<2, 4, 8, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  (int)WrShape<2, 4, 8, 4>::LDS) == hipSuccess;
     ok = hipFuncSetAttribute((const void*)k_fx_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FB_LDS) ==
              hipSuccess && ok;
     ok = hipFuncSetAttribute((const void*)k_dx_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)DB_LDS) ==
-             hipSuccess && ok;
-    ok = hipFuncSetAttribute((const void*)k_wgrad_gemm, hipFuncAttributeMaxDynamicSharedMemorySize, (int)WM_LDS) ==
              hipSuccess && ok;
     return ok ? 0 : -1;
 }

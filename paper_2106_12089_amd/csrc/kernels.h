@@ -48,6 +48,15 @@ struct TransArgs {
     const void* src2;                   // second job (K2 columns), or unused when every matrix is the first job's
     void* dst2;
     int K2;
+    // bf16: job 1 also writes xm [n1][B][ldm], src times the mask rows of its
+    // matrices (and dst only if non-null); job 2 writes h0 of (layer, direction) k
+    // times mask2 row tf into hm + k*hm_stride bytes at step tf = 0 (direction 0)
+    // or n1 - 1, [n1][B][ldh] (dst2 unused)
+    void* xm; int ldm;
+    const uint8_t* mask;
+    void* hm; size_t hm_stride; int ldh, D;
+    const uint8_t* mask2;               // RH mask of k = 0; the next at n1*kmax bytes each
+    int kmax;
     // with n_init > 0, one more grid slice initialises the forward pass:
     // hT <- h0 (as float), cT <- c0 (n_init elements), barrier counters <- 0
     const void* h0;
@@ -90,18 +99,21 @@ struct StepDir {
     float* gates;                       // [B][H][4] (the four gates of a unit together)
     float* cres;                        // [B][H]
     void* hrec;                         // [B][H] row-major h_t (dtype)
-    void* hrecT;                        // [H][BP] h_t transposed (dtype)
+    void* hrecT;                        // f32: [H][BP] h_t transposed
+    void* hm;                           // bf16: [B][ldh] h_t times the next step's RH mask, or null (last step)
+    const uint8_t* hmask;               // bf16: that mask row
+    const uint8_t* ymask;               // bf16, inner layer: NR mask row of the layer above at t
     float* hT;                          // [B][H] fp32 state, in place
     float* cT;                          // [B][H] fp32 state, in place
     float* y;                           // top layer output rows + d*H, or null
-    void* ybuf;                         // inter-layer output rows + d*H (ld ldy), or null
+    void* ybuf;                         // inter-layer output rows + d*H (ld ldyb; bf16: masked), or null
     void* ybufT;                        // inter-layer output transposed rows + d*H (ld BP), or null
     int t;
 };
 struct StepArgs {
     StepDir d[2];
     const int32_t* lengths;
-    int B, H, ldy, BP, dense;
+    int B, H, ldy, ldyb, ldh, BP, dense;
     float s;
 };
 
@@ -129,7 +141,7 @@ struct BwdDir {
     float* dhc;                         // [B][H] pass-through carry, in place
     float* dcs;                         // [B][H] cell-gradient carry, in place
     void* da;                           // DA_t, fragment-major [B][G] (dtype)
-    void* daT;                          // [G][BP] dtype (transposed)
+    void* daT;                          // f32: [G][BP] (transposed)
     float* dh0;                         // final pass: [B][H]
     float* dc0;
     int t;
@@ -171,17 +183,34 @@ struct WgArgs {
     float* db;                          // non-null: also the bias gradient (Eq. 11), the sum of DA^T
     int K, B, BP, G, T, dense;
     int full;                           // every keep list of the site is the identity (p = 0, or dense mode)
-    int staged;                         // (set at launch) a kernel with LDS-staged operands
-    int fullmask;                       // (set at launch) a row-sparse problem on the full kernel, rows times the mask
     float s;
 };
-// Weight gradients of a pass (row-sparse and full problems) in one launch
+// Weight gradients (fp32) of a pass (row-sparse and full problems) in one launch
 constexpr int WG_MAXP = 8;
 struct WgBatch {
     WgArgs p[WG_MAXP];
     int np;
-    int big;                            // bf16 at a large batch: the register-accumulated kernel
     const int* status;                  // sticky barrier status of the step, or null: when set, NaN is written
+};
+
+// Weight gradients (bf16) of a pass in one launch: out[k][n] = s * sum over the rows
+// r = (t, b) of A[r][k] da[r][n].
+struct WrProblem {
+    const void* A;                      // [T*B][lda], masked; lda a multiple of 8
+    const void* da;                     // [T] x fragment-major [B][G]
+    float* out;                         // [K][G]
+    float* db;                          // non-null: also the column sums of da
+    int lda, K;
+    float s;
+    int nrb, tiles;                     // (set at launch) row blocks; tiles in all
+};
+constexpr int WR_MAXP = 32;
+struct WrBatch {
+    WrProblem p[WR_MAXP];
+    int np, B, T, R, G;                 // R = T*B rows
+    long das;                           // elements of one DA block
+    const int* status;                  // sticky barrier status of the step, or null
+    int total, per;                     // (set at launch) tiles of all problems; per XCD
 };
 
 // Persistent forward recurrence of one layer (both directions): one
@@ -275,17 +304,17 @@ struct RFwdSlot {
     const void* h0;                     // [B][H]
     const float* c0;                    // [B][H]
     const uint8_t* rmask;               // RH mask rows
-    const uint8_t* umask;               // NR mask rows of the layer above (with xout)
+    const uint8_t* umask;               // inner layer: NR mask rows of the layer above
     void* hx;                           // [2] exchange slots of the masked h_t
     void* xout;                         // [T] exchange slots of the masked output for the layer above, or null
     float* gates;                       // [T][B][H][4]
     float* cres;                        // [T][B][H]
-    void* hrecT;                        // [T][H][BP]
+    void* hm;                           // [T][B][ldh] h_{t-1} times the RH mask of t (the dU operand; the first step's from elsewhere)
     float* hT;                          // [B][H]
     float* cT;                          // [B][H]
     float* y;                           // top layer: y + d*H (rows ld ldy), or null
-    void* ybuf;                         // inner layer: ybuf + d*H, or null
-    void* ybufT;
+    void* ybuf;                         // inner layer: ybuf + d*H (rows ld ldyb), masked by umask, or null
+    void* ybufT;                        // its transpose + d*H*BP, or null
 };
 struct RFwdArgs {
     RFwdSlot d[8];
@@ -293,7 +322,7 @@ struct RFwdArgs {
     unsigned* bar;
     int* err;
     long long timeout;
-    int B, H, T, BP, ldy, kmax, mtiles, nslots;
+    int B, H, T, BP, ldy, ldyb, ldh, kmax, mtiles, nslots;
     int ntiles, mgroups, mg0, rg, gpx;  // (set by the launcher) unit tiles; row groups of the launch, the first one, their rows; groups per XCD
 };
 struct RBwdSlot {
@@ -312,7 +341,6 @@ struct RBwdSlot {
     const float* dcT;
     float* dxw;                         // [T][B][H]: a worker's output, a fed layer's input
     void* da;                           // [T] x fragment-major [B][4H] (worker: of the layer above)
-    void* daT;                          // [T][4H][BP]
     float* dh0;
     float* dc0;
 };
@@ -322,7 +350,7 @@ struct RBwdArgs {
     unsigned* bar;
     int* err;
     long long timeout;
-    int B, H, T, BP, kmax, mtiles, nslots;
+    int B, H, T, kmax, mtiles, nslots;
     int ntiles, mgroups, mg0, rg, gpx;
 };
 

@@ -156,9 +156,9 @@ __device__ __forceinline__ void clear_counters(unsigned* bar) {
 }
 
 // ---------------------------------------------------------------------------
-// src [N][B][K] -> dst [N][K][BP], zero rows b in [B, BP); two such jobs
-// (matrices z < n1 from the first, the others from the second) in one grid,
-// and, with n_init > 0, the forward pass's initialisation in slice z = N.
+// src [N][B][K] -> dst [N][K][BP], zero rows b in [B, BP) (with dst), and in bf16
+// the masked row-major copy the weight gradients read; two such jobs (matrices
+// z < n1 from the first, the others from the second) in one grid, and, with n_init > 0, the forward pass's initialisation in slice z = N.
 // One workgroup (256 threads) of a grid (gx = ceil(max K/32), gy = BP/32,
 // N (+1)): block (bx, by, bz).
 template <typename T>
@@ -185,11 +185,28 @@ __device__ __forceinline__ void transpose_block(const TransArgs& a, int N, int b
     const int k0 = bx * 32, b0 = by * 32;
     if (k0 >= K) return;                       // (the whole workgroup)
     const T* src = (const T*)(second ? a.src2 : a.src) + (size_t)n * a.B * K;
-    T* dst = (T*)(second ? a.dst2 : a.dst) + (size_t)n * K * a.BP;
-    for (int i = ty; i < 32; i += 8) {
-        const int b = b0 + i, k = k0 + tx;
-        tile[i][tx] = (b < a.B && k < K) ? src[(size_t)b * K + k] : zero_val<T>();
+    // bf16: the masked row-major copy of the matrix
+    T* xm = nullptr;
+    int ldm = 0;
+    const uint8_t* mrow = nullptr;
+    if constexpr (sizeof(T) == 2) {
+        const int tf = second && n % a.D ? a.n1 - 1 : 0;
+        ldm = second ? a.ldh : a.ldm;
+        xm = second ? (T*)((char*)a.hm + (size_t)n * a.hm_stride) + (size_t)tf * a.B * ldm
+                    : (T*)a.xm + (size_t)n * a.B * ldm;
+        mrow = second ? a.mask2 + ((size_t)n * a.n1 + tf) * a.kmax : a.mask + (size_t)n * a.kmax;
     }
+    const bool trans = second ? a.dst2 != nullptr : a.dst != nullptr;
+    const int kc = k0 + tx;
+    const bool kept = sizeof(T) == 2 && kc < K && mrow[kc] != 0;
+    for (int i = ty; i < 32; i += 8) {
+        const int b = b0 + i;
+        const T v = (b < a.B && kc < K) ? src[(size_t)b * K + kc] : zero_val<T>();
+        if (trans) tile[i][tx] = v;
+        if (sizeof(T) == 2 && b < a.B && kc < K) xm[(size_t)b * ldm + kc] = kept ? v : zero_val<T>();
+    }
+    if (!trans) return;
+    T* dst = (T*)(second ? a.dst2 : a.dst) + (size_t)n * K * a.BP;
     __syncthreads();
     for (int i = ty; i < 32; i += 8) {
         const int k = k0 + i, b = b0 + tx;
@@ -433,16 +450,20 @@ __global__ void __launch_bounds__(1024) k_step(StepArgs a) {
             D.cres[(size_t)b * H + u] = valid ? cn : cp;
             const T hv = valid ? from_f32<T>(hn) : hp[(size_t)b * H + u];
             ((T*)D.hrec)[(size_t)b * H + u] = hv;
-            ((T*)D.hrecT)[(size_t)u * a.BP + b] = hv;
+            if constexpr (sizeof(T) == 2) {
+                if (D.hm) ((T*)D.hm)[(size_t)b * a.ldh + u] = D.hmask[u] ? hv : zero_val<T>();
+            } else {
+                ((T*)D.hrecT)[(size_t)u * a.BP + b] = hv;
+            }
             if (valid) {
                 D.cT[(size_t)b * H + u] = cn;
                 D.hT[(size_t)b * H + u] = hn;
             }
             if (D.y) D.y[(size_t)b * a.ldy + u] = valid ? hn : 0.0f;
             if (D.ybuf) {
-                const T yv = valid ? from_f32<T>(hn) : zero_val<T>();
-                ((T*)D.ybuf)[(size_t)b * a.ldy + u] = yv;
-                ((T*)D.ybufT)[(size_t)u * a.BP + b] = yv;
+                const T yv = valid && (sizeof(T) == 4 || D.ymask[u]) ? from_f32<T>(hn) : zero_val<T>();
+                ((T*)D.ybuf)[(size_t)b * a.ldyb + u] = yv;
+                if (D.ybufT) ((T*)D.ybufT)[(size_t)u * a.BP + b] = yv;
             }
         }
     }
@@ -576,7 +597,7 @@ __global__ void __launch_bounds__(1024) k_bwd(BwdArgs a) {
             for (int g = 0; g < 4; ++g) {
                 const T v = from_f32<T>(da4[g]);
                 ((T*)D.da)[frag_off(b, g * H + u, (G + 31) / 32)] = v;
-                dat[(size_t)(g * H + u) * a.BP + b] = v;
+                if (sizeof(T) == 4) dat[(size_t)(g * H + u) * a.BP + b] = v;
             }
         }
     }
@@ -723,19 +744,6 @@ template <typename T>
 inline size_t wgrad_lds_bytes(int K) {
     return (size_t)(wgrad_tsplit<T>(K) ? 2 : 1) * ((K + NXCD - 1) / NXCD + 1) * WG_LDC * sizeof(float);
 }
-
-// Layout of the staged row-sparse kernel's LDS: the accumulator rows of the
-// largest slice (+ a spare row), two stage buffers (DA^T: 8 fragment tiles;
-// the kept rows: up to wgs_tiles tiles; their accumulator row offsets), and
-// the keep-list ranges of every step
-__host__ __device__ inline int wgs_rows(int K) { return (K + NXCD - 1) / NXCD; }
-__host__ __device__ inline int wgs_tiles(int K) { return (wgs_rows(K) + 15) / 16; }
-__host__ __device__ inline int wgs_stage_bytes(int K) { return (8 + wgs_tiles(K)) * 1024 + 16 * wgs_tiles(K) * 4; }
-inline size_t wgs_lds_bytes(int K, int T) {
-    return (size_t)(wgs_rows(K) + 1) * WG_LDC * 4 + 2 * (size_t)wgs_stage_bytes(K) + (size_t)T * 8;
-}
-constexpr int WGS_MAX_ROWS = 128;          // a stage buffer row per thread piece: 512 / 4
-constexpr size_t WGS_MAX_LDS = 80 * 1024;  // two workgroups per CU
 
 // workgroup i -> (row slice x, column block cb).  Workgroup i runs on XCD
 // i % 8, which takes the column blocks i % 8 + 8j with every row slice: one
@@ -988,357 +996,6 @@ __device__ __forceinline__ void wgrad_gather(const WgArgs& a, float* acc_lds) {
     }
 }
 
-// Row-sparse weight gradient with LDS-staged operands (bf16, batch <= 32,
-// slices of at most 128 rows).  Same grid, slots and result as the kernel
-// above; what differs is how a step's operands reach the waves.  There,
-// every wave loaded its own fragments from memory: the four waves of a half
-// the same gathered rows, the two halves the same DA^T columns, so the
-// vector memory pipe moved about three times the step's data and set the
-// step time.  Here the 512 threads load a step's operands once, one 16-byte
-// piece each: a piece is 8 batch entries of a DA^T column of the block (8
-// KB, one piece per thread) and of a kept row of the step in the slice
-// (gathered through the keep list; absent rows read past the resource,
-// i.e. zeros), and the threads store them fragment-major in LDS, with
-// the accumulator row offset of each kept row beside them.  Wave w then
-// multiplies DA^T column tile w with every kept-row tile of the step and
-// adds the tiles into its 16 columns of the LDS accumulator.  Loads run two
-// steps ahead of the store into LDS (register ring), keep-list entries two
-// steps ahead of those; the stage buffers alternate, one barrier per step.
-// The slice's keep-list ranges for every step sit in LDS ([T][2] ints).
-template <typename T>
-__device__ __forceinline__ void wgrad_staged(const WgArgs& a, float* lds) {
-    static_assert(sizeof(T) == 2, "bf16 only");
-    int x, cb;
-    wg_slot(x, cb);
-    if (cb * WG_NB >= a.G) return;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);     // (wave-uniform)
-    const int n0 = cb * WG_NB;
-    const int r0 = slice_start(x, a.K), nrow = slice_start(x + 1, a.K) - r0;
-    const int ntmax = wgs_tiles(a.K);
-    float* acc = lds;                                              // [rows of the slice + 1][WG_LDC]
-    char* stg = (char*)(lds + (size_t)(wgs_rows(a.K) + 1) * WG_LDC);
-    const int sbytes = wgs_stage_bytes(a.K);                       // one stage buffer
-    int* seg = (int*)(stg + 2 * sbytes);                           // [T][2]: keep-list range of the slice
-    for (int i = tid; i < (nrow + 1) * WG_NB; i += blockDim.x) acc[(i / WG_NB) * WG_LDC + i % WG_NB] = 0.0f;
-    for (int t = tid; t < a.T; t += blockDim.x) {
-        const int32_t* ks = a.site.kseg + (size_t)t * (NSEG + 1) + 2 * x;
-        seg[2 * t] = ks[0];
-        seg[2 * t + 1] = ks[2];
-    }
-    __syncthreads();
-
-    // this thread's piece: row / column j of the step, batch entries 8q .. 8q+7
-    // (lane l of a wave takes fragment position l of a 16-row tile: a wave's
-    // LDS stores are one contiguous 1 KB block, free of bank conflicts)
-    const int j = (tid & 15) + 16 * (tid >> 6), q = (tid >> 4) & 3;
-    uint32_t pm[4];
-    pad_mask<T>(8 * q, a.B, pm);
-    const uint32_t abytes = (uint32_t)a.K * a.BP * 2, bbytes = (uint32_t)a.G * a.BP * 2;
-    const uint32_t boff = n0 + j < a.G ? (uint32_t)((n0 + j) * a.BP + 8 * q) * 2 : OOB_OFF;
-    const int frag = ((j & 15) + 16 * q) * 16 + (j >> 4) * 1024;   // fragment-major LDS offset of the piece
-    const bool arow = j < 16 * ntmax;                              // a row of the stage buffer
-    const int spare = nrow * WG_LDC;
-    const uint32_t kbytes = (uint32_t)a.site.kmax * 4;
-    auto clampt = [&](int t) { return t < a.T ? t : a.T - 1; };
-    auto act_rsrc = [&](int t) {
-        const T* act = (a.actT_first && t == a.t_first) ? (const T*)a.actT_first
-                                                        : (const T*)a.actT + (long)(t + a.shift) * a.tstride;
-        return buf_rsrc(act, abytes);
-    };
-    // ring slots: keep-list entry, staged pieces and accumulator row offset of a step
-    int kv[2], la[2];
-    uint4 ra[2], rb[2];
-    auto issue_kv = [&](int t, int sl) {
-        t = clampt(t);
-        const int jb = seg[2 * t], n = seg[2 * t + 1] - jb;
-        const __amdgpu_buffer_rsrc_t kr = buf_rsrc(a.site.keep + (size_t)t * a.site.kmax, kbytes);
-        kv[sl] = (int)__builtin_amdgcn_raw_buffer_load_b32(kr, j < n ? (uint32_t)(jb + j) * 4 : OOB_OFF, 0, 0);
-    };
-    auto issue_ab = [&](int t, int sl) {
-        t = clampt(t);
-        const int n = seg[2 * t + 1] - seg[2 * t];
-        const bool ok = j < n;
-        const u32x4_t va = __builtin_amdgcn_raw_buffer_load_b128(
-            act_rsrc(t), ok ? ((uint32_t)kv[sl] * a.BP + 8 * q) * 2 : OOB_OFF, 0, 0);
-        const u32x4_t vb = __builtin_amdgcn_raw_buffer_load_b128(
-            buf_rsrc((const T*)a.daT + (size_t)t * a.G * a.BP, bbytes), boff, 0, 0);
-        ra[sl] = make_uint4(va[0], va[1], va[2], va[3]);
-        rb[sl] = make_uint4(vb[0], vb[1], vb[2], vb[3]);
-        la[sl] = ok ? (kv[sl] - r0) * WG_LDC : spare;
-    };
-    auto stage = [&](int buf, int sl) {
-        char* sb = stg + buf * sbytes;
-        const uint4 b4 = make_uint4(rb[sl].x & pm[0], rb[sl].y & pm[1], rb[sl].z & pm[2], rb[sl].w & pm[3]);
-        *(uint4*)(sb + frag) = b4;
-        if (arow) {
-            const uint4 a4 = make_uint4(ra[sl].x & pm[0], ra[sl].y & pm[1], ra[sl].z & pm[2], ra[sl].w & pm[3]);
-            *(uint4*)(sb + 8 * 1024 + frag) = a4;
-            if (q == 0) ((int*)(sb + (8 + ntmax) * 1024))[j] = la[sl];
-        }
-    };
-    const bool dbw = a.db && x == 0;
-    float dbacc = 0.0f;
-    const int cq = 16 * w + 4 * (lane >> 4);                       // this lane's 4 accumulator columns
-    auto compute = [&](int t, int buf) {
-        const char* sb = stg + buf * sbytes;
-        const int n = __builtin_amdgcn_readfirstlane(seg[2 * t + 1] - seg[2 * t]);
-        const int ntile = (n + 15) >> 4;
-        Raw8<T> fb;
-        raw_lds(fb, (const T*)(sb + w * 1024 + lane * 16));
-        if (dbw) db_add_raw(fb, dbacc);
-        const int* lab = (const int*)(sb + (8 + ntmax) * 1024);
-        for (int rt0 = 0; rt0 < ntile; rt0 += 4) {
-            Raw8<T> fa[4];
-            int lr[4];
-            f32x4_t d[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (rt0 + i < ntile) {
-                    raw_lds(fa[i], (const T*)(sb + 8 * 1024 + (rt0 + i) * 1024 + lane * 16));
-                    lr[i] = lab[(rt0 + i) * 16 + (lane & 15)];
-                }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (rt0 + i < ntile) {
-                    d[i] = f32x4_t{0, 0, 0, 0};
-                    raw_mma(fb, fa[i], d[i]);
-                }
-            float4 old[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (rt0 + i < ntile) old[i] = *(const float4*)(acc + lr[i] + cq);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (rt0 + i < ntile) {
-                    float4 v = old[i];
-                    v.x += a.s * d[i][0];
-                    v.y += a.s * d[i][1];
-                    v.z += a.s * d[i][2];
-                    v.w += a.s * d[i][3];
-                    *(float4*)(acc + lr[i] + cq) = v;
-                }
-        }
-    };
-    // step t: stage t+1 (its loads went out two steps earlier), issue the
-    // operand loads of t+3 and the keep-list entries of t+5, multiply t
-    auto iter = [&](int t, int sl) {
-        stage((t + 1) & 1, sl ^ 1);
-        issue_ab(t + 3, sl ^ 1);
-        issue_kv(t + 5, sl ^ 1);
-        if (t < a.T) compute(t, t & 1);
-        __syncthreads();
-    };
-    issue_kv(0, 0);
-    issue_kv(1, 1);
-    issue_ab(0, 0);
-    issue_kv(2, 0);
-    issue_ab(1, 1);
-    issue_kv(3, 1);
-    stage(0, 0);
-    issue_ab(2, 0);
-    issue_kv(4, 0);
-    __syncthreads();
-    for (int t = 0; t < a.T; t += 2) {
-        iter(t, 0);
-        iter(t + 1, 1);
-    }
-    if (dbw) {                                                     // lanes l, l+16, l+32, l+48 hold column l
-        dbacc += __shfl_xor(dbacc, 16);
-        dbacc += __shfl_xor(dbacc, 32);
-        if (lane < 16 && n0 + 16 * w + lane < a.G) a.db[n0 + 16 * w + lane] = dbacc;
-    }
-    for (int i = tid; i < nrow * WG_NB; i += blockDim.x) {
-        const int rr = i / WG_NB, cc = i % WG_NB;
-        if (n0 + cc < a.G) a.out[(size_t)(r0 + rr) * a.G + n0 + cc] = acc[rr * WG_LDC + cc];
-    }
-}
-
-// Weight gradient of a full problem (identity keep lists, the dense
-// comparison mode, or a row-sparse problem routed here: in the last two the
-// mask byte zeroes the dropped rows) with LDS-staged rows (bf16, batch <=
-// 32).  Same grid and slots as the kernels above.
-// Wave w owns CT DA^T column tiles of the block (16 columns each, their
-// fragments loaded straight into registers: no other wave reads them) and
-// every row of the slice, in passes of up to 6 row tiles whose accumulators
-// stay in registers over all steps.  The rows are the operand every wave
-// shares: the workgroup loads a step's rows once (16-byte pieces: 8 batch
-// entries of one row, zeroed when the row is dropped) and stores them
-// fragment-major in LDS, where each wave reads its fragments; each fragment
-// read feeds CT products.  Loads run three steps ahead (register ring), the
-// two stage buffers alternate, one barrier per step.  8/CT waves.
-constexpr int WFS_TILES = 6;               // 16-row tiles of a pass
-constexpr int WFS_RING = 3;                // steps whose loads are in flight
-constexpr size_t WFS_LDS = 2 * WFS_TILES * 1024;
-
-template <typename T, bool MASKED, int CT = 1>
-__device__ __forceinline__ void wgrad_full_staged(const WgArgs& a, float* lds) {
-    static_assert(sizeof(T) == 2, "bf16 only");
-    constexpr int NTH = 512 / CT;                               // threads
-    constexpr int PP = (64 * WFS_TILES + NTH - 1) / NTH;        // staged pieces per thread and step
-    int x, cb;
-    wg_slot(x, cb);
-    if (cb * WG_NB >= a.G) return;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);     // (wave-uniform)
-    const int n0 = cb * WG_NB, g8 = 8 * (lane >> 4);
-    int nc[CT];
-#pragma unroll
-    for (int h = 0; h < CT; ++h) nc[h] = n0 + 16 * (CT * w + h) + (lane & 15);
-    const int r0 = slice_start(x, a.K), r1 = slice_start(x + 1, a.K);
-    char* stg = (char*)lds;
-    // staging: piece i = tid + NTH*p is row j of the pass, 8-entry part q
-    // (lane l of a wave takes fragment position l of a 16-row tile: its LDS
-    // stores are free of bank conflicts)
-    int sj[PP], sfrag[PP];
-    uint32_t pm[PP][4];
-#pragma unroll
-    for (int p = 0; p < PP; ++p) {
-        const int i = tid + NTH * p, j = (i & 15) + 16 * (i >> 6), q = (i >> 4) & 3;
-        sj[p] = j < 16 * WFS_TILES ? j : -1;
-        sfrag[p] = ((j & 15) + 16 * q) * 16 + (j >> 4) * 1024;   // fragment-major LDS offset of the piece
-        pad_mask<T>(8 * q, a.B, pm[p]);
-    }
-    uint32_t pmb[CT][4], boff[CT];
-#pragma unroll
-    for (int h = 0; h < CT; ++h) {
-        pad_mask<T>(g8, a.B, pmb[h]);
-        if (nc[h] >= a.G) pmb[h][0] = pmb[h][1] = pmb[h][2] = pmb[h][3] = 0u;
-        boff[h] = g8 < a.B ? (uint32_t)(min(nc[h], a.G - 1) * a.BP + g8) * 2 : OOB_OFF;   // (as the row pieces)
-    }
-    const uint32_t abytes = (uint32_t)a.K * a.BP * 2, bbytes = (uint32_t)a.G * a.BP * 2;
-    const bool dbw = a.db && x == NXCD - 1;                        // (the last slice is never empty)
-    const bool masked = MASKED || a.fullmask;                      // dropped rows zeroed by the mask byte
-    // the bias gradient (the last slice's workgroups): each DA^T fragment
-    // times a fragment of ones, i.e. its column sums, on the matrix cores
-    f32x4_t dbacc[CT];
-#pragma unroll
-    for (int h = 0; h < CT; ++h) dbacc[h] = f32x4_t{0, 0, 0, 0};
-    Raw8<T> ones;
-#pragma unroll
-    for (int q = 0; q < Raw8<T>::NW; ++q) ones.w[q] = 0x3f803f80u;       // bf16 1.0, twice
-    auto act_rsrc = [&](int t) {
-        const T* act = (a.actT_first && t == a.t_first) ? (const T*)a.actT_first
-                                                        : (const T*)a.actT + (long)(t + a.shift) * a.tstride;
-        return buf_rsrc(act, abytes);
-    };
-    for (int rp = r0; rp < r1; rp += 16 * WFS_TILES) {            // passes over the slice's rows
-        const int nt = min(WFS_TILES, (r1 - rp + 15) >> 4);        // row tiles of the pass
-        const bool first = rp == r0 && dbw;                        // (the bias gradient: first pass)
-        bool rok[PP];
-#pragma unroll
-        for (int p = 0; p < PP; ++p) rok[p] = sj[p] >= 0 && rp + sj[p] < r1;
-        // pieces wholly past the batch (entries 24-31 at B <= 24) read 0
-        // without moving data, like rows past the slice
-        bool aok[PP];
-#pragma unroll
-        for (int p = 0; p < PP; ++p) aok[p] = rok[p] && 8 * (((tid + NTH * p) >> 4) & 3) < a.B;
-        uint4 ra[WFS_RING][PP];
-        Raw8<T> rb[WFS_RING][CT];
-        int mk[WFS_RING][PP];
-        auto issue = [&](int t, int sl) {
-            t = t < a.T ? t : a.T - 1;
-            const __amdgpu_buffer_rsrc_t ar = act_rsrc(t);
-            // (the mask load is always issued, past the resource when
-            // unmasked: a load under a branch would make the compiler wait
-            // for every load on its own)
-            const __amdgpu_buffer_rsrc_t mr = buf_rsrc(a.site.mask + (size_t)t * a.site.kmax, (uint32_t)a.site.kmax);
-#pragma unroll
-            for (int p = 0; p < PP; ++p) {
-                const int row = rp + sj[p], q = ((tid + NTH * p) >> 4) & 3;
-                const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(
-                    ar, aok[p] ? (uint32_t)(row * a.BP + 8 * q) * 2 : OOB_OFF, 0, 0);
-                ra[sl][p] = make_uint4(v[0], v[1], v[2], v[3]);
-                mk[sl][p] = (int)__builtin_amdgcn_raw_buffer_load_b8(mr, masked && rok[p] ? (uint32_t)row : OOB_OFF, 0, 0);
-            }
-            const __amdgpu_buffer_rsrc_t br = buf_rsrc((const T*)a.daT + (size_t)t * a.G * a.BP, bbytes);
-#pragma unroll
-            for (int h = 0; h < CT; ++h) raw_load(rb[sl][h], br, boff[h]);
-        };
-        auto stage = [&](int buf, int sl) {
-#pragma unroll
-            for (int p = 0; p < PP; ++p)
-                if (sj[p] >= 0) {
-                    uint4 v = make_uint4(ra[sl][p].x & pm[p][0], ra[sl][p].y & pm[p][1], ra[sl][p].z & pm[p][2],
-                                         ra[sl][p].w & pm[p][3]);
-                    if (masked && !mk[sl][p]) v = make_uint4(0u, 0u, 0u, 0u);
-                    *(uint4*)(stg + buf * (WFS_TILES * 1024) + sfrag[p]) = v;
-                }
-        };
-        f32x4_t acc[WFS_TILES][CT];
-#pragma unroll
-        for (int i = 0; i < WFS_TILES; ++i)
-#pragma unroll
-            for (int h = 0; h < CT; ++h) acc[i][h] = f32x4_t{0, 0, 0, 0};
-        auto compute = [&](int buf, int sl) {
-            Raw8<T> fb[CT];
-#pragma unroll
-            for (int h = 0; h < CT; ++h) {
-                fb[h] = rb[sl][h];
-                raw_and(fb[h], pmb[h]);
-                if (first) raw_mma(fb[h], ones, dbacc[h]);
-            }
-            const char* sb = stg + buf * (WFS_TILES * 1024);
-            // every tile, also past nt (their accumulators are never written
-            // out): the LDS reads then go out together instead of one read,
-            // wait and product at a time behind a branch
-            Raw8<T> fa[WFS_TILES];
-#pragma unroll
-            for (int i = 0; i < WFS_TILES; ++i) raw_lds(fa[i], (const T*)(sb + i * 1024 + lane * 16));
-#pragma unroll
-            for (int i = 0; i < WFS_TILES; ++i)
-#pragma unroll
-                for (int h = 0; h < CT; ++h) raw_mma(fb[h], fa[i], acc[i][h]);
-        };
-        // step t: stage t+1 (its loads went out two steps earlier), multiply
-        // t, then its slot takes the loads of t+3
-        auto iter = [&](int t, int sl) {
-            stage((t + 1) & 1, (sl + 1) % WFS_RING);
-            if (t < a.T) compute(t & 1, sl);
-            issue(t + WFS_RING, sl);
-            __syncthreads();
-        };
-#pragma unroll
-        for (int i = 0; i < WFS_RING; ++i) issue(i, i);
-        stage(0, 0);
-        __syncthreads();
-        for (int t = 0; t < a.T; t += WFS_RING) {
-#pragma unroll
-            for (int i = 0; i < WFS_RING; ++i) iter(t + i, i);
-        }
-        // (transposed products) output r of this lane is gradient column
-        // 4*(lane/16)+r of tile h, in the lane's own row
-#pragma unroll
-        for (int h = 0; h < CT; ++h) {
-            const int nq = n0 + 16 * (CT * w + h) + 4 * (lane >> 4);
-#pragma unroll
-            for (int i = 0; i < WFS_TILES; ++i) {
-                const int orow = rp + 16 * i + (lane & 15);
-                if (i < nt && orow < r1) {
-                    float* o = a.out + (size_t)orow * a.G + nq;
-                    if (nq + 3 < a.G) {
-                        *(float4*)o = make_float4(a.s * acc[i][h][0], a.s * acc[i][h][1], a.s * acc[i][h][2],
-                                                  a.s * acc[i][h][3]);
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r)
-                            if (nq + r < a.G) o[r] = a.s * acc[i][h][r];
-                    }
-                }
-            }
-        }
-    }
-    if (dbw && (lane & 15) == 0) {                                 // output r of lane 16j: column 4j+r's sum
-#pragma unroll
-        for (int h = 0; h < CT; ++h)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int n = n0 + 16 * (CT * w + h) + 4 * (lane >> 4) + r;
-                if (n < a.G) a.db[n] = dbacc[h][r];
-            }
-    }
-}
-
 // Weight gradient of a site whose keep lists are all the identity (p = 0,
 // or the dense comparison mode, where the mask zeroes the dropped rows):
 // every row takes part at every t, so the accumulators stay in registers
@@ -1545,44 +1202,15 @@ constexpr size_t wgrad_full_lds_bytes() { return (size_t)WG_NWV * (WgTiles<T>::N
 // others the row-sparse one; either way every workgroup runs every step, so
 // the two kinds overlap instead of taking a launch each.
 template <typename T, bool MASKED, bool MULTI>
-__global__ void __launch_bounds__(128 * WG_NWV) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 && !MULTI ? 4 : 1))) k_wgrad(WgBatch bt) {
+__global__ void __launch_bounds__(128 * WG_NWV) k_wgrad(WgBatch bt) {
     extern __shared__ float acc_lds[];
     const WgArgs& a = bt.p[blockIdx.z];
     if (bt.status && *bt.status != 0) {        // the step's recurrence timed out: NaN in every output
         wgrad_poison(a);
         return;
     }
-    if (a.full) {
-        if constexpr (sizeof(T) == 2) {
-            if (a.staged) wgrad_full_staged<T, MASKED>(a, acc_lds);
-            else wgrad_full<T, MASKED, WgTiles<T>::N / 2, MULTI>(a, acc_lds);
-        } else wgrad_full<T, MASKED, WgTiles<T>::N / 2, MULTI>(a, acc_lds);
-    } else if constexpr (sizeof(T) == 2) {
-        if (a.staged) wgrad_staged<T>(a, acc_lds);
-        else wgrad_gather<T, MULTI>(a, acc_lds);
-    } else wgrad_gather<T, MULTI>(a, acc_lds);
-}
-
-// 4 waves of 2 column tiles: each row fragment read from LDS feeds two
-// products (8 waves of one tile: 43 us at LM-medium against 41), 145
-// registers, 3 waves per SIMD, 3 workgroups per CU
-constexpr int WFS_FS_CT = 2;
-constexpr int WFS_FS_THREADS = 512 / WFS_FS_CT;
-constexpr int WFS_FS_WPE = 3;
-
-// The same pass when every problem runs on the staged full kernel (bf16,
-// batch <= 32): built on its own for three workgroups per CU, so that a
-// pass's workgroups (the grid is 64 per 1024 gradient columns and problem)
-// mostly run in one round.
-template <bool MASKED>
-__global__ void __launch_bounds__(WFS_FS_THREADS) __attribute__((amdgpu_waves_per_eu(WFS_FS_WPE))) k_wgrad_fs(WgBatch bt) {
-    extern __shared__ float stage_lds[];
-    const WgArgs& a = bt.p[blockIdx.z];
-    if (bt.status && *bt.status != 0) {
-        wgrad_poison(a);
-        return;
-    }
-    wgrad_full_staged<bf16, MASKED, WFS_FS_CT>(a, stage_lds);
+    if (a.full) wgrad_full<T, MASKED, WgTiles<T>::N / 2, MULTI>(a, acc_lds);
+    else wgrad_gather<T, MULTI>(a, acc_lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1764,22 +1392,27 @@ __global__ void __launch_bounds__(256) k_case1_undrop(const float* dx, const uin
 // gradient kernels above (K = the LSTM output width, G = the vocabulary);
 // these kernels prepare their operands.
 
-// y [T][B][F] f32 -> yb [T][B][F] and ybT [T][F][BP] in the compute type
-// (rows b >= B of ybT are zero).  grid (ceil(F/32), BP/32, T), block 256.
+// y [T][B][F] f32 -> yb [T][B][ld] and, with ybT, [T][F][BP] in the compute type
+// (rows b >= B of ybT are zero); bf16: times the output mask (the weight gradient's
+// operand; the forward reads kept columns only).  grid (ceil(F/32), BP/32, T),
+// block 256.
 template <typename T>
-__global__ void __launch_bounds__(256) k_head_prep(const float* y, T* yb, T* ybT, int B, int F, int BP) {
+__global__ void __launch_bounds__(256) k_head_prep(const float* y, T* yb, T* ybT, SiteView site, int B, int F, int BP,
+                                                   int ld) {
     __shared__ float tile[32][33];
     const int f0 = blockIdx.x * 32, b0 = blockIdx.y * 32, t = blockIdx.z;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5, fc = f0 + tx;
+    const bool kept = sizeof(T) == 4 || (fc < F && site.mask[(size_t)t * site.kmax + fc] != 0);
     for (int r = ty; r < 32; r += 8) {
-        const int b = b0 + r, f = f0 + tx;
+        const int b = b0 + r;
         float v = 0.0f;
-        if (b < B && f < F) {
-            v = y[((size_t)t * B + b) * F + f];
-            yb[((size_t)t * B + b) * F + f] = from_f32<T>(v);
+        if (b < B && fc < F) {
+            if (kept) v = y[((size_t)t * B + b) * F + fc];
+            yb[((size_t)t * B + b) * ld + fc] = from_f32<T>(v);
         }
         tile[r][tx] = v;
     }
+    if (!ybT) return;
     __syncthreads();
     for (int r = ty; r < 32; r += 8) {
         const int f = f0 + r, b = b0 + tx;
@@ -1896,8 +1529,9 @@ __device__ __forceinline__ void st8(float* dst, const float* v) {
 }
 
 // dz = (softmax(z) - onehot(target)) / N on rows that count, 0 elsewhere,
-// written in the compute type twice: fragment-major per t (the A operand of
-// the dX product) and transposed [T][V][BP] (the weight-gradient operand).
+// written in the compute type fragment-major per t (the A operand of the dX
+// product; in bf16 also of the weight gradient) and, in fp32, transposed
+// [T][V][BP] (the weight-gradient operand).
 // grid (ceil(V/64), T), block 256: a workgroup owns 64 columns of one t and
 // walks the rows 32 at a time through an LDS tile.
 template <typename T>
@@ -1935,7 +1569,7 @@ __global__ void __launch_bounds__(256) k_ce_grad(const float* z, const int32_t* 
                                                         : 0.0f;
         }
         __syncthreads();
-        {   // transposed: thread -> column v0 + tid/4, rows 8*(tid%4) .. +7
+        if constexpr (sizeof(T) == 4) {        // transposed: thread -> column v0 + tid/4, rows 8*(tid%4) .. +7
             const int v = v0 + (tid >> 2), r0 = 8 * (tid & 3);
             if (v < V) {
                 float o[8];
@@ -2168,47 +1802,18 @@ void launch_dx(const DxArgs& a, int K, hipStream_t st) {
     else if (a.B <= 32) launch_k(KID_DX, k_dx<T, 2>, grid, dim3(256), 0, st, a);
     else launch_k(KID_DX, k_dx<T, 4>, grid, dim3(256), 0, st, a);
 }
-void launch_wgrad_big(const WgBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
-void launch_wgrad_gemm(const WgBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
 int setup_big_attributes();
-// LSTM_SD_WGRAD_GEMM=0: the large-batch weight gradients on the row-sparse
-// kernel (per-step gathered rows) instead of the mask-multiplied GEMM
-static bool use_wgrad_gemm() {
-    const char* v = getenv("LSTM_SD_WGRAD_GEMM");
-    return !(v && v[0] == '0');
-}
-
-// LSTM_SD_WGRAD_STAGED=0 keeps row-sparse problems on the unstaged kernel
-static bool use_wgrad_staged() {
-    const char* v = getenv("LSTM_SD_WGRAD_STAGED");
-    return !(v && v[0] == '0');
-}
-// Whether a row-sparse problem (bf16, batch <= 32) runs on the full kernel
-// with its rows times the mask byte instead of the row-sparse scatter.  At a
-// batch this small a step's products are nearly free, while the scatter
-// pays, at every step, a chain of dependent reads (keep-list range, entries,
-// rows) and an LDS read-modify-write of every kept row; measured at hidden
-// 650 and 256 (batch 20 and 32) and at the AWD-LSTM shape, the full kernel
-// is faster at every rate from 0.3 to 0.9, so it is the default there.
-// LSTM_SD_WGRAD_ROWSPARSE=1 takes the scatter.
-static bool wgrad_as_full() {
-    const char* v = getenv("LSTM_SD_WGRAD_ROWSPARSE");
-    return !(v && v[0] == '1');
+// the bf16 weight gradients of a pass
+void launch_wgrad_bf16(WrBatch& b, hipStream_t st) {
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (g_timer_kid == KID_WGRAD && b.np) { e0 = timer_event(); e1 = timer_event(); }
+    launch_wgrad_rows(b, st, e0, e1);
 }
 
 template <typename T>
 void launch_wgrad(const WgBatch& b, hipStream_t st) {
     if (b.np == 0) return;
-    // bf16 past 32 batch rows: one GEMM per problem over every (step, batch
-    // row) pair, rows times the mask byte; or (LSTM_SD_WGRAD_GEMM=0) the
-    // large-batch row-sparse kernel where it applies
-    if (sizeof(T) == 2 && (b.big || b.p[0].B > 32) && (use_wgrad_gemm() || b.big)) {
-        hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (g_timer_kid == KID_WGRAD) { e0 = timer_event(); e1 = timer_event(); }
-        if (use_wgrad_gemm()) launch_wgrad_gemm(b, st, e0, e1);
-        else launch_wgrad_big(b, st, e0, e1);
-        return;
-    }
     WgBatch bs = b;
     const WgArgs& a = bs.p[0];                 // the problems share G, B and the mode
     const int ncb = (a.G + WG_NB - 1) / WG_NB;  // column blocks (wg_slot: 8 XCDs x 8 slices each)
@@ -2217,37 +1822,14 @@ void launch_wgrad(const WgBatch& b, hipStream_t st) {
     bool multi = a.B > 32;                     // builds with the extra loops (batch chunks, tile rounds)
     for (int i = 0; i < bs.np; ++i) {
         WgArgs& p = bs.p[i];
-        p.staged = p.fullmask = 0;
         if (p.full) {
-            if (sizeof(T) == 2 && p.B <= 32 && use_wgrad_staged()) {
-                p.staged = 1;
-                lds = std::max(lds, WFS_LDS);
-            } else lds = std::max(lds, wgrad_full_lds_bytes<T>());
-            continue;
-        }
-        if (sizeof(T) == 2 && p.B <= 32 && use_wgrad_staged() && wgrad_as_full()) {
-            p.full = p.staged = p.fullmask = 1;
-            lds = std::max(lds, WFS_LDS);
-            continue;
-        }
-        if (sizeof(T) == 2 && p.B <= 32 && wgs_rows(p.K) <= WGS_MAX_ROWS && wgs_lds_bytes(p.K, p.T) <= WGS_MAX_LDS &&
-            use_wgrad_staged()) {
-            p.staged = 1;
-            lds = std::max(lds, wgs_lds_bytes(p.K, p.T));
+            lds = std::max(lds, wgrad_full_lds_bytes<T>());
             continue;
         }
         lds = std::max(lds, wgrad_lds_bytes<T>(p.K));
         multi = multi || (p.K + NSEG - 1) / NSEG > 16 * (WgTiles<T>::N / 2);
     }
     const dim3 blk(128 * WG_NWV);
-    bool all_fs = sizeof(T) == 2;
-    for (int i = 0; i < bs.np; ++i) all_fs = all_fs && bs.p[i].full && bs.p[i].staged;
-    if (all_fs) {
-        const dim3 bfs(WFS_FS_THREADS);
-        if (a.dense) launch_k(KID_WGRAD, k_wgrad_fs<true>, grid, bfs, WFS_LDS, st, bs);
-        else launch_k(KID_WGRAD, k_wgrad_fs<false>, grid, bfs, WFS_LDS, st, bs);
-        return;
-    }
     if (a.dense) {
         if (multi) launch_k(KID_WGRAD, k_wgrad<T, true, true>, grid, blk, lds, st, bs);
         else launch_k(KID_WGRAD, k_wgrad<T, true, false>, grid, blk, lds, st, bs);
@@ -2268,12 +1850,13 @@ void launch_emb_grad(const int32_t* tokens, int N, int B, int V, const float* dx
              B, V, dx, nr0, I, d_emb);
 }
 template <typename T>
-void launch_head_prep(const float* y, void* yb, void* ybT, int T_, int B, int F, int BP, hipStream_t st) {
-    launch_k(KID_NONE, k_head_prep<T>, dim3((F + 31) / 32, BP / 32, T_), dim3(256), 0, st, y, (T*)yb, (T*)ybT, B, F,
-             BP);
+void launch_head_prep(const float* y, void* yb, void* ybT, const SiteView& site, int T_, int B, int F, int BP, int ld,
+                      hipStream_t st) {
+    launch_k(KID_NONE, k_head_prep<T>, dim3((F + 31) / 32, BP / 32, T_), dim3(256), 0, st, y, (T*)yb, (T*)ybT, site, B,
+             F, BP, ld);
 }
-template void launch_head_prep<float>(const float*, void*, void*, int, int, int, int, hipStream_t);
-template void launch_head_prep<bf16>(const float*, void*, void*, int, int, int, int, hipStream_t);
+template void launch_head_prep<float>(const float*, void*, void*, const SiteView&, int, int, int, int, int, hipStream_t);
+template void launch_head_prep<bf16>(const float*, void*, void*, const SiteView&, int, int, int, int, int, hipStream_t);
 void launch_ce_loss(const float* z, const int32_t* tgt, const int32_t* lengths, int T_, int B, int V, float* lse,
                     float* rowloss, float* rowok, float* loss, float* ninv, hipStream_t st) {
     launch_k(KID_CE, k_ce_rows, dim3((unsigned)((long)T_ * B)), dim3(256), 0, st, z, tgt, lengths, B, V, lse, rowloss,
@@ -2320,10 +1903,8 @@ static int g_attr_done = 0;
 int setup_kernel_attributes() {
     if (g_attr_done) return 0;
     const int lds = 160 * 1024 - 1024;     // (the kernels also hold up to 1 KB of static LDS)
-    const void* fns[8] = {(const void*)k_wgrad<float, false, false>, (const void*)k_wgrad<bf16, false, false>,
-                          (const void*)k_wgrad<float, true, false>, (const void*)k_wgrad<bf16, true, false>,
-                          (const void*)k_wgrad<float, false, true>, (const void*)k_wgrad<bf16, false, true>,
-                          (const void*)k_wgrad<float, true, true>, (const void*)k_wgrad<bf16, true, true>};
+    const void* fns[4] = {(const void*)k_wgrad<float, false, false>, (const void*)k_wgrad<float, true, false>,
+                          (const void*)k_wgrad<float, false, true>, (const void*)k_wgrad<float, true, true>};
     for (const void* f : fns)
         if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds) != hipSuccess) return LSTM_SD_EHIP;
     if (setup_big_attributes()) return LSTM_SD_EHIP;
@@ -2336,9 +1917,9 @@ int setup_kernel_attributes() {
     template void launch_step<T>(const StepArgs&, int, hipStream_t);                        \
     template void launch_bwd<T>(const BwdArgs&, int, hipStream_t);                          \
     template void launch_dx<T>(const DxArgs&, int, hipStream_t);                            \
-    template void launch_wgrad<T>(const WgBatch&, hipStream_t);                             \
 
 LSD_INST(float)
 LSD_INST(bf16)
+template void launch_wgrad<float>(const WgBatch&, hipStream_t);
 
 }  // namespace lsd

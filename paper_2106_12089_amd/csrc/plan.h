@@ -17,9 +17,10 @@ struct Plan {
     int esize;            // bytes per element of x/W/U/h copies
     int G;                // 4H
     int BP;               // batch rounded up to 32 (transposed copies)
-    int MGc;              // number of 64-row groups of the batch
+    int IP, DHP;          // I, D*H rounded up to 8 (row pitches of the bf16 masked copies)
     int sites, kmax, kin_max;
-    int HP;               // H rounded up to 8 (row pitch of the per-step h buffer)
+    int HP;               // H rounded up to 8 (row pitch of the per-step h buffer and the masked copy of h)
+    int da_regs;          // DA regions: every (layer, direction), or one set of directions that the layers reuse
     int mtiles;           // 16-row tiles of the batch
     size_t das, hxs;      // elements of one fragment-major DA block / h exchange slot
     size_t xxs;           // elements of one layer-input exchange slot (stacked forward)
@@ -28,9 +29,10 @@ struct Plan {
     size_t m_mask, m_keep, m_pos, m_count, m_drop, m_dcount, m_kseg, m_dseg, m_total;
 
     // reserve
-    size_t r_gates, r_c, r_hrecT, r_dir_bytes;  // inside one (l, d) block
-    size_t r_xT, r_h0T;                         // layer-0 input and h0, transposed
-    size_t r_ybuf_base, r_ybuf_bytes;           // per layer l < L-1: ybuf then ybufT
+    size_t r_gates, r_c, r_hrecT, r_dir_bytes;  // inside one (l, d) block (r_hrecT: f32 h transposed; bf16 masked h_{t-1})
+    size_t r_xT, r_h0T;                         // layer-0 input (bf16: from 64 rows) and h0 (f32), transposed
+    size_t r_xm;                                // bf16: the masked layer-0 input
+    size_t r_ybuf_base, r_ybuf_bytes;           // per layer l < L-1: ybuf (bf16: masked) then ybufT (bf16: from 64 rows)
     size_t r_ybufT_off;                         // offset of ybufT inside a layer block
     size_t r_total;
 

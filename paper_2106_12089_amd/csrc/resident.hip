@@ -188,14 +188,14 @@ __device__ __forceinline__ uint32_t half_of(uint2 x, int v) { return half_of(v &
 // keep both the stores and these loads free of bank conflicts.
 constexpr int RF_QP = 17, RF_FP = 4 * RF_QP;               // float4 pitches in red
 __host__ __device__ constexpr int rf_wpitch(int NTL) { return 16 * NTL + 8; }   // staged weight row (elements)
-// LDS: red, later rows of it staged weights; then the transposed stages
+// LDS: red (first the staged weights); then the transposed stage
 template <int NTL, int MT>
 constexpr size_t rf_red_bytes() {
     const size_t r = (size_t)8 * NTL * MT * RF_FP * 16, s = (size_t)8 * 32 * rf_wpitch(NTL) * 2;
     return r > s ? r : s;
 }
 template <int NTL, int MT>
-constexpr size_t rf_lds_bytes() { return rf_red_bytes<NTL, MT>() + (size_t)4 * 4 * NTL * (16 * MT + 8) * 2; }
+constexpr size_t rf_lds_bytes() { return rf_red_bytes<NTL, MT>() + (size_t)2 * 4 * NTL * (16 * MT + 8) * 2; }
 
 template <int KC, int NTL, int MT>
 __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
@@ -207,8 +207,7 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
     constexpr int SP = MG + 8;                             // row pitch of a transposed stage (elements)
     extern __shared__ __align__(16) char smem[];
     float4* red = (float4*)smem;                           // [8 waves][NF][RF_FP]
-    bf16* sth = (bf16*)(smem + rf_red_bytes<NTL, MT>());   // [2][UT][SP] h_t of the tile, transposed
-    bf16* sty = sth + 2 * UT * SP;                         // [2][UT][SP] its masked-by-length copy
+    bf16* sty = (bf16*)(smem + rf_red_bytes<NTL, MT>());   // [2][UT][SP] layer output of the tile, transposed
     __shared__ int len_s[MG];                              // lengths of the rows
     const int H = a.H, G = 4 * H, B = a.B, T_ = a.T;
     const int total = a.nslots * a.mgroups * a.ntiles;
@@ -412,19 +411,17 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
                 for (int k = 0; k < 4; ++k) gxr[q][k] = gp[k * H];
             }
             mnx[q] = D.rmask[(size_t)tn * a.kmax + r.u];
-            if (D.xout) mup[q] = D.umask[(size_t)t * a.kmax + r.u];
+            if (D.umask) mup[q] = D.umask[(size_t)t * a.kmax + r.u];
         }
     };
-    // rows of h_t^T (and of the layer output's) staged at step s, 4 at a time
+    // rows of the transposed layer output staged at step s, 4 at a time
     auto store_transposed = [&](int s) {
         const int t = step_t(s), p = tid - P0;
         if (p < 0 || p >= UT * 4 * MT) return;
         const int u = p / (4 * MT), col = 4 * (p % (4 * MT));
         if (u0 + u >= H || m0 + col >= m1) return;
         const int o = (s & 1) * UT * SP + u * SP + col;
-        *(uint2*)((bf16*)D.hrecT + ((size_t)t * H + u0 + u) * a.BP + m0 + col) = *(const uint2*)(sth + o);
-        if (D.ybuf)
-            *(uint2*)((bf16*)D.ybufT + ((size_t)t * a.ldy + u0 + u) * a.BP + m0 + col) = *(const uint2*)(sty + o);
+        *(uint2*)((bf16*)D.ybufT + ((size_t)t * a.ldy + u0 + u) * a.BP + m0 + col) = *(const uint2*)(sty + o);
     };
     int done = 0;                                          // steps whose outputs are staged
     // prologue: h0 times the first step's RH mask into slot 0
@@ -476,9 +473,10 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
             if (D.xout) store_coherent((bf16*)D.xout + (size_t)t * hxs, hxs, o, (vq && mup[q]) ? f2bf(hnv[q]) : (bf16)0);
         }
         res_arrive(a.bar, g, tile);
-        // outputs only later kernels read, and the next step's inputs.  The
-        // transposed copies go through LDS: staged here, stored as 16-byte
-        // pieces of a unit's rows a step later (past the barriers between)
+        // outputs only later kernels read, and the next step's inputs.  A
+        // transposed copy goes through LDS: staged here, stored as pieces of a
+        // unit's rows a step later (past the barriers between)
+        const int tn = step_t(min(s + 1, T_ - 1));
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
             const Pair r = pair_of(q, th);
@@ -487,22 +485,22 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
             const float cn = vq ? cnv[q] : creg[q], hn = vq ? hnv[q] : hreg[q];
             creg[q] = cn;
             hreg[q] = hn;
-            const bf16 hv = r.ok ? f2bf(hn) : (bf16)0, yv = r.ok && vq ? hv : (bf16)0;
-            sth[(s & 1) * UT * SP + r.s] = hv;
-            if (D.ybuf) sty[(s & 1) * UT * SP + r.s] = yv;
+            const bf16 hv = f2bf(hn), yv = r.ok && vq && mup[q] ? hv : (bf16)0;
+            if (D.ybufT) sty[(s & 1) * UT * SP + r.s] = yv;
             if (!r.ok) continue;
             const size_t o = (size_t)t * B + r.b;
+            if (s + 1 < T_) ((bf16*)D.hm)[((size_t)tn * B + r.b) * a.ldh + r.u] = mnx[q] ? hv : (bf16)0;
             *(float4*)(D.gates + o * G + 4 * r.u) = make_float4(og4[q][0], og4[q][1], og4[q][2], og4[q][3]);
             D.cres[o * H + r.u] = cn;
             if (D.y) D.y[o * a.ldy + r.u] = vq ? hn : 0.0f;
-            if (D.ybuf) ((bf16*)D.ybuf)[o * a.ldy + r.u] = yv;
+            if (D.ybuf) ((bf16*)D.ybuf)[o * a.ldyb + r.u] = yv;
         }
-        if (s > 0) store_transposed(s - 1);
+        if (D.ybufT && s > 0) store_transposed(s - 1);
         prefetch(s + 1);
         done = s + 1;
     }
     lds_barrier();
-    if (done > 0) store_transposed(done - 1);
+    if (D.ybufT && done > 0) store_transposed(done - 1);
     // final state (NaN if a barrier wait timed out, and then every step of y)
     const bool failed = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
 #pragma unroll
@@ -532,12 +530,11 @@ template <int KB, int KL, int NB, int MT, int R>
 __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
     constexpr int UB = 16 * NB, MG = 16 * MT, NF = NB * MT, NP = NF * 256, NTH = 512, NW = 8, KR = KB - KL;
     constexpr int PPT = (NP + NTH - 1) / NTH, P0 = NP <= NTH ? (NTH - NP) / 64 * 64 : 0;
-    constexpr int FW = RB_FP, SP = MG + 8;                 // SP: row pitch of the transposed stage (elements)
+    constexpr int FW = RB_FP;
     extern __shared__ __align__(16) char smem[];
     float* red = (float*)smem;                             // [8 waves][NF][FW]
     __shared__ int len_s[MG];                              // lengths of the rows
-    bf16* std_ = (bf16*)(smem + (size_t)NW * NF * FW * 4); // [2][4*UB][SP] DA of the tile, transposed
-    uint4* ul = (uint4*)(smem + (size_t)NW * NF * FW * 4 + (size_t)2 * 4 * UB * SP * 2);   // [8 waves][KL][NB][64]
+    uint4* ul = (uint4*)(smem + (size_t)NW * NF * FW * 4); // [8 waves][KL][NB][64]
     const int H = a.H, G = 4 * H, B = a.B, T_ = a.T;
     const int total = a.nslots * a.mgroups * a.ntiles;
     int g, tile;
@@ -577,17 +574,16 @@ __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
     }
     lds_barrier();                                         // (the lengths)
     // pair q of this thread (derived anew per step, as in the forward)
-    struct Pair { int b, u, i, s; bool in, ok; };          // i: its word in red; s: its element (gate 0) in the stage
+    struct Pair { int b, u, i; bool ok; };                 // i: its word in red
     auto pair_of = [&](int q, int th) {
         Pair r;
         const int p = th - P0 + NTH * q;
-        r.in = p >= 0 && p < NP;
-        const int u = r.in ? p % UB : 0, row = r.in ? p / UB : 0;
+        const bool in = p >= 0 && p < NP;
+        const int u = in ? p % UB : 0, row = in ? p / UB : 0;
         r.b = m0 + row;
         r.u = u0 + u;
         r.i = ((row >> 4) * NB + (u >> 4)) * FW + ((u >> 2) & 3) * RB_QP + (row & 15) * 4 + (u & 3);
-        r.s = u * SP + row;
-        r.ok = r.in && r.b < m1 && r.u < H;
+        r.ok = in && r.b < m1 && r.u < H;
         if (!r.ok) { r.b = m0; r.u = u0; }
         return r;
     };
@@ -700,18 +696,6 @@ __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
             mkr[q] = D.mask[(size_t)tn * a.kmax + r.u];
         }
     };
-    // rows of DA_t^T staged at step s
-    auto store_transposed = [&](int s) {
-        const int t = step_t(s);
-        bf16* dat = (bf16*)D.daT + (size_t)t * G * a.BP;
-        for (int p = tid < P0 ? 4 * UB * 4 * MT : tid - P0; p < 4 * UB * 4 * MT; p += NTH - P0) {
-            const int gu = p / (4 * MT), col = 4 * (p % (4 * MT)), u = u0 + gu % UB;
-            if (u < H && m0 + col < m1)
-                *(uint2*)(dat + (size_t)((gu / UB) * H + u) * a.BP + m0 + col) =
-                    *(const uint2*)(std_ + (s & 1) * 4 * UB * SP + gu * SP + col);
-        }
-    };
-    int done = 0;                                          // steps whose DA is staged
     prefetch(0);
     bool good = true;
     for (int s = 0; s <= T_; ++s) {
@@ -733,10 +717,8 @@ __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
         }
         if (s > 0) product((const bf16*)D.da + (size_t)tn * das);
         const __amdgpu_buffer_rsrc_t dw = buf_rsrc((const bf16*)D.da + (size_t)max(t, 0) * das, (uint32_t)(das * 2));
-        uint2 dpk[PPT];                                     // DA of the pair: gates i, f | g, o
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
-            dpk[q] = make_uint2(0u, 0u);
             const Pair r = pair_of(q, th);
             if (!r.ok) continue;
             float dh = dhc[q];
@@ -763,35 +745,15 @@ __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
             } else {
                 dhc[q] = dh;                                           // frozen row: pass through
             }
-            bf16 d4[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                d4[k] = f2bf(da4[k]);
-                __builtin_amdgcn_raw_buffer_store_b16(d4[k], dw, (uint32_t)frag_off(r.b, k * H + r.u, nch) * 2u, 0,
+            for (int k = 0; k < 4; ++k)
+                __builtin_amdgcn_raw_buffer_store_b16(f2bf(da4[k]), dw, (uint32_t)frag_off(r.b, k * H + r.u, nch) * 2u, 0,
                                                       CPOL_SC1);
-            }
-            dpk[q] = make_uint2((uint32_t)d4[0] | ((uint32_t)d4[1] << 16), (uint32_t)d4[2] | ((uint32_t)d4[3] << 16));
         }
         if (final_pass) break;
         res_arrive(a.bar, g, tile);                         // DA_t is published
-        // DA^T (the weight gradients' operand) through LDS: staged here, stored
-        // as 16-byte pieces a step later
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-            const Pair r = pair_of(q, th);
-            if (!r.in) continue;
-            bf16* st = std_ + (s & 1) * 4 * UB * SP + r.s;
-            st[0] = (bf16)(dpk[q].x & 0xffffu);
-            st[UB * SP] = (bf16)(dpk[q].x >> 16);
-            st[2 * UB * SP] = (bf16)(dpk[q].y & 0xffffu);
-            st[3 * UB * SP] = (bf16)(dpk[q].y >> 16);
-        }
-        if (s > 0) store_transposed(s - 1);
-        done = s + 1;
         prefetch(s + 1);
     }
-    lds_barrier();
-    if (done > 0) store_transposed(done - 1);
     // a timed-out barrier, here or in the forward pass of the step, poisons
     // the input-state gradients
     if (!good || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
@@ -822,7 +784,7 @@ static int cu_count() {
 }
 
 // A tiling of a launch: the unit tile and row tile classes, the rows of a group
-// (a multiple of 4: the transposed copies are stored 4 rows at a time), and the
+// (a multiple of 4: a transposed copy is stored 4 rows at a time), and the
 // groups that one launch takes (more rows run as further launches: rows are
 // independent).
 struct Tiling { int ni, mt, ntiles, rg, mg, gpl, gpx, launches; double cost; };
@@ -981,7 +943,7 @@ hipError_t launch_bwd_res(RBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t 
     if (t.ni < 0) return hipErrorInvalidValue;
     int kl = 0, r = 0;
     void (*fn)(RBwdArgs) = bwd_res_pick(kb, t.ni, t.mt, &kl, &r);
-    const size_t lds = (size_t)8 * t.ni * t.mt * RB_FP * 4 + (size_t)2 * 4 * 16 * t.ni * (16 * t.mt + 8) * 2 +
+    const size_t lds = (size_t)8 * t.ni * t.mt * RB_FP * 4 +
                        (size_t)8 * kl * t.ni * 1024;
     return launch_groups(fn, a, t, lds, st, timer_on, e0, e1);
 }
