@@ -26,6 +26,9 @@ template <typename T> void launch_bwd(const BwdArgs& a, int D, hipStream_t st);
 template <typename T> void launch_dx(const DxArgs& a, int K, hipStream_t st);
 template <typename T> void launch_wgrad(const WgBatch& b, hipStream_t st);
 void launch_wgrad_bf16(WrBatch& b, hipStream_t st);
+void launch_fx_bf16(RowsArgs& a, hipStream_t st);
+void launch_dx_bf16(RowsArgs& a, size_t part_bytes, hipStream_t st);
+void launch_prep_bf16(const FxArgs& a, hipStream_t st);
 void launch_bwd_init(const float*, const float*, float*, float*, long, void*, int, int, int, long, long, unsigned*, int*,
                      hipStream_t);
 void launch_emb_grad(const int32_t*, int, int, int, const float*, const SiteView&, int, float*, hipStream_t);
@@ -77,6 +80,27 @@ static int fail(int code, const std::string& msg) {
 }
 
 static float inv_keep(double p) { return p > 0.0 ? (float)(1.0 / (1.0 - p)) : 1.0f; }
+
+// Whether layer l's input product (bf16) runs as one product over all rows or as a
+// product per step over its kept neurons, and the same of its input gradient (us at
+// 20 steps, hidden 650 / 1024 / 1500, product + gradient, p = 0.5 and 0.65):
+//   batch  64:  44 /  80 / 158 over rows,  92 / 140 / 317 and  87 / 130 / 298 per step
+//   batch 128:  57 / 178 / 282 over rows,  96 / 223 / 328 and  92 / 213 / 309 per step
+//   batch 256: 107 / 384 / 427 over rows, 107 / 311 / 355 and 104 / 294 / 336 per step
+// so the line lies at 256 rows a step: from there the per-step kernels' 256-row tiles are
+// full and skipping pays.  It pays only above half the neurons dropped where the
+// products over rows fill the chip with 256 x 256 tiles (64 steps x batch 256 x hidden
+// 1024, p = 0.5: 349 against 368 us the products, 289 against 349 the gradients); the
+// dense mode skips nothing.
+static bool skip_pays(const Plan& P, int l) { return P.B >= 256 && P.compact && P.p_nr[l] > 0.0f; }
+static bool fx_rows(const Plan& P, int l) {
+    const long tiles = (long)((P.T * P.B + 255) / 256) * ((P.G + 255) / 256) * P.D;
+    return P.dtype == LSTM_SD_DTYPE_BF16 && !(skip_pays(P, l) && (P.p_nr[l] > 0.5f || tiles < 1024));
+}
+static bool dx_rows(const Plan& P, int l) {
+    const long tiles = (long)((P.T * P.B + 255) / 256) * ((P.kin(l) + 255) / 256);
+    return P.dtype == LSTM_SD_DTYPE_BF16 && !(skip_pays(P, l) && (P.p_nr[l] > 0.5f || tiles < 208));
+}
 
 int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     if (!d) { *why = "dims is NULL"; return LSTM_SD_EINVAL; }
@@ -145,7 +169,9 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     off = 0;
     q.r_gates = off; off = align_up(off + T * B * G * 4, A);
     q.r_c = off;     off = align_up(off + T * B * H * 4, A);
-    const bool b16 = es == 2, xt = !b16 || B >= 64;   // (bf16: transposed inputs feed the large-batch products only)
+    const bool b16 = es == 2;
+    bool xt = !b16;                           // (bf16: transposed inputs feed the per-step products only)
+    for (int l = 0; l < q.L; ++l) xt = xt || !fx_rows(q, l);
     q.r_hrecT = off; off = align_up(off + (b16 ? T * B * (size_t)q.HP : T * H * BP) * es, A);
     q.r_dir_bytes = off;
     off = (size_t)q.L * D * q.r_dir_bytes;
@@ -172,6 +198,14 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     q.da_regs = b16 && (size_t)q.L * D * q.das <= NR * (q.das + G * BP) ? q.L * (int)D : (int)NR;
     q.w_da = off;     off = align_up(off + (size_t)q.da_regs * T * (size_t)q.das * es, A);
     q.w_daT = off;    off = align_up(off + (b16 ? 0 : NR * T * G * BP * es), A);
+    // bf16: what that leaves holds the partial sums of split input gradients
+    q.w_part = off;
+    q.part_bytes = 0;
+    if (b16) {
+        const size_t most = NR * T * (q.das + G * BP) * es, used = (size_t)q.da_regs * T * q.das * es;
+        q.part_bytes = most > used ? (most - used) / A * A : 0;
+        off += q.part_bytes;
+    }
     q.w_dxw = off;    off = align_up(off + (size_t)(q.L - 1) * T * B * H * 4, A);
     q.w_dc = off;     off = align_up(off + D * B * H * 4, A);
     q.w_dhc = off;    off = align_up(off + D * B * H * 4, A);
@@ -194,13 +228,6 @@ static bool use_stacked() {
 // LSTM_SD_FWD_WORKERS=0: a stacked fp32 forward without input-product workers
 static bool use_fwd_workers() {
     const char* v = getenv("LSTM_SD_FWD_WORKERS");
-    return !(v && v[0] == '0');
-}
-
-// LSTM_SD_GEMM_BIG=0: the input products and input gradients of a large
-// batch on the small-batch kernels
-static bool use_gemm_big() {
-    const char* v = getenv("LSTM_SD_GEMM_BIG");
     return !(v && v[0] == '0');
 }
 
@@ -309,17 +336,16 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
     char* R = (char*)reserve;
     char* W = (char*)ws;
     // x (T matrices) and h0 (L*D matrices) as the weight gradients read them
-    // (fp32: transposed; bf16: masked), and the pass initialised (hT, cT, barrier counters): these ride on the first input
-    // product launch (independent work, one launch less)
+    // (fp32: transposed; bf16: masked), and the pass initialised (hT, cT, barrier
+    // counters): in fp32 these ride on the first input product launch (independent
+    // work, one launch less), in bf16 that product reads the masked copy
     TransArgs tr;
     memset(&tr, 0, sizeof(tr));
     tr.src = x; tr.dst = R + P.r_xT; tr.B = B; tr.K = P.I; tr.BP = BP; tr.n1 = T;
     tr.src2 = h0; tr.dst2 = R + P.r_h0T; tr.K2 = H;
     const bool b16 = std::is_same<E, bf16>::value;
-    // large batches (bf16): the input products read the transposed inputs
-    const bool gemm_big = b16 && B >= 64 && use_gemm_big();
     if (b16) {
-        if (!gemm_big) tr.dst = nullptr;
+        if (fx_rows(P, 0)) tr.dst = nullptr;
         tr.dst2 = nullptr;
         tr.xm = R + P.r_xm; tr.ldm = P.IP;
         tr.mask = site_view(P, mbuf, P.site_nr(0)).mask;
@@ -380,6 +406,27 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
     auto launch_fx_layer = [&](int l) {
         const int kin = P.kin(l);
         const void* X = l == 0 ? x : (const void*)(R + P.rybuf(l - 1));
+        if (b16 && fx_rows(P, l)) {
+            if (l == 0) {                     // the masked input first
+                FxArgs f;
+                memset(&f, 0, sizeof(f));
+                attach_tr(f);
+                if (f.tr_gz > 0) launch_prep_bf16(f, st);
+            }
+            RowsArgs f;
+            memset(&f, 0, sizeof(f));
+            f.R = T * B; f.B = B; f.K = kin; f.G = G;
+            f.x = l == 0 ? (const void*)(R + P.r_xm) : X;
+            f.lda = l == 0 ? P.IP : P.DHP;
+            f.np = D; f.s = P.s_nr[l];
+            for (int d = 0; d < D; ++d) {
+                f.W[d] = w->W[l * D + d];
+                f.bias[d] = w->b[l * D + d];
+                f.out[d] = (float*)(W + P.w_gx) + (size_t)d * T * B * G;
+            }
+            launch_fx_bf16(f, st);
+            return;
+        }
         for (int d = 0; d < D; ++d) {
             FxArgs f;
             memset(&f, 0, sizeof(f));
@@ -389,7 +436,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
             f.site = site_view(P, mbuf, P.site_nr(l));
             f.Gx = (float*)(W + P.w_gx) + (size_t)d * T * B * G;
             f.K = kin; f.B = B; f.G = G; f.T = T; f.dense = !P.compact; f.s = P.s_nr[l];
-            if (gemm_big) {
+            if (b16) {
                 f.XT = l == 0 ? (const void*)(R + P.r_xT) : (const void*)(R + P.rybufT(l - 1));
                 f.xt_tstride = (long)kin * BP;
                 f.xt_ld = BP;
@@ -488,7 +535,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
                     x.y = y + d * H;
                 } else {
                     x.ybuf = R + P.rybuf(l) + (size_t)d * H * es;
-                    if (gemm_big && l + 1 == l0 + nl) x.ybufT = R + P.rybufT(l) + (size_t)d * H * BP * es;
+                    if (!fx_rows(P, l + 1) && l + 1 == l0 + nl) x.ybufT = R + P.rybufT(l) + (size_t)d * H * BP * es;
                 }
             }
         }
@@ -572,7 +619,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
                     sd.y = y + (size_t)t * B * D * H + d * H;
                 } else {
                     sd.ybuf = R + P.rybuf(l) + ((size_t)t * B * a.ldyb + d * H) * es;
-                    if (!b16 || gemm_big) sd.ybufT = R + P.rybufT(l) + ((size_t)t * D * H + d * H) * BP * es;
+                    if (!fx_rows(P, l + 1)) sd.ybufT = R + P.rybufT(l) + ((size_t)t * D * H + d * H) * BP * es;
                 }
             }
             launch_step<E>(a, D, st);
@@ -687,19 +734,32 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
     auto layer_dx = [&](int l, int reg0, float* dxc_here) {
         const int kin = P.kin(l);
         const SiteView nv = site_view(P, mbuf, P.site_nr(l));
+        if (dx_rows(P, l)) {
+            RowsArgs f;
+            memset(&f, 0, sizeof(f));
+            f.R = T * B; f.B = B; f.M = kin; f.G = G; f.D = D;
+            f.das = (long)P.das; f.kmax = P.kmax; f.mask = nv.mask; f.status = sync_status;
+            f.part = (float*)(W + P.w_part);
+            f.s = P.s_nr[l];
+            for (int d = 0; d < D; ++d) {
+                f.da[d] = da_of(reg0 + d);
+                f.W[d] = w->W[l * D + d];
+            }
+            f.out[0] = l == 0 ? dx : dxc_here;
+            launch_dx_bf16(f, P.part_bytes, st);
+            return;
+        }
         DxArgs a;
         memset(&a, 0, sizeof(a));
         for (int d = 0; d < D; ++d) {
             a.da[d] = da_of(reg0 + d);
             a.W[d] = w->W[l * D + d];
         }
-        // layer 0 writes the caller's full-width dx directly; full width too
-        // where the layer below reads it by unit
-        a.site = nv; a.out = l == 0 ? dx : dxc_here; a.scatter = l == 0 || res; a.D = D; a.B = B; a.G = G; a.ldo = kin;
+        // layer 0 writes the caller's full-width dx directly; bf16 always full width
+        a.site = nv; a.out = l == 0 ? dx : dxc_here; a.scatter = l == 0 || b16; a.D = D; a.B = B; a.G = G; a.ldo = kin;
         a.T = T; a.K = kin; a.tps = ((kin + 7) / 8 + 15) / 16; a.mtiles = P.mtiles;
         a.dense = !P.compact; a.s = P.s_nr[l];
         a.status = sync_status;
-        a.big = std::is_same<E, bf16>::value && B >= 64 && use_gemm_big();
         launch_dx<E>(a, kin, st);
     };
     // weight and bias gradients (Eq. 11) of layer l: its problems join one
@@ -911,8 +971,8 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
                     bd.dy = dy + (size_t)t * B * D * H + d * H;
                 } else {
                     const SiteView sv = site_view(P, mbuf, P.site_nr(l + 1));
-                    bd.dxc = dxc_above + (size_t)t * B * a.lddx;
-                    bd.dxpos = sv.pos + (size_t)t * P.kmax + d * H;
+                    bd.dxc = dxc_above + (size_t)t * B * a.lddx + (b16 ? d * H : 0);
+                    bd.dxpos = b16 ? nullptr : sv.pos + (size_t)t * P.kmax + d * H;
                 }
                 bd.da = (char*)da_of(reg_of(l) + d) + (size_t)t * P.das * es;
                 if (!b16) bd.daT = (char*)daT_of(d) + (size_t)t * G * BP * es;
@@ -941,6 +1001,7 @@ struct HeadPlan {
     size_t m_mask, m_keep, m_pos, m_count, m_drop, m_dcount, m_kseg, m_dseg, m_total;
     // workspace
     size_t w_yb, w_ybT, w_da, w_daT, w_lse, w_rowloss, w_rowok, w_ninv, w_total;
+    size_t part_bytes;                  // bf16: the space at w_daT for partial input gradients
 };
 
 static int make_head_plan(const lstm_sd_head_dims* d, HeadPlan* p, const char** why) {
@@ -986,7 +1047,9 @@ static int make_head_plan(const lstm_sd_head_dims* d, HeadPlan* p, const char** 
     q.w_yb = off;      off = align_up(off + T * B * (size_t)q.FP * es, A);
     q.w_ybT = off;     off = align_up(off + (es == 4 ? T * F * BP * es : 0), A);
     q.w_da = off;      off = align_up(off + T * q.das * es, A);
-    q.w_daT = off;     off = align_up(off + (es == 4 ? T * V * BP * es : 0), A);
+    // (bf16: partial input gradients, in place of the transposed dz of fp32)
+    q.w_daT = off;     off = align_up(off + T * V * BP * es, A);
+    q.part_bytes = T * V * BP * es;
     q.w_lse = off;     off = align_up(off + T * B * 4, A);
     q.w_rowloss = off; off = align_up(off + T * B * 4, A);
     q.w_rowok = off;   off = align_up(off + T * B * 4, A);
@@ -1020,14 +1083,16 @@ static void head_backward_impl(const HeadPlan& P, const void* W_fc, const int32_
                    ninv, st);
     launch_ce_grad<E>(logits, tgt, lengths, lse, ninv, P.T, P.B, P.V, P.BP, P.mtiles, W + P.w_da, W + P.w_daT, st);
     const SiteView site = head_site(P, mbuf);
-    DxArgs a;
-    memset(&a, 0, sizeof(a));
-    a.da[0] = W + P.w_da; a.W[0] = W_fc;
-    a.site = site; a.out = dy; a.scatter = 1; a.D = 1; a.B = P.B; a.G = P.V; a.ldo = P.F;
-    a.T = P.T; a.K = P.F; a.tps = ((P.F + 7) / 8 + 15) / 16; a.mtiles = P.mtiles;
-    a.dense = !P.compact; a.s = P.s;
-    launch_dx<E>(a, P.F, st);
     if constexpr (std::is_same<E, bf16>::value) {
+        RowsArgs f;
+        memset(&f, 0, sizeof(f));
+        f.R = P.T * P.B; f.B = P.B; f.M = P.F; f.G = P.V; f.D = 1;
+        f.da[0] = W + P.w_da; f.das = (long)P.das; f.W[0] = W_fc;
+        f.kmax = P.F; f.mask = site.mask;
+        f.part = (float*)(W + P.w_daT);
+        f.s = P.s;
+        f.out[0] = dy;
+        launch_dx_bf16(f, P.part_bytes, st);
         WrBatch wr;
         memset(&wr, 0, sizeof(wr));
         wr.np = 1; wr.B = P.B; wr.T = P.T; wr.R = P.T * P.B; wr.G = P.V; wr.das = (long)P.das;
@@ -1037,6 +1102,13 @@ static void head_backward_impl(const HeadPlan& P, const void* W_fc, const int32_
         launch_wgrad_bf16(wr, st);
         return;
     }
+    DxArgs a;
+    memset(&a, 0, sizeof(a));
+    a.da[0] = W + P.w_da; a.W[0] = W_fc;
+    a.site = site; a.out = dy; a.scatter = 1; a.D = 1; a.B = P.B; a.G = P.V; a.ldo = P.F;
+    a.T = P.T; a.K = P.F; a.tps = ((P.F + 7) / 8 + 15) / 16; a.mtiles = P.mtiles;
+    a.dense = !P.compact; a.s = P.s;
+    launch_dx<E>(a, P.F, st);
     WgBatch b;
     memset(&b, 0, sizeof(b));
     b.np = 1;
@@ -1239,6 +1311,7 @@ int lstm_sd_head_forward(const lstm_sd_head_dims* hd, const void* W_fc, const fl
     if (mask_bytes < P.m_total) return fail(LSTM_SD_EWORKSPACE, "mask_bytes smaller than lstm_sd_head_mask_bytes()");
     if (workspace_bytes < P.w_total)
         return fail(LSTM_SD_EWORKSPACE, "workspace_bytes smaller than lstm_sd_head_workspace_bytes()");
+    if (setup_kernel_attributes()) return fail(LSTM_SD_EHIP, "hipFuncSetAttribute failed");
     hipStream_t st = (hipStream_t)stream;
     char* W = (char*)workspace;
     FxArgs f;
@@ -1247,7 +1320,12 @@ int lstm_sd_head_forward(const lstm_sd_head_dims* hd, const void* W_fc, const fl
     f.Gx = logits; f.B = P.B; f.G = P.V; f.T = P.T; f.dense = !P.compact; f.s = P.s;
     if (P.dtype == LSTM_SD_DTYPE_BF16) {
         launch_head_prep<bf16>(y, W + P.w_yb, nullptr, f.site, P.T, P.B, P.F, P.BP, P.FP, st);
-        launch_fx<bf16>(f, st);
+        RowsArgs x;
+        memset(&x, 0, sizeof(x));
+        x.R = P.T * P.B; x.B = P.B; x.K = P.F; x.G = P.V;
+        x.x = W + P.w_yb; x.lda = P.FP; x.np = 1; x.s = P.s;
+        x.W[0] = W_fc; x.bias[0] = b_fc; x.out[0] = logits;
+        launch_fx_bf16(x, st);
     } else {
         launch_head_prep<float>(y, W + P.w_yb, W + P.w_ybT, f.site, P.T, P.B, P.F, P.BP, P.FP, st);
         launch_fx<float>(f, st);

@@ -34,9 +34,8 @@ namespace lsd {
 // buffered so that chunk i+1 is in flight while chunk i is multiplied, and
 // both operands' fragments are read with ds_read_b64_tr_b16 (lanes 4e..4e+3
 // of a 16-lane group address row e of the group's four at columns 0, 4, 8,
-// 12: lane i receives column i of the four rows).  Dropped rows of the
-// dense mode and rows past the count read as zero (an offset past the
-// buffer).  Rows past B and columns past G are computed and not stored.
+// 12: lane i receives column i of the four rows).  Rows past the count read
+// as zero (an offset past the buffer).  Rows past B and columns past G are computed and not stored.
 constexpr int FB_M = 256, FB_N = 128, FB_KC = 64, FB_AP = FB_M + 16, FB_BP = FB_N + 16;
 constexpr size_t FB_LDS = (size_t)2 * FB_KC * (FB_AP + FB_BP) * 2 + (size_t)(LSTM_SD_MAX_K + 2 * FB_KC) * 4;
 
@@ -49,12 +48,11 @@ __global__ void __launch_bounds__(512) k_fx_big(FxArgs a) {
     const int t = blockIdx.y, n0 = blockIdx.x * FB_N, m0 = blockIdx.z * FB_M;
     const int K = a.K, G = a.G, B = a.B;
     const int32_t* krow = a.site.keep + (size_t)t * a.site.kmax;
-    const uint8_t* mrow = a.site.mask + (size_t)t * a.site.kmax;
     const int cnt = a.site.count[t];
     // the keep list, then -1 through two chunks past the last (rows read as
     // zero: the loop fetches two chunks ahead without a condition)
     const int cpad = ((cnt + FB_KC - 1) / FB_KC + 2) * FB_KC;
-    for (int j = tid; j < cpad; j += 512) kidx[j] = j >= cnt || (a.dense && !mrow[j]) ? -1 : krow[j];
+    for (int j = tid; j < cpad; j += 512) kidx[j] = j >= cnt ? -1 : krow[j];
     __syncthreads();
     const __amdgpu_buffer_rsrc_t xr = buf_rsrc((const bf16*)a.XT + (size_t)t * a.xt_tstride,
                                                (uint32_t)((size_t)K * a.xt_ld * 2));
@@ -194,7 +192,6 @@ __global__ void __launch_bounds__(512) k_dx_big(DxArgs a) {
     const bool failed = a.status && *a.status != 0;
     const int cnt = a.site.count[t];
     const int32_t* krow = a.site.keep + (size_t)t * a.site.kmax;
-    const uint8_t* mrow = a.site.mask + (size_t)t * a.site.kmax;
     float* out = a.out + (size_t)t * B * a.ldo;
     if (a.scatter) {                           // the dropped columns of this tile's drop-list range
         const int dn = a.site.dcount[t];
@@ -292,14 +289,13 @@ __global__ void __launch_bounds__(512) k_dx_big(DxArgs a) {
         const int jl = wc0 + 16 * j + cl, jj = j0 + jl;
         if (jj >= cnt) continue;
         const int kk = kcol[jl];                 // (a kept column: a valid row)
-        const float sc = (a.dense && !mrow[kk]) ? 0.0f : a.s;
         const int oc = a.scatter ? kk : jj;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = m0 + wr0 + 16 * i + acc_row(lane, r);
-                if (row < B) out[(size_t)row * a.ldo + oc] = failed ? __builtin_nanf("") : sc * acc[i][j][r];
+                if (row < B) out[(size_t)row * a.ldo + oc] = failed ? __builtin_nanf("") : a.s * acc[i][j][r];
             }
     }
 }
@@ -549,6 +545,309 @@ void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
     }
 }
 
+// ---------------------------------------------------------------------------
+// Input products and input gradients (bf16) as matrix products over all T*B (step,
+// row) pairs:
+//   ROWS_FX: out[r][n] = s * sum_k x[r][k] W[k][n] + bias[n]   (x masked, row-major)
+//   ROWS_DX: out[r][k] = s * m_t[k] * sum over directions and n of DA[r][n] W[k][n]
+// At 20 to 64 rows a step, a product per step over its kept neurons reads their rows
+// of W again for each step and pads its rows to the tile: that, not the
+// multiplications, was its time, so one product over all steps that multiplies the
+// dropped columns' zeros is 2 to 4 times as fast.
+// The MFMA's row side (TM = WM*MI*16) is the output's contiguous side, so a lane
+// holds four adjacent outputs of one row.  The rows' operand is staged fragment-major
+// (1 KB blocks, 16 rows x 32 of the contraction); so are the rows of W for ROWS_DX,
+// while W is staged contraction-major for ROWS_FX and read by transposing LDS reads.
+// Two LDS buffers of KC chunks of 32 each, loads two buffers ahead of the staging, one
+// LDS-only barrier per buffer: the small tiles, a few workgroups to a CU, take the time
+// of a load and a barrier per buffer whatever its depth, so they run at KC 4.
+// slices > 1 (ROWS_DX) splits the contraction over workgroups, each writing its
+// partial product; k_rows_reduce adds them in order.
+constexpr int ROWS_FX = 0, ROWS_DX = 1;
+template <int MODE, int WM, int WN, int MI, int NI, int KC>
+struct RowsShape {
+    static constexpr int NW = WM * WN, NTH = 64 * NW, TM = WM * MI * 16, TN = WN * NI * 16;
+    static constexpr int MP = TM + 16;                               // contraction-major row pitch
+    static constexpr int MEL = MODE == ROWS_FX ? 32 * MP : TM * 32, NEL = TN * 32;   // elements of a chunk
+    static constexpr size_t LDS = (size_t)2 * KC * (MEL + NEL) * 2;
+};
+
+template <int MODE, int WM, int WN, int MI, int NI, int KC>
+__global__ void __launch_bounds__(64 * WM * WN, 2) k_rows(RowsArgs a) {
+    using S = RowsShape<MODE, WM, WN, MI, NI, KC>;
+    constexpr int NTH = S::NTH, NW = S::NW, TM = S::TM, TN = S::TN, MP = S::MP;
+    constexpr int PM = TM * 4 / NTH, PN = TN / 16 / NW;              // row-side pieces per thread; row blocks per wave
+    static_assert(PM * NTH == TM * 4 && PN * NW * 16 == TN, "whole pieces");
+    extern __shared__ __align__(16) char smem[];
+    bf16* Ms = (bf16*)smem;                                          // [2][KC][MEL]
+    bf16* Ns = Ms + 2 * KC * S::MEL;                                 // [2][KC][NEL]
+    int pos = (int)(blockIdx.x % 8) * a.per + (int)(blockIdx.x / 8);
+    if (pos >= a.total) return;
+    // (problem or slice, column tile, row tile): an XCD's range shares its W columns
+    const int nrt = (a.R + TN - 1) / TN, nmt = (a.M + TM - 1) / TM;
+    const int z = pos / (nrt * nmt), mt = pos / nrt % nmt, rt = pos % nrt;
+    const int m0 = mt * TM, r0 = rt * TN;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = w / WN, wn = w % WN;
+    const int br = lane & 15, bk = lane >> 4;
+    const int G = a.G, B = a.B;
+    // the steps (KC chunks of the contraction) of this workgroup: ROWS_FX all of problem
+    // z; ROWS_DX slice z of the directions' steps one after the other
+    const int KK = MODE == ROWS_FX ? a.K : G;
+    const int nch = (KK + 31) / 32, nsd = (nch + KC - 1) / KC;
+    const int nall = MODE == ROWS_FX ? nsd : a.D * nsd;
+    const int c0 = MODE == ROWS_FX ? 0 : (int)((long)nall * z / a.slices);
+    const int c1 = MODE == ROWS_FX ? nall : (int)((long)nall * (z + 1) / a.slices);
+    const int nc = c1 - c0;
+    // rows' operand: block w + NW*i holds rows r0 + 16*(w + NW*i) .. +15
+    size_t nbase[PN];                                                // element offset of this lane's piece of chunk 0
+#pragma unroll
+    for (int i = 0; i < PN; ++i) {
+        const int r = min(r0 + 16 * (w + NW * i) + br, a.R - 1);
+        if constexpr (MODE == ROWS_FX) {
+            nbase[i] = (size_t)r * a.lda + 8 * bk;
+        } else {
+            const int t = r / B, b = r % B;
+            nbase[i] = (size_t)t * a.das + frag_lane_off(0, b >> 4, bk * 16 + (b & 15), nch);
+        }
+    }
+    // W: ROWS_FX rows of the chunk (tid / (TM/8) + passes), 8 columns each; ROWS_DX
+    // block (wave + NW*i): 16 rows of W, this lane's row and 8 of the contraction
+    constexpr int MPR = TM / 8;
+    uint32_t mofs[PM];
+#pragma unroll
+    for (int i = 0; i < PM; ++i) {
+        if constexpr (MODE == ROWS_FX) {
+            mofs[i] = (uint32_t)((tid / MPR + i * (NTH / MPR)) * G + m0 + 8 * (tid % MPR)) * 2u;
+        } else {
+            const int k = min(m0 + 16 * (w + NW * i) + br, a.M - 1);
+            mofs[i] = ((uint32_t)k * (uint32_t)G + 8u * bk) * 2u;
+        }
+    }
+    const uint32_t wbytes = (uint32_t)(MODE == ROWS_FX ? a.K : a.M) * (uint32_t)G * 2u;
+    const void* W0 = MODE == ROWS_FX ? a.W[z] : a.W[0];
+    u32x4_t rm[2][KC][PM], rn[2][KC][PN];
+    int ci = c0;                                                     // next step to load
+    auto issue = [&](int sl) {
+        const int cc = min(ci, c1 - 1);
+        const int d = MODE == ROWS_DX && cc >= nsd ? 1 : 0;
+        const __amdgpu_buffer_rsrc_t wr = buf_rsrc(MODE == ROWS_FX ? W0 : a.W[d], wbytes);
+        const bf16* X = (const bf16*)(MODE == ROWS_FX ? a.x : a.da[d]);
+#pragma unroll
+        for (int q = 0; q < KC; ++q) {
+            const int c = min((cc - d * nsd) * KC + q, nch - 1);     // (chunks past the end: cleared when staged)
+            const uint32_t wadd = MODE == ROWS_FX ? (uint32_t)c * 64u * (uint32_t)G : 64u * (uint32_t)c;
+#pragma unroll
+            for (int i = 0; i < PM; ++i) rm[sl][q][i] = __builtin_amdgcn_raw_buffer_load_b128(wr, mofs[i] + wadd, 0, 0);
+#pragma unroll
+            for (int i = 0; i < PN; ++i) {
+                if constexpr (MODE == ROWS_FX) {
+                    // (pieces past the row's end: its last one, cleared when staged)
+                    const size_t o = 32 * c + 8 * bk < a.lda ? (size_t)32 * c : (size_t)(a.lda - 8 - 8 * bk);
+                    rn[sl][q][i] = *(const u32x4_t*)(X + nbase[i] + o);
+                } else {
+                    rn[sl][q][i] = *(const u32x4_t*)(X + nbase[i] + (size_t)c * 512);
+                }
+            }
+        }
+        ++ci;
+    };
+    int cs = c0;                                                     // next step to stage
+    auto stage = [&](int buf, int sl) {
+        const int cc = MODE == ROWS_DX && cs >= nsd ? cs - nsd : cs;
+#pragma unroll
+        for (int q = 0; q < KC; ++q) {
+            bf16* Mb = Ms + (buf * KC + q) * S::MEL;
+            bf16* Nb = Ns + (buf * KC + q) * S::NEL;
+            const int k0 = 32 * (cc * KC + q);
+            if (k0 + 32 > KK) {                // the contraction's ragged end: zeros past it
+                uint32_t m[4];
+                pad_mask<bf16>(k0 + 8 * bk, KK, m);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                    for (int i = 0; i < PN; ++i) rn[sl][q][i][e] &= m[e];
+                    if constexpr (MODE == ROWS_DX)
+#pragma unroll
+                        for (int i = 0; i < PM; ++i) rm[sl][q][i][e] &= m[e];
+                }
+                if constexpr (MODE == ROWS_FX)
+#pragma unroll
+                    for (int i = 0; i < PM; ++i)
+                        if (k0 + tid / MPR + i * (NTH / MPR) >= KK) rm[sl][q][i] = u32x4_t{0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int i = 0; i < PM; ++i) {
+                if constexpr (MODE == ROWS_FX)
+                    *(u32x4_t*)(Mb + (tid / MPR + i * (NTH / MPR)) * MP + 8 * (tid % MPR)) = rm[sl][q][i];
+                else
+                    *(u32x4_t*)(Mb + (w + NW * i) * 512 + lane * 8) = rm[sl][q][i];
+            }
+#pragma unroll
+            for (int i = 0; i < PN; ++i) *(u32x4_t*)(Nb + (w + NW * i) * 512 + lane * 8) = rn[sl][q][i];
+        }
+        ++cs;
+    };
+    f32x4_t acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) acc[i][j] = f32x4_t{0, 0, 0, 0};
+    const int trow = 8 * (lane >> 4) + ((lane & 15) >> 2), tcol = 4 * (lane & 3);
+    auto multiply = [&](int buf) {
+#pragma unroll
+        for (int q = 0; q < KC; ++q) {
+            const bf16* Mb = Ms + (buf * KC + q) * S::MEL;
+            const bf16* Nb = Ns + (buf * KC + q) * S::NEL + (wn * NI) * 512 + lane * 8;
+            Raw8<bf16> fn[NI];
+#pragma unroll
+            for (int j = 0; j < NI; ++j) raw_lds(fn[j], Nb + j * 512);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                Raw8<bf16> fm;
+                if constexpr (MODE == ROWS_FX) {
+                    const bf16* p = Mb + trow * MP + (wm * MI + i) * 16 + tcol;
+                    const uint2 lo = lds_tr4(p), hi = lds_tr4(p + 4 * MP);
+                    fm.w[0] = lo.x; fm.w[1] = lo.y; fm.w[2] = hi.x; fm.w[3] = hi.y;
+                } else {
+                    raw_lds(fm, Mb + (wm * MI + i) * 512 + lane * 8);
+                }
+#pragma unroll
+                for (int j = 0; j < NI; ++j) raw_mma(fm, fn[j], acc[i][j]);
+            }
+        }
+    };
+    auto barrier = [&]() {                     // LDS only: the loads stay in flight
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    issue(0);
+    issue(1);
+    stage(0, 0);
+    issue(0);
+    barrier();
+    int c = 0;
+    for (; c + 1 < nc; c += 2) {
+        stage(1, 1);
+        issue(1);
+        multiply(0);
+        barrier();
+        stage(0, 0);
+        issue(0);
+        multiply(1);
+        barrier();
+    }
+    if (c < nc) multiply(0);
+    // output r of this lane: column 4*(lane/16)+r of the tile, row lane%16
+    const bool failed = MODE == ROWS_DX && a.status && *a.status != 0;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int r = r0 + (wn * NI + j) * 16 + br;
+        if (r >= a.R) continue;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int n = m0 + (wm * MI + i) * 16 + 4 * bk;
+            if (n >= a.M) continue;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = a.s * acc[i][j][e];
+            if constexpr (MODE == ROWS_FX) {
+                const float4 bn = *(const float4*)(a.bias[z] + n);   // (M = G is a multiple of 4)
+                *(float4*)(a.out[z] + (size_t)r * a.M + n) = make_float4(v[0] + bn.x, v[1] + bn.y, v[2] + bn.z, v[3] + bn.w);
+            } else if (a.slices > 1) {
+                float* o = a.part + ((size_t)z * a.R + r) * a.M + n;
+                if ((a.M & 3) == 0) {
+                    *(float4*)o = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < a.M) o[e] = v[e];
+                }
+            } else {
+                const uint8_t* mk = a.mask + (size_t)(r / B) * a.kmax + n;
+                float* o = a.out[0] + (size_t)r * a.M + n;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    v[e] = failed ? __builtin_nanf("") : mk[min(e, a.M - 1 - n)] ? v[e] : 0.0f;
+                if ((a.M & 3) == 0) {
+                    *(float4*)o = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < a.M) o[e] = v[e];
+                }
+            }
+        }
+    }
+}
+
+// out[r][k] = m_t[k] * sum of the slices in order.  grid (ceil(M/256), ceil(R/4)).
+__global__ void __launch_bounds__(256) k_rows_reduce(RowsArgs a) {
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= a.M) return;
+    const bool failed = a.status && *a.status != 0;
+    const size_t n = (size_t)a.R * a.M;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = blockIdx.y * 4 + i;
+        if (r >= a.R) return;
+        const float* p = a.part + (size_t)r * a.M + k;
+        float v = 0.0f;
+        for (int z = 0; z < a.slices; ++z) v += p[(size_t)z * n];
+        a.out[0][(size_t)r * a.M + k] = failed ? __builtin_nanf("") : a.mask[(size_t)(r / a.B) * a.kmax + k] ? v : 0.0f;
+    }
+}
+
+template <int MODE, int WM, int WN, int MI, int NI, int KC>
+static void rows_go(RowsArgs& a, int z, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+    using S = RowsShape<MODE, WM, WN, MI, NI, KC>;
+    a.total = ((a.R + S::TN - 1) / S::TN) * ((a.M + S::TM - 1) / S::TM) * z;
+    a.per = (a.total + 7) / 8;
+    const dim3 grid(8 * a.per), blk(S::NTH);
+    if (e0 && e1) hipExtLaunchKernelGGL((k_rows<MODE, WM, WN, MI, NI, KC>), grid, blk, (uint32_t)S::LDS, st, e0, e1, 0, a);
+    else k_rows<MODE, WM, WN, MI, NI, KC><<<grid, blk, S::LDS, st>>>(a);
+}
+static long rows_tiles(const RowsArgs& a, int TM, int TN) {
+    return (long)((a.R + TN - 1) / TN) * ((a.M + TM - 1) / TM);
+}
+// Tiles of the input products (us a pass, both layers or directions where there are
+// two).  256x256 from four a CU: 349 against 462 at 128x128 (16384 rows x 1024 x 4096,
+// two layers), 141 against 163 (3200 x 500 x 20000).  128x128 from one a CU: 35 against
+// 40 at 64x64 (700 x 1500 x 6000, two), 20 against 25 (1400 x 1150 x 4600, two).  64x64
+// below: 13.6 against 16.6 (700 x 650 x 2600, two).
+void launch_fx_rows(RowsArgs& a, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+    a.M = a.G;
+    if (rows_tiles(a, 256, 256) * a.np >= 1024) rows_go<ROWS_FX, 2, 4, 8, 4, 1>(a, a.np, st, e0, e1);
+    else if (rows_tiles(a, 128, 128) * a.np >= 256) rows_go<ROWS_FX, 2, 2, 4, 4, 1>(a, a.np, st, e0, e1);
+    else rows_go<ROWS_FX, 2, 2, 2, 2, 2>(a, a.np, st, e0, e1);
+}
+// Tiles of the input gradients.  256x256 from one a CU: 289 against 385 at 128x128
+// (16384 rows x 1024 outputs x 4096, two layers).  64x64 for contractions up to 5000:
+// 27 against 38 at 128x128 sliced (3200 x 500 x 2000), 34 against 51 (1400 x 1150 x
+// 4600).  128x128 with the contraction sliced to two workgroups a CU for the rest: 97
+// against 111 at 64x64 (700 x 1500 x 6000, two), 131 against 196 (3200 x 500 x 20000).
+void launch_dx_rows(RowsArgs& a, size_t part_bytes, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+    const long n256 = rows_tiles(a, 256, 256), n128 = rows_tiles(a, 128, 128);
+    a.slices = 1;
+    if (n256 >= 208) return rows_go<ROWS_DX, 2, 4, 8, 4, 1>(a, 1, st, e0, e1);
+    if (n128 < 512 && (long)a.D * a.G <= 5000) return rows_go<ROWS_DX, 2, 2, 2, 2, 2>(a, 1, st, e0, e1);
+    const long most = (long)std::min<size_t>(part_bytes / ((size_t)a.R * a.M * 4), 16);
+    const long want = std::min(std::min((512 + n128 - 1) / n128, most), (long)a.D * ((a.G + 63) / 64) / 4);
+    if (n128 >= 256 || want < 2) return rows_go<ROWS_DX, 2, 4, 4, 2, 2>(a, 1, st, e0, e1);
+    a.slices = (int)want;
+    if (e0) (void)hipEventRecord(e0, st);
+    rows_go<ROWS_DX, 2, 4, 4, 2, 2>(a, a.slices, st, nullptr, nullptr);
+    k_rows_reduce<<<dim3((a.M + 255) / 256, (a.R + 3) / 4), 256, 0, st>>>(a);
+    if (e1) (void)hipEventRecord(e1, st);
+}
+
+template <int MODE, int WM, int WN, int MI, int NI, int KC>
+static bool rows_lds() {
+    return hipFuncSetAttribute((const void*)k_rows<MODE, WM, WN, MI, NI, KC>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)RowsShape<MODE, WM, WN, MI, NI, KC>::LDS) == hipSuccess;
+}
 int setup_big_attributes() {
     bool ok = hipFuncSetAttribute((const void*)k_wgrad_rows<2, 4, 8, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)WrShape<2, 4, 8, 4>::LDS) == hipSuccess;
@@ -556,6 +855,8 @@ int setup_big_attributes() {
              hipSuccess && ok;
     ok = hipFuncSetAttribute((const void*)k_dx_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)DB_LDS) ==
              hipSuccess && ok;
+    ok = rows_lds<ROWS_FX, 2, 4, 8, 4, 1>() && rows_lds<ROWS_DX, 2, 4, 8, 4, 1>() &&
+         rows_lds<ROWS_DX, 2, 4, 4, 2, 2>() && ok;
     return ok ? 0 : -1;
 }
 

@@ -78,8 +78,7 @@ struct FxArgs {
     float* Gx;                          // [T][B][G]
     int B, G, T, dense;
     float s;
-    // the input transposed, XT + t*xt_tstride + k*xt_ld + b, bf16: when set
-    // (batch >= 64), the large-batch kernel runs (after the transposes)
+    // bf16: the input transposed, XT + t*xt_tstride + k*xt_ld + b
     const void* XT; long xt_tstride; int xt_ld;
     // with tr_gz > 0, the launch also runs the transposes (and the pass
     // initialisation) of tr, as a virtual (tr_gx, tr_gy, tr_gz) grid of
@@ -165,7 +164,6 @@ struct DxArgs {
     int D, B, G, ldo, T, K, tps, dense, mtiles;
     float s;
     const int* status;                  // sticky barrier status of the step, or null: when set, NaN is written
-    int big;                            // bf16, batch >= 64: the large-batch kernel
 };
 
 // Weight gradient of one (layer, direction, site), summed over every step:
@@ -211,6 +209,25 @@ struct WrBatch {
     long das;                           // elements of one DA block
     const int* status;                  // sticky barrier status of the step, or null
     int total, per;                     // (set at launch) tiles of all problems; per XCD
+};
+
+// Input products and input gradients (bf16) over all rows r = (t, b) of a pass.
+struct RowsArgs {
+    int R, B, K, G, M;                  // rows T*B; K neurons; G gate columns; M outputs per row (set by the fx launcher)
+    // input product: problem z (direction) out[z] = s * x W[z] + bias[z]
+    const void* x; int lda;             // [R][lda] masked, lda a multiple of 8
+    int np;                             // problems
+    // input gradient: out[0] = s * mask * sum over D directions of da[d] W[d]^T
+    const void* da[2]; long das;        // [T] x fragment-major [B][G]
+    int D, kmax, slices;                // (slices set at launch)
+    const uint8_t* mask;                // [T][kmax] rows of the output's neurons
+    const int* status;                  // sticky barrier status of the step, or null
+    float* part;                        // partial products of the slices
+    const void* W[2];                   // [K][G]
+    const float* bias[2];
+    float* out[2];
+    float s;
+    int total, per;                     // (set at launch)
 };
 
 // Persistent forward recurrence of one layer (both directions): one

@@ -215,7 +215,7 @@ __device__ __forceinline__ void transpose_block(const TransArgs& a, int N, int b
 }
 
 // ---------------------------------------------------------------------------
-// Forward input product, all t (Eq. 1-4 first term; Sec. 3.2, FP input
+// Forward input product (fp32), all t (Eq. 1-4 first term; Sec. 3.2, FP input
 // sparsity: the dropped columns of x and rows of W are skipped).
 // grid (ceil(G/128) on the XCD mapping, T, ceil(B/32)), block 256.  A
 // workgroup computes a 32-row x 128-column tile of Gx_t; wave w owns columns
@@ -229,8 +229,9 @@ __device__ __forceinline__ void transpose_block(const TransArgs& a, int N, int b
 constexpr int FX_NB = 128, FX_MB = 32, FX_KC = 32, FX_LD = FX_KC + 8;
 constexpr int FX_WLD = FX_NB + 8;
 
-template <typename T, bool DENSE>
+template <bool DENSE>
 __global__ void __launch_bounds__(256) k_fx(FxArgs a) {
+    using T = float;
     constexpr uint32_t ES = sizeof(T);
     __shared__ __attribute__((aligned(16))) T ws[2][FX_KC][FX_WLD];   // W chunk [k][n]
     __shared__ __attribute__((aligned(16))) T xs[2][FX_MB][FX_LD];    // X chunk [row][k]
@@ -261,7 +262,7 @@ __global__ void __launch_bounds__(256) k_fx(FxArgs a) {
 
     // staging roles: W row r = tid/8, 16 columns at 16*(tid%8); X row tid/8, 4 kept columns at 4*(tid%8)
     const int sr = tid >> 3, sq = tid & 7;
-    constexpr int WNW = 16 * (int)ES / 16;             // 16-byte loads per W segment (2 bf16, 4 f32)
+    constexpr int WNW = 16 * (int)ES / 16;             // 16-byte loads per W segment
     u32x4_t wreg[WNW];
     T xreg[4];
     auto fetch = [&](int kc) {
@@ -300,40 +301,19 @@ __global__ void __launch_bounds__(256) k_fx(FxArgs a) {
     for (int ch = 0; ch < nchunk; ++ch) {
         const int buf = ch & 1;
         if (ch + 1 < nchunk) fetch((ch + 1) * FX_KC);
-        if constexpr (sizeof(T) == 2) {
-            // A: 8 consecutive kept columns of the lane's row, one 16-byte
-            // read; B: column n of the K-major W chunk over 8 rows, two
-            // transposing reads (lanes 4e..4e+3 of a 16-lane group address
-            // columns 0, 4, 8, 12 of row e; lane i receives column i)
-            Raw8<T> fa[2], fb[2];
+        Frag<T> fa[2], fb[2];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) raw_lds(fa[i], &xs[buf][16 * i + cl][g8]);
-            const int e4 = (lane & 15) >> 2, j4 = lane & 3;
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) {
-                const int nb = 32 * w + 16 * c + 4 * j4;
-                const uint2 lo = lds_tr4(&ws[buf][g8 + e4][nb]), hi = lds_tr4(&ws[buf][g8 + 4 + e4][nb]);
-                fb[c].w[0] = lo.x; fb[c].w[1] = lo.y; fb[c].w[2] = hi.x; fb[c].w[3] = hi.y;
-            }
+            for (int e = 0; e < 8; ++e) fa[i].v[e] = xs[buf][16 * i + cl][g8 + e];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+        for (int c = 0; c < 2; ++c)
 #pragma unroll
-                for (int c = 0; c < 2; ++c) raw_mma(fa[i], fb[c], acc[i][c]);
-        } else {
-            Frag<T> fa[2], fb[2];
+            for (int e = 0; e < 8; ++e) fb[c].v[e] = ws[buf][g8 + e][32 * w + 16 * c + cl];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) fa[i].v[e] = xs[buf][16 * i + cl][g8 + e];
-#pragma unroll
-            for (int c = 0; c < 2; ++c)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) fb[c].v[e] = ws[buf][g8 + e][32 * w + 16 * c + cl];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int c = 0; c < 2; ++c) mma_16x16x32(fa[i], fb[c], acc[i][c]);
-        }
+            for (int c = 0; c < 2; ++c) mma_16x16x32(fa[i], fb[c], acc[i][c]);
         if (ch + 1 < nchunk) commit(buf ^ 1);
         __syncthreads();
     }
@@ -570,7 +550,7 @@ __global__ void __launch_bounds__(1024) k_bwd(BwdArgs a) {
             if (valid) {
                 if (D.dy) dh += D.dy[(size_t)b * a.ldy + u];
                 if (D.dxc) {
-                    const int p = D.dxpos[u];
+                    const int p = D.dxpos ? D.dxpos[u] : u;
                     if (p >= 0) dh += D.dxc[(size_t)b * a.lddx + p];
                 }
             }
@@ -604,7 +584,7 @@ __global__ void __launch_bounds__(1024) k_bwd(BwdArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Output-sparse input gradient, all t (Eq. 10), summed over directions.
+// Output-sparse input gradient (fp32), all t (Eq. 10), summed over directions.
 // grid (32 * tps * ceil(T/4), 1, ceil(B/64)), block 256: 16 kept columns per
 // workgroup, the contraction over 4H split over the 4 waves.  Workgroup i
 // runs on XCD c = i % 8, which takes the steps t = c/2 (mod 4) and the W
@@ -613,9 +593,10 @@ __global__ void __launch_bounds__(1024) k_bwd(BwdArgs a) {
 // the output is the full-width gradient: kept columns go to their own
 // positions, and the workgroup of (slice, tile) also writes the zeros of
 // the same tile of the slice's dropped columns.
-template <typename T, int MT>
+template <int MT>
 __global__ void __launch_bounds__(256) k_dx(DxArgs a) {
-    constexpr int U = sizeof(T) == 2 ? 4 : 2;           // 32-column chunks per wave loaded together
+    using T = float;
+    constexpr int U = 2;                                // 32-column chunks per wave loaded together
     constexpr uint32_t ES = sizeof(T);
     __shared__ float red[4][64][17];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -1760,10 +1741,21 @@ __global__ void __launch_bounds__(256) k_trans(FxArgs a) {
     transpose_block<T>(a.tr, a.trN, blockIdx.x, blockIdx.y, blockIdx.z, a.tr_gx, a.tr_gy, tile);
 }
 
+void launch_fx_rows(RowsArgs& a, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+void launch_dx_rows(RowsArgs& a, size_t part_bytes, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
+void launch_prep_bf16(const FxArgs& a, hipStream_t st) {
+    launch_k(KID_TRANS, k_trans<bf16>, dim3(a.tr_gx, a.tr_gy, a.tr_gz), dim3(256), 0, st, a);
+}
+// the bf16 input product of a layer: over all rows, or per step over the kept neurons
+void launch_fx_bf16(RowsArgs& a, hipStream_t st) {
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (g_timer_kid == KID_FX) { e0 = timer_event(); e1 = timer_event(); }
+    launch_fx_rows(a, st, e0, e1);
+}
 template <typename T>
 void launch_fx(const FxArgs& a, hipStream_t st) {
-    if (sizeof(T) == 2 && a.XT) {              // large batch: the transposed input feeds the product
-        if (a.tr_gz > 0) launch_k(KID_TRANS, k_trans<T>, dim3(a.tr_gx, a.tr_gy, a.tr_gz), dim3(256), 0, st, a);
+    if constexpr (sizeof(T) == 2) {
+        if (a.tr_gz > 0) launch_prep_bf16(a, st);
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (g_timer_kid == KID_FX) { e0 = timer_event(); e1 = timer_event(); }
         launch_fx_big(a, st, e0, e1);
@@ -1774,8 +1766,8 @@ void launch_fx(const FxArgs& a, hipStream_t st) {
         const long ntr = (long)a.tr_gx * a.tr_gy * a.tr_gz, per_y = (long)grid.x * grid.z;
         grid.y += (unsigned)((ntr + per_y - 1) / per_y);
     }
-    if (a.dense) launch_k(KID_FX, k_fx<T, true>, grid, dim3(256), 0, st, a);
-    else launch_k(KID_FX, k_fx<T, false>, grid, dim3(256), 0, st, a);
+    if (a.dense) launch_k(KID_FX, k_fx<true>, grid, dim3(256), 0, st, a);
+    else launch_k(KID_FX, k_fx<false>, grid, dim3(256), 0, st, a);
 }
 template <typename T>
 void launch_step(const StepArgs& a, int D, hipStream_t st) {
@@ -1789,18 +1781,24 @@ void launch_bwd(const BwdArgs& a, int D, hipStream_t st) {
     const int nx = (a.has_next ? 2 : 1) * NXCD * a.tps;
     launch_k(KID_BWD, k_bwd<T>, dim3(nx, (a.B + 63) / 64, D), dim3(1024), 0, st, a);
 }
+// the bf16 input gradient of a layer: over all rows, or per step over the kept neurons
+void launch_dx_bf16(RowsArgs& a, size_t part_bytes, hipStream_t st) {
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    if (g_timer_kid == KID_DX) { e0 = timer_event(); e1 = timer_event(); }
+    launch_dx_rows(a, part_bytes, st, e0, e1);
+}
 template <typename T>
 void launch_dx(const DxArgs& a, int K, hipStream_t st) {
-    if (sizeof(T) == 2 && a.big) {
+    if constexpr (sizeof(T) == 2) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         if (g_timer_kid == KID_DX) { e0 = timer_event(); e1 = timer_event(); }
         launch_dx_big(a, st, e0, e1);
         return;
     }
     const dim3 grid(NXCD * a.tps * 4 * ((a.T + 3) / 4), 1, (a.B + 63) / 64);
-    if (a.B <= 16) launch_k(KID_DX, k_dx<T, 1>, grid, dim3(256), 0, st, a);
-    else if (a.B <= 32) launch_k(KID_DX, k_dx<T, 2>, grid, dim3(256), 0, st, a);
-    else launch_k(KID_DX, k_dx<T, 4>, grid, dim3(256), 0, st, a);
+    if (a.B <= 16) launch_k(KID_DX, k_dx<1>, grid, dim3(256), 0, st, a);
+    else if (a.B <= 32) launch_k(KID_DX, k_dx<2>, grid, dim3(256), 0, st, a);
+    else launch_k(KID_DX, k_dx<4>, grid, dim3(256), 0, st, a);
 }
 void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
 int setup_big_attributes();

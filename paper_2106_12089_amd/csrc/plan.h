@@ -30,15 +30,16 @@ struct Plan {
 
     // reserve
     size_t r_gates, r_c, r_hrecT, r_dir_bytes;  // inside one (l, d) block (r_hrecT: f32 h transposed; bf16 masked h_{t-1})
-    size_t r_xT, r_h0T;                         // layer-0 input (bf16: from 64 rows) and h0 (f32), transposed
+    size_t r_xT, r_h0T;                         // layer-0 input (bf16: per-step products) and h0 (f32), transposed
     size_t r_xm;                                // bf16: the masked layer-0 input
-    size_t r_ybuf_base, r_ybuf_bytes;           // per layer l < L-1: ybuf (bf16: masked) then ybufT (bf16: from 64 rows)
+    size_t r_ybuf_base, r_ybuf_bytes;           // per layer l < L-1: ybuf (bf16: masked) then ybufT (bf16: per-step products)
     size_t r_ybufT_off;                         // offset of ybufT inside a layer block
     size_t r_total;
 
     // workspace
     size_t w_gx, w_hrec, w_hx, w_xx, w_gxs;     // forward (w_gxs: input products of the stacked layers above the first)
     size_t w_da, w_daT, w_dxw, w_dc, w_dhc, w_dxc;  // backward
+    size_t w_part, part_bytes;                  // backward, bf16: partial input gradients
     size_t w_sync;                              // barrier counters and error flag
     size_t w_loss, w_total;
 
