@@ -36,6 +36,8 @@ void launch_case1_drop(int, int, const void*, void*, uint8_t*, int, int, int, ui
                        float, hipStream_t);
 void launch_case1_undrop(const float*, const uint8_t*, float*, long, float, hipStream_t);
 template <typename T> void launch_head_prep(const float*, void*, void*, const SiteView&, int, int, int, int, int, hipStream_t);
+bool launch_ce_bf16(const float*, const int32_t*, const int32_t*, int, int, int, int, float*, float*, float*, float*,
+                    void*, hipStream_t);
 void launch_ce_loss(const float*, const int32_t*, const int32_t*, int, int, int, float*, float*, float*, float*, float*,
                     hipStream_t);
 template <typename T>
@@ -1079,9 +1081,12 @@ static void head_backward_impl(const HeadPlan& P, const void* W_fc, const int32_
                                char* W, hipStream_t st) {
     float* lse = (float*)(W + P.w_lse);
     float* ninv = (float*)(W + P.w_ninv);
-    launch_ce_loss(logits, tgt, lengths, P.T, P.B, P.V, lse, (float*)(W + P.w_rowloss), (float*)(W + P.w_rowok), loss,
-                   ninv, st);
-    launch_ce_grad<E>(logits, tgt, lengths, lse, ninv, P.T, P.B, P.V, P.BP, P.mtiles, W + P.w_da, W + P.w_daT, st);
+    float *rowloss = (float*)(W + P.w_rowloss), *rowok = (float*)(W + P.w_rowok);
+    if (!std::is_same<E, bf16>::value || !launch_ce_bf16(logits, tgt, lengths, P.T, P.B, P.V, P.mtiles, rowloss, rowok,
+                                                         loss, ninv, W + P.w_da, st)) {
+        launch_ce_loss(logits, tgt, lengths, P.T, P.B, P.V, lse, rowloss, rowok, loss, ninv, st);
+        launch_ce_grad<E>(logits, tgt, lengths, lse, ninv, P.T, P.B, P.V, P.BP, P.mtiles, W + P.w_da, W + P.w_daT, st);
+    }
     const SiteView site = head_site(P, mbuf);
     if constexpr (std::is_same<E, bf16>::value) {
         RowsArgs f;

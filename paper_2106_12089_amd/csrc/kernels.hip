@@ -17,6 +17,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <type_traits>
 #include <vector>
 
 #include "device.h"
@@ -1575,6 +1576,112 @@ __global__ void __launch_bounds__(256) k_ce_grad(const float* z, const int32_t* 
     }
 }
 
+// The number of rows that count, as ninv = 1/N (0 when N = 0).  One workgroup.
+__global__ void __launch_bounds__(1024) k_ce_count(const int32_t* tgt, const int32_t* lengths, int T_, int B, int V,
+                                                   float* ninv) {
+    __shared__ int red[16];
+    int n = 0;
+    const int nr = T_ * B;
+    for (int i = threadIdx.x; i < nr; i += 1024) n += ce_row_valid(tgt, lengths, i / B, i % B, B, V) ? 1 : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 16; ++w) n += red[w];
+        ninv[0] = n > 0 ? 1.0f / (float)n : 0.0f;
+    }
+}
+
+// bf16: the losses and dz of RW rows in one pass over their logits, which are
+// held in registers (PP pieces of 8 columns per thread).  Bound by memory: the
+// logits once in, dz once out (half as many bytes); k_ce_rows + k_ce_grad read
+// them twice from memory and once more from cache, also in rows that do not
+// count.  dz is fragment-major, where a row's pieces are 16 bytes in every 256:
+// the workgroups of a row tile are neighbours on one XCD (workgroup i runs on
+// XCD i % 8), so that its L2 merges them.  It does so in part (199 MB written for
+// 125 of dz), but 2 or 4 rows per workgroup, which write 32 or 64 bytes at a
+// place, were no faster above 2048 columns: loads, exponentials and stores of
+// the few rows that fit a CU do not overlap enough.
+// Measured at 3200 rows of 20000 columns, 70% of which count: 149 us for the
+// three launches before, 100 with these (89 of it this kernel); 700 rows of
+// 10000: 29 and 26 us.
+// Workgroup -> (tile of 16 rows of a step, RW rows of it); thread -> (piece,
+// row), rows innermost.  Rows that do not count, and rows past B, get zeros.
+template <int RW, int NTH, int PP>
+__global__ void __launch_bounds__(NTH) k_ce_dz(const float* z, const int32_t* tgt, const int32_t* lengths,
+                                               const float* ninv, int T_, int B, int V, int mtiles, float* rowloss,
+                                               float* rowok, bf16* da) {
+    constexpr int NW = NTH / 64, NG = 16 / RW, NQ = NTH / RW;
+    __shared__ float rm[NW][RW], rs[NW][RW];
+    const int tid = threadIdx.x, j = blockIdx.x >> 3;
+    const int tl = (j / NG) * 8 + (blockIdx.x & 7);
+    if (tl >= T_ * mtiles) return;
+    const int lr = tid % RW, q0 = tid / RW, rr = (j % NG) * RW + lr;
+    const int t = tl / mtiles, b = 16 * (tl % mtiles) + rr;
+    const int nchunk = (V + 31) / 32, np = 4 * nchunk;
+    bf16* dst = da + (size_t)tl * nchunk * 512 + 8 * rr;           // piece p of the row: + 128*p
+    const bool ok = b < B && ce_row_valid(tgt, lengths, t, b, B, V);
+    const size_t row = (size_t)t * B + b;
+    const int vend = ok ? V : 0;
+    const float* zr = z + (ok ? row * V : 0);
+    const int g = ok ? tgt[row] : -1;
+    const float sc = ninv[0];
+    float4 v[PP][2];                                       // V is a multiple of 4
+#pragma unroll
+    for (int i = 0; i < PP; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = 8 * (q0 + NQ * i) + 4 * h;
+            v[i][h] = c < vend ? *(const float4*)(zr + c) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        }
+    float m = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < PP; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            m = fmaxf(m, fmaxf(fmaxf(v[i][h].x, v[i][h].y), fmaxf(v[i][h].z, v[i][h].w)));
+#pragma unroll
+    for (int o = 32; o >= RW; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+    if ((tid & 63) < RW) rm[tid >> 6][lr] = m;
+    __syncthreads();
+    float M = rm[0][lr];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) M = fmaxf(M, rm[w][lr]);
+    float sum = 0.0f;
+#pragma unroll
+    for (int i = 0; i < PP; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            float4& q = v[i][h];
+            q = make_float4(expf(q.x - M), expf(q.y - M), expf(q.z - M), expf(q.w - M));
+            if (8 * (q0 + NQ * i) + 4 * h < vend) sum += ((q.x + q.y) + q.z) + q.w;
+        }
+#pragma unroll
+    for (int o = 32; o >= RW; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((tid & 63) < RW) rs[tid >> 6][lr] = sum;
+    __syncthreads();
+    float S = rs[0][lr];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) S += rs[w][lr];
+    const float is = 1.0f / S;
+#pragma unroll
+    for (int i = 0; i < PP; ++i) {
+        const int p = q0 + NQ * i, c = 8 * p;
+        if (p < np) {
+            const float e[8] = {v[i][0].x, v[i][0].y, v[i][0].z, v[i][0].w, v[i][1].x, v[i][1].y, v[i][1].z, v[i][1].w};
+            float o[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) o[k] = c + k < vend ? (e[k] * is - (c + k == g ? 1.0f : 0.0f)) * sc : 0.0f;
+            st8(dst + (size_t)128 * p, o);
+        }
+    }
+    if (q0 == 0 && b < B) {
+        rowloss[row] = ok ? (M + logf(S)) - zr[g] : 0.0f;
+        rowok[row] = ok ? 1.0f : 0.0f;
+    }
+}
+
 // MSE loss gradient (a loss of the synthetic workloads).
 __device__ __forceinline__ float nvalid_rows(const int32_t* lengths, int B, int T) {
     if (!lengths) return (float)B * T;
@@ -1861,6 +1968,36 @@ void launch_ce_loss(const float* z, const int32_t* tgt, const int32_t* lengths, 
              rowok);
     launch_k(KID_CE, k_ce_final, dim3(1), dim3(256), 0, st, (const float*)rowloss, (const float*)rowok, (long)T_ * B,
              loss, ninv);
+}
+// Loss and bf16 dz in one pass where a row's logits fit a workgroup's
+// registers; false (nothing launched) where they do not: the caller then takes
+// launch_ce_loss and launch_ce_grad.
+// The line is the registers of 1024 threads at two workgroups to a CU (32
+// logits a thread).  At 20 x 35 rows of 32768 columns the whole head takes 260 us
+// with k_ce_rows + k_ce_grad and 250 with this.  Below 2048 columns a
+// row is too little work for a workgroup (12000 rows of 252: 279 us for the head
+// with one row, 272 with two, 268 with four; 15360 of 1000: 386, 381, 379).
+bool launch_ce_bf16(const float* z, const int32_t* tgt, const int32_t* lengths, int T_, int B, int V, int mtiles,
+                    float* rowloss, float* rowok, float* loss, float* ninv, void* da, hipStream_t st) {
+    if (V > 32768) return false;
+    launch_k(KID_CE, k_ce_count, dim3(1), dim3(1024), 0, st, tgt, lengths, T_, B, V, ninv);
+    auto go = [&](auto rw, auto nth, auto pp) {
+        constexpr int RW = decltype(rw)::value, NTH = decltype(nth)::value, PP = decltype(pp)::value;
+        launch_k(KID_CE, k_ce_dz<RW, NTH, PP>, dim3((unsigned)(((long)T_ * mtiles + 7) / 8 * (128 / RW))), dim3(NTH), 0,
+                 st, z, tgt, lengths, (const float*)ninv, T_, B, V, mtiles, rowloss, rowok, (bf16*)da);
+    };
+    if (V <= 512) go(std::integral_constant<int, 4>(), std::integral_constant<int, 256>(), std::integral_constant<int, 1>());
+    else if (V <= 1024) go(std::integral_constant<int, 2>(), std::integral_constant<int, 256>(), std::integral_constant<int, 1>());
+    else if (V <= 2048) go(std::integral_constant<int, 2>(), std::integral_constant<int, 256>(), std::integral_constant<int, 2>());
+    else if (V <= 4096) go(std::integral_constant<int, 1>(), std::integral_constant<int, 256>(), std::integral_constant<int, 2>());
+    else if (V <= 8192) go(std::integral_constant<int, 1>(), std::integral_constant<int, 256>(), std::integral_constant<int, 4>());
+    else if (V <= 12288) go(std::integral_constant<int, 1>(), std::integral_constant<int, 512>(), std::integral_constant<int, 3>());
+    else if (V <= 16384) go(std::integral_constant<int, 1>(), std::integral_constant<int, 512>(), std::integral_constant<int, 4>());
+    else if (V <= 24576) go(std::integral_constant<int, 1>(), std::integral_constant<int, 1024>(), std::integral_constant<int, 3>());
+    else go(std::integral_constant<int, 1>(), std::integral_constant<int, 1024>(), std::integral_constant<int, 4>());
+    launch_k(KID_CE, k_ce_final, dim3(1), dim3(256), 0, st, (const float*)rowloss, (const float*)rowok, (long)T_ * B,
+             loss, ninv);
+    return true;
 }
 template <typename T>
 void launch_ce_grad(const float* z, const int32_t* tgt, const int32_t* lengths, const float* lse, const float* ninv,
