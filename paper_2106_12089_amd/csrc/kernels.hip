@@ -1849,9 +1849,121 @@ __global__ void __launch_bounds__(256) k_trans(FxArgs a) {
     transpose_block<T>(a.tr, a.trN, blockIdx.x, blockIdx.y, blockIdx.z, a.tr_gx, a.tr_gy, tile);
 }
 
+// N consecutive bf16 of p as VW at a time
+template <int VW>
+__device__ __forceinline__ void ld_run(const bf16* p, int n, uint32_t (&w)[4]) {
+    // n: elements of the run inside the row (a multiple of VW, or the whole run)
+    if constexpr (VW == 8) {
+        const uint4 q = *(const uint4*)p;
+        w[0] = q.x; w[1] = q.y; w[2] = q.z; w[3] = q.w;
+    } else if constexpr (VW == 4) {
+        const uint2 a = *(const uint2*)p, b = *(const uint2*)(p + (n > 4 ? 4 : 0));
+        w[0] = a.x; w[1] = a.y; w[2] = b.x; w[3] = b.y;
+    } else if constexpr (VW == 2) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = *(const uint32_t*)(p + (2 * e < n ? 2 * e : 0));
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            w[e] = (uint32_t)p[2 * e < n ? 2 * e : 0] | ((uint32_t)p[2 * e + 1 < n ? 2 * e + 1 : 0] << 16);
+    }
+}
+
+// bf16: the masked row-major copies of x and h0 and the pass initialisation of
+// TransArgs, where nothing is transposed.  Bound by memory: a thread takes 8
+// columns (one 16-byte store) of R rows, loaded VW elements at a time as the
+// rows' and the caller's alignment allow.  R = 4 where that leaves two blocks a CU,
+// else 1 (a launch's time either way).  The blocks of k_trans (32 x 32, 2 bytes
+// a lane) took 48 us for 16384 rows of 1024 (67 MB), these 20; 3200 rows
+// of 500 8.2 and 5.9.
+// grid: blocks of x, then of h0, then of the initialisation.
+template <int R>
+__global__ void __launch_bounds__(256) k_mask_rows(TransArgs a, int T_, int LD, int nbx, int nbh) {
+    const int tid = threadIdx.x;
+    const int bid = blockIdx.x;
+    if (bid >= nbx + nbh) {
+        if (bid == nbx + nbh) {
+            clear_counters(a.bar);
+            if (tid == 0) {
+                *a.err = 0;
+                *(int*)((char*)a.err + (SYNC_STATUS_OFS - SYNC_ERR_OFS)) = 0;   // a new step's status
+            }
+        }
+        const long nb = gridDim.x - nbx - nbh;
+        for (long i = (long)(bid - nbx - nbh) * 256 + tid; i < a.n_init; i += nb * 256) {
+            a.hT[i] = bf2f(((const bf16*)a.h0)[i]);
+            a.cT[i] = a.c0[i];
+        }
+        return;
+    }
+    const bool second = bid >= nbx;
+    const int K = second ? a.K2 : a.K, ldm = second ? a.ldh : a.ldm, np = (K + 7) / 8, rpb = 256 / np;
+    const long rows = (long)(second ? LD : T_) * a.B;
+    const int lr = tid / np, c = 8 * (tid % np), n = min(8, K - c);
+    if (lr >= rpb) return;
+    const bf16* src = (const bf16*)(second ? a.src2 : a.src);
+    const long r0 = (long)(second ? bid - nbx : bid) * R * rpb + lr;
+    const uint32_t al = (uint32_t)(uintptr_t)src | (2u * (uint32_t)K);
+    const bool m8 = (((uint32_t)(uintptr_t)(second ? a.mask2 : a.mask) | (uint32_t)a.kmax) & 7) == 0;
+    auto go = [&](auto vw) {
+        constexpr int VW = decltype(vw)::value;
+        uint32_t w[R][4];
+        uint64_t m[R];                                     // a byte per column
+        bf16* dst[R];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const long r = min(r0 + (long)i * rpb, rows - 1);
+            const int z = (int)(r / a.B), b = (int)(r - (long)z * a.B);   // matrix (step, or layer and direction), row
+            const uint8_t* mrow = a.mask + (size_t)z * a.kmax;
+            dst[i] = (bf16*)a.xm + (size_t)r * ldm + c;
+            if (second) {
+                const int tf = z % a.D ? a.n1 - 1 : 0;
+                mrow = a.mask2 + ((size_t)z * a.n1 + tf) * a.kmax;
+                dst[i] = (bf16*)((char*)a.hm + (size_t)z * a.hm_stride) + ((size_t)tf * a.B + b) * ldm + c;
+            }
+            if (m8) {                                      // (K <= kmax: within the row)
+                m[i] = *(const uint64_t*)(mrow + c);
+            } else {
+                m[i] = 0;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m[i] |= (uint64_t)mrow[c + (e < n ? e : 0)] << (8 * e);
+            }
+            ld_run<VW>(src + (size_t)r * K + c, n, w[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if (r0 + (long)i * rpb >= rows) return;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t lo = 2 * e < n && (m[i] >> (16 * e) & 0xff) ? 0xffffu : 0u;
+                const uint32_t hi = 2 * e + 1 < n && (m[i] >> (16 * e + 8) & 0xff) ? 0xffff0000u : 0u;
+                w[i][e] &= lo | hi;
+            }
+            *(uint4*)dst[i] = make_uint4(w[i][0], w[i][1], w[i][2], w[i][3]);
+        }
+    };
+    if ((al & 15) == 0) go(std::integral_constant<int, 8>());
+    else if ((al & 7) == 0) go(std::integral_constant<int, 4>());
+    else if ((al & 3) == 0) go(std::integral_constant<int, 2>());
+    else go(std::integral_constant<int, 1>());
+}
+
 void launch_fx_rows(RowsArgs& a, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
 void launch_dx_rows(RowsArgs& a, size_t part_bytes, hipStream_t st, hipEvent_t e0, hipEvent_t e1);
 void launch_prep_bf16(const FxArgs& a, hipStream_t st) {
+    const TransArgs& t = a.tr;
+    if (!t.dst && !t.dst2) {                   // (T matrices of x, the rest of h0)
+        const int LD = a.trN - t.n1;
+        const int rpt = (long)t.n1 * t.B * t.K >= 2L * 256 * 256 * 8 * 4 ? 4 : 1;
+        auto blocks = [&](long rows, int K) {
+            const long per = rpt * (256 / ((K + 7) / 8));
+            return (int)((rows + per - 1) / per);
+        };
+        const int nbx = blocks((long)t.n1 * t.B, t.K), nbh = blocks((long)LD * t.B, t.K2), nbi = nblk(t.n_init, 1024, 512);
+        launch_k(KID_TRANS, rpt == 4 ? k_mask_rows<4> : k_mask_rows<1>, dim3(nbx + nbh + nbi), dim3(256), 0, st, t, t.n1,
+                 LD, nbx, nbh);
+        return;
+    }
     launch_k(KID_TRANS, k_trans<bf16>, dim3(a.tr_gx, a.tr_gy, a.tr_gz), dim3(256), 0, st, a);
 }
 // the bf16 input product of a layer: over all rows, or per step over the kept neurons
