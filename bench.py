@@ -604,9 +604,10 @@ def cpu_baseline(wl, p_nr, p_rh, budget_s=12.0, max_steps=50, rows=None):
 
 KERNEL_SYMBOLS = {"fwd_persist": ("lsd::k_fwd_persist<", "lsd::k_fwd_res<"), "step": ("lsd::k_step<",),
                   "bwd_persist": ("lsd::k_bwd_persist<", "lsd::k_bwd_res<"), "bwd": ("lsd::k_bwd<",),
-                  "wgrad": ("lsd::k_wgrad",),            # the row-sparse, the full and the large-batch kernel
-                  "fx": ("lsd::k_fx<", "lsd::k_fx_big"), "dx": ("lsd::k_dx<", "lsd::k_dx_big"),
-                  "mask_build": ("lsd::k_mask_build",), "transpose": ("lsd::k_trans",)}
+                  "wgrad": ("lsd::k_wgrad",),            # every weight-gradient kernel
+                  "fx": ("lsd::k_fx<", "lsd::k_fx_big", "lsd::k_rows<0,"),
+                  "dx": ("lsd::k_dx<", "lsd::k_dx_big", "lsd::k_rows<1,"),
+                  "mask_build": ("lsd::k_mask_build",), "transpose": ("lsd::k_trans", "lsd::k_mask_rows")}
 SIMDS = 256 * 4             # MI355X: 256 compute units of 4 SIMDs
 XCDS = 8                    # GRBM_GUI_ACTIVE is counted once per XCD
 MFMA_BF16_FLOP_PER_MOP = 512

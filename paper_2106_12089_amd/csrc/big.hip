@@ -533,10 +533,7 @@ void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
         if (e0 && e1) hipExtLaunchKernelGGL(kern, grid, blk, (uint32_t)lds, st, e0, e1, 0, b);
         else kern<<<grid, blk, lds, st>>>(b);
     };
-    int big = b.R >= 4096 ? 200 : 1 << 30, mid = 256;
-#ifdef LSD_TUNE
-    if (const char* v = getenv("LSD_TUNE_W")) { big = v[0] == '2' ? 0 : 1 << 30; mid = v[0] == '1' ? 0 : 1 << 30; }
-#endif
+    const int big = b.R >= 4096 ? 200 : 1 << 30, mid = 256;
     if (fill(256, 256) >= big) go(k_wgrad_rows<2, 4, 8, 4>, 512, WrShape<2, 4, 8, 4>::LDS);
     else if (fill(128, 128) >= mid) go(k_wgrad_rows<2, 2, 4, 4>, 256, WrShape<2, 2, 4, 4>::LDS);
     else {

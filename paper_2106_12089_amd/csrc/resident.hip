@@ -799,16 +799,10 @@ template <typename Have>
 static Tiling best_tiling(int B, int H, int nslots, int ncu, int kchunks, double bytes_per_row, double base, double red,
                           const int* nis, const int* upt, int nn, Have rounds) {
     Tiling best{-1, 0, 0, 0, 0, 0, 0, 0, 0.0};
-#ifdef LSD_TUNE
-    const char* tv = getenv(nn == 2 ? "LSD_TUNE_B" : "LSD_TUNE_F");
-#endif
     for (int i = 0; i < nn; ++i)
         for (int mt = 1; mt <= 2; ++mt) {
             const double nr = rounds(nis[i], mt);                      // (< 0: no such build)
             if (nr < 0.0) continue;
-#ifdef LSD_TUNE
-            if (tv && (atoi(tv) != nis[i] || atoi(tv + 2) != mt)) continue;
-#endif
             Tiling t;
             t.ni = nis[i]; t.mt = mt;
             t.ntiles = (H + upt[i] - 1) / upt[i];
