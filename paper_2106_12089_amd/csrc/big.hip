@@ -1,14 +1,11 @@
-// Products of the step at large batches (gfx950, bf16, 64 rows or more): the
-// weight gradients (Eq. 11), the input products (Eq. 1-4) and the input
-// gradients (Eq. 10).  At a batch of a few hundred rows every product is a
-// large GEMM over gathered rows, so these kernels stage operand chunks in LDS
-// for a whole workgroup (8 waves on a 128- or 256-row tile), with the loads
-// issued two chunks ahead, where the small-batch kernels (one contraction
-// chunk per step, operands straight from the cache) are bound by latency.
+// Products off the recurrence (gfx950, bf16): weight gradients (Eq. 11), input
+// products (Eq. 1-4) and input gradients (Eq. 10).  k_wgrad_rows and k_rows are
+// matrix products over all (step, row) pairs on masked operands; k_fx_big and
+// k_dx_big gather a step's kept neurons, for batches of 256 and more where
+// skipping the dropped ones pays.  All stage operand chunks in LDS for a whole
+// workgroup, with the loads issued two chunks ahead.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
-
-#include <stdlib.h>
 
 #include <algorithm>
 #include <type_traits>
@@ -331,9 +328,10 @@ void launch_dx_big(const DxArgs& a, hipStream_t st, hipEvent_t e0, hipEvent_t e1
 // fewest bytes per product; 128 x 128 and 64 x 128 fill the chip when a pass has
 // few of those.  Against the kernels before (a step's rows padded to 32, transposed
 // operands, 128 x 256 tiles): batch 256 x hidden 1024 826 -> 565 us, AWD 277 -> 116,
-// LM-large 151 -> 83, LM-medium 38 -> 27, vocabulary head at batch 64 189 -> 105 us.  Workgroup i runs on XCD i % 8, which takes a contiguous range of
-// (problem, column block, row block): an XCD's L2 holds its columns' DA for all
-// their row blocks.
+// LM-large 151 -> 83, LM-medium 38 -> 27, vocabulary head at batch 64 189 -> 105 us.
+// Workgroup i runs on XCD i % 8, which takes a contiguous range of (problem,
+// column block, row block): an XCD's L2 holds its columns' DA for all their row
+// blocks.
 template <int WM, int WN, int MI, int NI>
 struct WrShape {
     static constexpr int NW = WM * WN, NTH = 64 * NW, TM = WM * MI * 16, TN = WN * NI * 16;

@@ -1,7 +1,8 @@
 // Persistent recurrent kernels of the fp32 path (gfx950; bf16 runs with its weights
-// in registers, elsewhere): one launch runs every time step of a layer.  Each workgroup keeps its slice of the recurrent
-// weight U in LDS and its part of the cell state in registers for the whole
-// sequence; the workgroups meet at a grid barrier once per step.
+// in registers, elsewhere): one launch runs every time step of a layer.  Each
+// workgroup keeps its slice of the recurrent weight U in LDS and its part of the
+// cell state in registers for the whole sequence; the workgroups meet at a grid
+// barrier once per step.
 //
 // The producer of h_t knows the next step's keep list (all masks are drawn
 // before the forward pass), so it writes h_t already compacted by that list
