@@ -339,7 +339,16 @@ struct WrShape {
     static constexpr size_t LDS = (size_t)2 * 32 * (AP + BP) * 2;
 };
 
-template <int WM, int WN, int MI, int NI>
+// Offsets into da are 32 bits from the step of a chunk's first row; where the steps that
+// a chunk's rows lie in take 2 GiB and more (a vocabulary head whose batch x columns
+// is 2^29 and more, or with a small batch a million columns), WIDE builds add up 64-bit
+// addresses.
+constexpr uint32_t WR_REACH = 0x7fffffffu;
+static bool wr_wide(const WrBatch& b) {
+    return (size_t)(b.B >= 32 ? 2 : 32 / b.B + 2) * (size_t)b.das * 2 > WR_REACH;
+}
+
+template <int WM, int WN, int MI, int NI, bool WIDE = false>
 __global__ void __launch_bounds__(64 * WM * WN, 2) k_wgrad_rows(WrBatch bt) {
     using S = WrShape<WM, WN, MI, NI>;
     constexpr int NTH = S::NTH, NW = S::NW, TM = S::TM, TN = S::TN, AP = S::AP, BPITCH = S::BP;
@@ -380,9 +389,12 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) k_wgrad_rows(WrBatch bt) {
     const int br = lane & 15, bk = lane >> 4;
     const uint32_t dasb = (uint32_t)(bt.das * 2);
     const uint32_t msmall = 65536u / (uint32_t)B + 1u;               // (B < 32: r / B = r * msmall >> 16 for r < 64)
-    uint32_t bofs[PB];                                               // column block, and this lane's column piece
+    typename std::conditional<WIDE, size_t, uint32_t>::type bofs[PB];   // column block, and this lane's column piece
 #pragma unroll
-    for (int i = 0; i < PB; ++i) bofs[i] = (uint32_t)min((n0 >> 5) + ((w + NW * i) >> 1), nch - 1) * 1024u + (uint32_t)bk * 256u;
+    for (int i = 0; i < PB; ++i) {
+        bofs[i] = min((n0 >> 5) + ((w + NW * i) >> 1), nch - 1);
+        bofs[i] = bofs[i] * 1024u + (uint32_t)bk * 256u;
+    }
     int it = 0, ib = 0;                                              // step and batch row of the next chunk's first row
     int ir = 0;                                                      // that row
     u32x4_t ra[2][PA], rbv[2][PB];
@@ -391,7 +403,7 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) k_wgrad_rows(WrBatch bt) {
             buf_rsrc((const bf16*)a.A + (size_t)ir * a.lda, (uint32_t)max(min(R - ir, 32), 0) * (uint32_t)a.lda * 2u);
         const size_t left = (size_t)max(bt.T - it, 0) * dasb;
         const __amdgpu_buffer_rsrc_t brc =
-            buf_rsrc((const bf16*)a.da + (size_t)it * bt.das, left < 0x7fffffffu ? (uint32_t)left : 0x7fffffffu);
+            buf_rsrc((const bf16*)a.da + (size_t)it * bt.das, left < WR_REACH ? (uint32_t)left : WR_REACH);
 #pragma unroll
         for (int i = 0; i < PA; ++i) ra[sl][i] = __builtin_amdgcn_raw_buffer_load_b128(arc, aofs + i * apass, 0, 0);
 #pragma unroll
@@ -399,8 +411,14 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) k_wgrad_rows(WrBatch bt) {
             const int r = ib + 16 * ((w + NW * i) & 1) + br;
             const int dt = B >= 32 ? (r >= B ? 1 : 0) : (int)(((uint32_t)r * msmall) >> 16);
             const int b = r - dt * B;
-            rbv[sl][i] = __builtin_amdgcn_raw_buffer_load_b128(
-                brc, (uint32_t)dt * dasb + (uint32_t)((b >> 4) * nch) * 1024u + (uint32_t)(b & 15) * 16u + bofs[i], 0, 0);
+            if constexpr (WIDE) {
+                const char* p = (const char*)a.da + (size_t)(it + dt) * (size_t)bt.das * 2 +
+                                (size_t)(b >> 4) * nch * 1024 + (size_t)(b & 15) * 16 + bofs[i];
+                rbv[sl][i] = it + dt < bt.T ? *(const u32x4_t*)p : u32x4_t{0, 0, 0, 0};
+            } else {
+                rbv[sl][i] = __builtin_amdgcn_raw_buffer_load_b128(
+                    brc, (uint32_t)dt * dasb + (uint32_t)((b >> 4) * nch) * 1024u + (uint32_t)(b & 15) * 16u + bofs[i], 0, 0);
+            }
         }
         ir += 32;
         if (B >= 32) {
@@ -532,7 +550,13 @@ void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
         else kern<<<grid, blk, lds, st>>>(b);
     };
     const int big = b.R >= 4096 ? 200 : 1 << 30, mid = 256;
-    if (fill(256, 256) >= big) go(k_wgrad_rows<2, 4, 8, 4>, 512, WrShape<2, 4, 8, 4>::LDS);
+    if (wr_wide(b)) {
+        if (fill(256, 256) >= big) go(k_wgrad_rows<2, 4, 8, 4, true>, 512, WrShape<2, 4, 8, 4>::LDS);
+        else {
+            fill(64, 128);
+            go(k_wgrad_rows<1, 4, 4, 2, true>, 256, WrShape<1, 4, 4, 2>::LDS);
+        }
+    } else if (fill(256, 256) >= big) go(k_wgrad_rows<2, 4, 8, 4>, 512, WrShape<2, 4, 8, 4>::LDS);
     else if (fill(128, 128) >= mid) go(k_wgrad_rows<2, 2, 4, 4>, 256, WrShape<2, 2, 4, 4>::LDS);
     else {
         fill(64, 128);
@@ -846,6 +870,8 @@ static bool rows_lds() {
 int setup_big_attributes() {
     bool ok = hipFuncSetAttribute((const void*)k_wgrad_rows<2, 4, 8, 4>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)WrShape<2, 4, 8, 4>::LDS) == hipSuccess;
+    ok = hipFuncSetAttribute((const void*)k_wgrad_rows<2, 4, 8, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)WrShape<2, 4, 8, 4>::LDS) == hipSuccess && ok;
     ok = hipFuncSetAttribute((const void*)k_fx_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)FB_LDS) ==
              hipSuccess && ok;
     ok = hipFuncSetAttribute((const void*)k_dx_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)DB_LDS) ==
