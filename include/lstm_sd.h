@@ -350,9 +350,13 @@ int lstm_sd_case1_dropout_backward(int32_t seq_len, int32_t batch, int32_t featu
  * step of Eq. 1-6 forward, of Eq. 7-10 backward, needs the whole h_{t-1} or
  * DA of the step before).  Every barrier wait is bounded by wall-clock time
  * (0.5 s by default); a wait that times out stops its launch, and then:
- *   - the forward writes NaN into hT, cT and every step of y;
+ *   - the forward writes NaN into hT, cT and every step of y, whole: also what
+ *     rows, directions and layers that were done before the time-out had written;
  *   - the backward writes NaN into dh0, dc0, dx and every weight and bias
- *     gradient (also when it was the forward of the same step that failed);
+ *     gradient (also when it was the forward of the same step that failed).
+ *     A pass of two directions or of more than four layers may keep the weight
+ *     gradients of the layers above the one that failed in its backward: they
+ *     are written before that one runs;
  *   - the pass bit (1 = forward, 2 = backward) is ORed into a status word in
  *     the workspace, which lstm_sd_forward's first kernel clears.
  * lstm_sd_status waits for `stream` (a host synchronisation: not for graph

@@ -265,6 +265,14 @@ static long long barrier_timeout_ticks() {
     if (sec < 0.0) return (long long)khz * 500;
     return (long long)(sec * 1000.0 * khz);
 }
+// LSTM_SD_FAIL_LAUNCH=n: the n-th persistent launch of every pass (from 0) gets a zero
+// time-out, so that tests of the failure path can fail one of several
+static thread_local int g_launch_no = 0;
+long long launch_timeout() {
+    const int n = g_launch_no++;
+    const char* v = getenv("LSTM_SD_FAIL_LAUNCH");
+    return v && v[0] && atoi(v) == n ? 0 : barrier_timeout_ticks();
+}
 
 static int hip_check(const char* where) {
     hipError_t e = hipGetLastError();
@@ -337,6 +345,9 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
     const size_t es = P.esize;
     char* R = (char*)reserve;
     char* W = (char*)ws;
+    const size_t ns = (size_t)L * D * B * H;
+    const Poison poison = {{hT, cT, y}, {ns, ns, (size_t)T * B * D * H}};
+    g_launch_no = 0;
     // x (T matrices) and h0 (L*D matrices) as the weight gradients read them
     // (fp32: transposed; bf16: masked), and the pass initialised (hT, cT, barrier
     // counters): in fp32 these ride on the first input product launch (independent
@@ -400,7 +411,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
         pa.lengths = lengths;
         pa.bar = (unsigned*)(W + P.w_sync);
         pa.err = (int*)(W + P.w_sync + SYNC_ERR_OFS);
-        pa.timeout = barrier_timeout_ticks();
+        pa.poison = poison;
         pa.B = B; pa.H = H; pa.HP = P.HP; pa.T = T; pa.BP = BP; pa.ldy = D * H; pa.dense = !P.compact;
         pa.mtiles = P.mtiles;
         pa.xxs = P.xxs;
@@ -498,7 +509,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
         ra.lengths = lengths;
         ra.bar = (unsigned*)(W + P.w_sync);
         ra.err = (int*)(W + P.w_sync + SYNC_ERR_OFS);
-        ra.timeout = barrier_timeout_ticks();
+        ra.poison = poison;
         ra.B = B; ra.H = H; ra.T = T; ra.BP = BP; ra.ldy = D * H; ra.ldyb = P.DHP; ra.ldh = P.HP; ra.kmax = P.kmax;
         ra.mtiles = P.mtiles;
         int n = 0;
@@ -639,6 +650,9 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
     const size_t es = P.esize;
     const char* R = (const char*)reserve;
     char* W = (char*)ws;
+    const size_t ns = (size_t)L * D * B * H;
+    const Poison poison = {{dh0, dc0, nullptr}, {ns, ns, 0}};
+    g_launch_no = 0;
     unsigned* sync_bar = (unsigned*)(W + P.w_sync);
     int* sync_err = (int*)(W + P.w_sync + SYNC_ERR_OFS);
     const int* sync_status = (const int*)(W + P.w_sync + SYNC_STATUS_OFS);
@@ -656,7 +670,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
         pa.lengths = lengths;
         pa.bar = (unsigned*)(W + P.w_sync);
         pa.err = (int*)(W + P.w_sync + SYNC_ERR_OFS);
-        pa.timeout = barrier_timeout_ticks();
+        pa.poison = poison;
         pa.B = B; pa.H = H; pa.T = T; pa.BP = BP; pa.ldy = D * H;
         pa.kmax = P.kmax; pa.dense = !P.compact; pa.mtiles = P.mtiles;
     };
@@ -689,7 +703,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
         ra.lengths = lengths;
         ra.bar = sync_bar;
         ra.err = sync_err;
-        ra.timeout = barrier_timeout_ticks();
+        ra.poison = poison;
         ra.B = B; ra.H = H; ra.T = T; ra.kmax = P.kmax; ra.mtiles = P.mtiles;
         int n = 0;
         for (int l = l1; l >= l0; --l) {

@@ -230,6 +230,17 @@ struct RowsArgs {
     int total, per;                     // (set at launch)
 };
 
+// Outputs of a pass that a timed-out barrier wait poisons with NaN (forward: hT, cT and
+// y; backward: dh0 and dc0), whole: also what launches, layers and row groups that were
+// done before wrote.
+struct Poison {
+    float* p[3];
+    size_t n[3];
+};
+// the bound of the next persistent launch's barrier waits, in wall-clock ticks (<= 0:
+// every wait fails at once)
+long long launch_timeout();
+
 // Persistent forward recurrence of one layer (both directions): one
 // launch runs all T steps.
 struct PFwdDir {
@@ -296,6 +307,7 @@ struct PFwdArgs {
     unsigned* bar;                      // barrier counters (BAR_LINES lines per slot; clear at launch)
     int* err;                           // barrier time-out flag
     long long timeout;                  // wall-clock ticks (<= 0: every wait fails at once)
+    Poison poison;
     int B, H, HP, T, BP, ldy, dense, ntiles, mgroups, mtiles;
     int nslots, KP, kin_max;            // KP: LDS pitch of the W slices (0: no slot has Win)
     size_t wofs, kofs;                  // LDS offsets of the W slice and the keep lists (set by the launcher)
@@ -339,6 +351,7 @@ struct RFwdArgs {
     unsigned* bar;
     int* err;
     long long timeout;
+    Poison poison;
     int B, H, T, BP, ldy, ldyb, ldh, kmax, mtiles, nslots;
     int ntiles, mgroups, mg0, rg, gpx;  // (set by the launcher) unit tiles; row groups of the launch, the first one, their rows; groups per XCD
 };
@@ -367,6 +380,7 @@ struct RBwdArgs {
     unsigned* bar;
     int* err;
     long long timeout;
+    Poison poison;
     int B, H, T, kmax, mtiles, nslots;
     int ntiles, mgroups, mg0, rg, gpx;
 };
@@ -407,6 +421,7 @@ struct PBwdArgs {
     unsigned* bar;
     int* err;
     long long timeout;                  // wall-clock ticks (<= 0: every wait fails at once)
+    Poison poison;
     int B, H, T, BP, ldy, lddx, kmax, dense, ntiles, mgroups, mtiles, nslots;
 };
 

@@ -367,7 +367,7 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
             prefetch(s + 1);
             grid_arrive(bar);                   // (also: every wave is past its reads of red)
         }
-        grid_exit(a.bar, a.nslots, a.err);
+        grid_exit(a.bar, a.nslots, a.err, a.poison);
         return;
     }
 
@@ -486,19 +486,15 @@ __global__ void __launch_bounds__(512) k_fwd_persist(PFwdArgs a) {
         prefetch(s + 1);
         if (has_x && s + 1 < T_ && !x_product(s + 1)) break;
     }
-    // ---- final state (NaN if the barrier timed out, and then also every
-    // step of the top layer's output)
-    const bool failed = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    // ---- final state
 #pragma unroll
     for (int q = 0; q < PPT; ++q) {
         if (pb[q] < B && pu[q] < H) {
-            D.hT[(size_t)pb[q] * H + pu[q]] = failed ? __builtin_nanf("") : hreg[q];
-            D.cT[(size_t)pb[q] * H + pu[q]] = failed ? __builtin_nanf("") : creg[q];
-            if (failed && D.y)
-                for (int t = 0; t < T_; ++t) D.y[((size_t)t * B + pb[q]) * a.ldy + pu[q]] = __builtin_nanf("");
+            D.hT[(size_t)pb[q] * H + pu[q]] = hreg[q];
+            D.cT[(size_t)pb[q] * H + pu[q]] = creg[q];
         }
     }
-    grid_exit(a.bar, a.nslots, a.err);
+    grid_exit(a.bar, a.nslots, a.err, a.poison);
 }
 
 // ---------------------------------------------------------------------------
@@ -699,7 +695,7 @@ __global__ void __launch_bounds__(1024) k_bwd_persist(PBwdArgs a) {
             }
             grid_arrive(bar);
         }
-        grid_exit(a.bar, a.nslots, a.err);
+        grid_exit(a.bar, a.nslots, a.err, a.poison);
         return;
     }
 
@@ -801,18 +797,7 @@ __global__ void __launch_bounds__(1024) k_bwd_persist(PBwdArgs a) {
         }
         prefetch(s + 1);
     }
-    // a timed-out barrier, here or in the forward pass of the step, poisons
-    // the input-state gradients
-    if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-        __hip_atomic_load(sync_status(a.err), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-#pragma unroll
-        for (int q = 0; q < PPT; ++q)
-            if (pb[q] < B && pu[q] < H) {
-                D.dh0[(size_t)pb[q] * H + pu[q]] = __builtin_nanf("");
-                D.dc0[(size_t)pb[q] * H + pu[q]] = __builtin_nanf("");
-            }
-    }
-    grid_exit(a.bar, a.nslots, a.err);
+    grid_exit(a.bar, a.nslots, a.err, a.poison);
 }
 
 // ---------------------------------------------------------------------------
@@ -881,6 +866,7 @@ hipError_t launch_fwd_persist(PFwdArgs& a, hipStream_t st, int kid_timer_on, hip
                                    : (MG == 32 ? k_fwd_persist<T, 2, 32> : k_fwd_persist<T, 2, 64>);
     hipError_t e = resident_limit((const void*)fn, 64 * PF_NW, lds, nwg);
     if (e != hipSuccess) return e;
+    a.timeout = launch_timeout();
     if (kid_timer_on) (void)hipEventRecord(e0, st);
     hipLaunchKernelGGL(fn, dim3(nwg), dim3(64 * PF_NW), lds, st, a);
     e = hipGetLastError();
@@ -896,10 +882,11 @@ size_t bwd_persist_lds(int H, int UB, int MG, int esize) {
 }
 
 template <typename T, int UB, int MG, int MC>
-static hipError_t launch_bwd_persist_t(const PBwdArgs& a, int nwg, size_t lds, hipStream_t st) {
+static hipError_t launch_bwd_persist_t(PBwdArgs& a, int nwg, size_t lds, hipStream_t st) {
     auto fn = k_bwd_persist<T, UB, MG, MC>;
     const hipError_t e = resident_limit((const void*)fn, 64 * PB_NW, lds, nwg);
     if (e != hipSuccess) return e;
+    a.timeout = launch_timeout();
     hipLaunchKernelGGL(fn, dim3(nwg), dim3(64 * PB_NW), lds, st, a);
     return hipGetLastError();
 }

@@ -129,9 +129,9 @@ __device__ __forceinline__ bool res_wait(unsigned* bar, int g, int n, unsigned s
     const bool r = ok != 0;
     return r;
 }
-// The last workgroup to leave (of `total` working ones) returns the counters,
-// the flags and the error flag to zero for the next launch.
-__device__ __forceinline__ void res_exit(unsigned* bar, int ngroups, int total, int* err) {
+// The last workgroup to leave (of `total` working ones) poisons the outputs of a failed
+// pass and returns the counters, the flags and the error flag to zero for the next launch.
+__device__ __forceinline__ void res_exit(unsigned* bar, int ngroups, int total, int* err, const Poison& out) {
     __shared__ int last;
     res_drain();
     if (threadIdx.x == 0)
@@ -139,6 +139,7 @@ __device__ __forceinline__ void res_exit(unsigned* bar, int ngroups, int total, 
                                       __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(total - 1);
     __syncthreads();
     if (!last) return;
+    poison_if_failed(out, err);
     for (int i = threadIdx.x; i < ngroups * RB_LINES * RB_PITCH; i += blockDim.x)
         __hip_atomic_store(bar + i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (threadIdx.x == 0) {
@@ -385,7 +386,7 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
             }
             res_signal(a.bar, g, tile, (unsigned)(s + 1));
         }
-        res_exit(a.bar, a.nslots * a.mgroups, total, a.err);
+        res_exit(a.bar, a.nslots * a.mgroups, total, a.err, a.poison);
         return;
     }
 
@@ -501,18 +502,15 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
     }
     lds_barrier();
     if (D.ybufT && done > 0) store_transposed(done - 1);
-    // final state (NaN if a barrier wait timed out, and then every step of y)
-    const bool failed = __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+    // final state
 #pragma unroll
     for (int q = 0; q < PPT; ++q) {
         const Pair r = pair_of(q, tid);
         if (!r.ok) continue;
-        D.hT[(size_t)r.b * H + r.u] = failed ? __builtin_nanf("") : hreg[q];
-        D.cT[(size_t)r.b * H + r.u] = failed ? __builtin_nanf("") : creg[q];
-        if (failed && D.y)
-            for (int t = 0; t < T_; ++t) D.y[((size_t)t * B + r.b) * a.ldy + r.u] = __builtin_nanf("");
+        D.hT[(size_t)r.b * H + r.u] = hreg[q];
+        D.cT[(size_t)r.b * H + r.u] = creg[q];
     }
-    res_exit(a.bar, a.nslots * a.mgroups, total, a.err);
+    res_exit(a.bar, a.nslots * a.mgroups, total, a.err, a.poison);
 }
 
 // ---------------------------------------------------------------------------
@@ -674,7 +672,7 @@ __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
             }
             res_signal(a.bar, g, tile, (unsigned)(s + 1));
         }
-        res_exit(a.bar, a.nslots * a.mgroups, total, a.err);
+        res_exit(a.bar, a.nslots * a.mgroups, total, a.err, a.poison);
         return;
     }
 
@@ -697,15 +695,14 @@ __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
         }
     };
     prefetch(0);
-    bool good = true;
     for (int s = 0; s <= T_; ++s) {
         const bool final_pass = s == T_;
         const int t = final_pass ? -1 : step_t(s);
         const int tn = D.dir == 0 ? T_ - s : s - 1;         // step processed just before
         // DA of the step before from every tile of the group, and the worker's
         // dx of this step (past the last one: its last flag, already seen)
-        if ((s > 0 || fed) && !(good = res_wait(a.bar, g, a.ntiles, (unsigned)s, gdep, tile, (unsigned)min(s + 1, T_), a.err,
-                                                a.timeout, STATUS_BWD)))
+        if ((s > 0 || fed) && !res_wait(a.bar, g, a.ntiles, (unsigned)s, gdep, tile, (unsigned)min(s + 1, T_), a.err,
+                                        a.timeout, STATUS_BWD))
             break;
         const int th = opaque_tid();
         if (fed && !final_pass) {
@@ -754,20 +751,7 @@ __global__ void __launch_bounds__(512) k_bwd_res(RBwdArgs a) {
         res_arrive(a.bar, g, tile);                         // DA_t is published
         prefetch(s + 1);
     }
-    // a timed-out barrier, here or in the forward pass of the step, poisons
-    // the input-state gradients
-    if (!good || __hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 ||
-        __hip_atomic_load(sync_status(a.err), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-#pragma unroll
-        for (int q = 0; q < PPT; ++q) {
-            const Pair r = pair_of(q, tid);
-            if (r.ok) {
-                D.dh0[(size_t)r.b * H + r.u] = __builtin_nanf("");
-                D.dc0[(size_t)r.b * H + r.u] = __builtin_nanf("");
-            }
-        }
-    }
-    res_exit(a.bar, a.nslots * a.mgroups, total, a.err);
+    res_exit(a.bar, a.nslots * a.mgroups, total, a.err, a.poison);
 }
 
 // ---------------------------------------------------------------------------
@@ -839,6 +823,7 @@ static hipError_t launch_groups(void (*fn)(Args), Args& a, const Tiling& t, size
     for (int g0 = 0; g0 < t.mg; g0 += t.gpl) {
         a.mg0 = g0;
         a.mgroups = std::min(t.gpl, t.mg - g0);
+        a.timeout = launch_timeout();
         hipLaunchKernelGGL(fn, dim3(grid(a.nslots * a.mgroups)), dim3(512), lds, st, a);
         e = hipGetLastError();
         if (e != hipSuccess) return e;

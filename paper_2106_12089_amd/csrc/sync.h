@@ -121,23 +121,38 @@ __device__ __forceinline__ bool grid_wait(unsigned* sbar, int slot, int nslot, u
     return ok != 0;
 }
 
+// The last workgroup of a launch to leave: NaN in the pass's outputs if a wait of this
+// launch, or of one before it in the pass, has timed out (the sticky status word).  A
+// workgroup cannot decide that for itself: rows, directions and layers that do not wait
+// for the one that fails have left by then, or ran in an earlier launch.  What they wrote
+// is complete at the coherence point before they counted themselves out (their stores
+// drained, then a release), and this workgroup has acquired since.
+__device__ __forceinline__ void poison_if_failed(const Poison& o, int* err) {
+    if (__hip_atomic_load(sync_status(err), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) return;
+    for (int k = 0; k < 3; ++k)
+        for (size_t i = threadIdx.x; i < o.n[k]; i += blockDim.x) o.p[k][i] = __builtin_nanf("");
+}
+
 // Every workgroup ends here, past its last barrier wait; the last one to
-// arrive returns the step counters, the error flag and the exit counter to
-// zero, so the next launch starts clear without a clearing kernel.  (The
-// outputs' time-out check comes before: the flag is read by then.  A
-// time-out stays recorded in the sticky status word, which this does not
-// clear.)
-__device__ __forceinline__ void grid_exit(unsigned* bar, int nslots, int* err) {
+// arrive poisons the outputs of a failed pass and returns the step counters,
+// the error flag and the exit counter to zero, so the next launch starts clear
+// without a clearing kernel.  (A time-out stays recorded in the sticky status
+// word, which this does not clear.)
+__device__ __forceinline__ void grid_exit(unsigned* bar, int nslots, int* err, const Poison& out) {
+    __shared__ int last;
+    unsigned* ex = slot_bar(bar, BAR_EXIT);
+    __builtin_amdgcn_s_waitcnt(0);      // this thread's stores have completed
     __syncthreads();
+    if (threadIdx.x == 0)
+        last = __hip_atomic_fetch_add(ex, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+    __syncthreads();
+    if (!last) return;
+    poison_if_failed(out, err);
     if (threadIdx.x == 0) {
-        unsigned* ex = slot_bar(bar, BAR_EXIT);
-        const unsigned tk = __hip_atomic_fetch_add(ex, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (tk == gridDim.x - 1) {
-            for (int i = 0; i < nslots * BAR_LINES; ++i)
-                __hip_atomic_store(bar + BAR_PITCH * i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(ex, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        for (int i = 0; i < nslots * BAR_LINES; ++i)
+            __hip_atomic_store(bar + BAR_PITCH * i, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(err, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(ex, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

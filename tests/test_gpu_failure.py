@@ -109,3 +109,59 @@ def test_forced_barrier_timeout_large_batch_recurrences():
     for k in ("dW", "dU", "db"):
         for i, (a, b) in enumerate(zip(got[k], ref[k])):
             assert np.array_equal(a, b), (k, i)
+
+
+@pytest.mark.parametrize("dtype,L,D,H,B", [
+    ("bf16", 2, 2, 40, 20),           # a launch per layer
+    ("f32", 2, 2, 40, 20),
+    ("bf16", 1, 2, 520, 300),         # several launches of row groups
+    ("bf16", 5, 1, 24, 17),           # more layers than one launch takes
+    ("f32", 5, 1, 24, 17),
+])
+@pytest.mark.parametrize("which", [0, 1])
+def test_one_launch_of_several_times_out(dtype, L, D, H, B, which, monkeypatch):
+    """A barrier time-out in one persistent launch of a pass that takes several (a zero
+    bound for that launch alone): what the launches before and after it wrote is poisoned
+    all the same, and the next pass is clean."""
+    import dataclasses
+    from paper_2106_12089_amd import binding as B_
+    from paper_2106_12089_amd.session import Session
+    cfg = dataclasses.replace(workloads.get_config("tiny"), name="fail", dtype=dtype, loss="mse", num_layers=L,
+                              num_dirs=D, input_dim=24, hidden=H, batch=B, seq_len=3)
+    wl = workloads.make_workload(cfg)
+    say(f"[gpu] one launch fails {dtype} L={L} D={D} H={H} B={B} which={which}")
+
+    def step(s, fwd, bwd):
+        s.masks(cfg.mask_seed, 0)
+        monkeypatch.setenv("LSTM_SD_FAIL_LAUNCH", str(which) if fwd else "")
+        s.forward()
+        s.loss_grad()
+        monkeypatch.setenv("LSTM_SD_FAIL_LAUNCH", str(which) if bwd else "")
+        s.backward()
+        torch.cuda.synchronize()
+        monkeypatch.setenv("LSTM_SD_FAIL_LAUNCH", "")
+        return s.outputs()
+
+    ref = step(Session(wl, 0.5, 0.3, 1), False, False)
+    s = Session(wl, 0.5, 0.3, 1)
+    out = step(s, True, False)
+    with pytest.raises(B_.LstmSdError, match="forward"):
+        B_.lstm_sd_status(s.dims, s.workspace)
+    for k in ("y", "hT", "cT", "dx", "dh0", "dc0"):
+        assert np.isnan(out[k]).all(), k
+    out = step(s, False, True)
+    with pytest.raises(B_.LstmSdError, match="backward"):
+        B_.lstm_sd_status(s.dims, s.workspace)
+    assert np.isfinite(out["y"]).all()
+    for k in ("dx", "dh0", "dc0"):
+        assert np.isnan(out[k]).all(), k
+    # (fp32 writes a layer's weight gradients before the next layer's recurrence runs;
+    # bf16 at these sizes writes all of them at the end)
+    low = L * D if dtype == "bf16" else D
+    for k in ("dW", "dU", "db"):
+        for i, a in enumerate(out[k][:low]):
+            assert np.isnan(a).all(), (k, i)
+    out = step(s, False, False)
+    B_.lstm_sd_status(s.dims, s.workspace)
+    for k in ("y", "hT", "cT", "dx", "dh0", "dc0"):
+        assert np.array_equal(out[k], ref[k]), k
