@@ -432,6 +432,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
             f.x = l == 0 ? (const void*)(R + P.r_xm) : X;
             f.lda = l == 0 ? P.IP : P.DHP;
             f.np = D; f.s = P.s_nr[l];
+            f.mask = site_view(P, mbuf, P.site_nr(l)).mask; f.kmax = P.kmax;
             for (int d = 0; d < D; ++d) {
                 f.W[d] = w->W[l * D + d];
                 f.bias[d] = w->b[l * D + d];
@@ -1344,6 +1345,7 @@ int lstm_sd_head_forward(const lstm_sd_head_dims* hd, const void* W_fc, const fl
         x.R = P.T * P.B; x.B = P.B; x.K = P.F; x.G = P.V;
         x.x = W + P.w_yb; x.lda = P.FP; x.np = 1; x.s = P.s;
         x.W[0] = W_fc; x.bias[0] = b_fc; x.out[0] = logits;
+        x.mask = f.site.mask; x.kmax = P.F;
         launch_fx_bf16(x, st);
     } else {
         launch_head_prep<float>(y, W + P.w_yb, W + P.w_ybT, f.site, P.T, P.B, P.F, P.BP, P.FP, st);

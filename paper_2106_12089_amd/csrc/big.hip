@@ -760,6 +760,7 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) k_rows(RowsArgs a) {
     }
     if (c < nc) multiply(0);
     // output r of this lane: column 4*(lane/16)+r of the tile, row lane%16
+    bool nan = false;
     const bool failed = MODE == ROWS_DX && a.status && *a.status != 0;
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
@@ -773,6 +774,7 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) k_rows(RowsArgs a) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = a.s * acc[i][j][e];
             if constexpr (MODE == ROWS_FX) {
+                nan = nan || v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3];
                 const float4 bn = *(const float4*)(a.bias[z] + n);   // (M = G is a multiple of 4)
                 *(float4*)(a.out[z] + (size_t)r * a.M + n) = make_float4(v[0] + bn.x, v[1] + bn.y, v[2] + bn.z, v[3] + bn.w);
             } else if (a.slices > 1) {
@@ -798,6 +800,26 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) k_rows(RowsArgs a) {
                         if (n + e < a.M) o[e] = v[e];
                 }
             }
+        }
+    }
+    // A weight row that holds Inf or NaN makes a dropped neuron's product with it NaN, where
+    // the method does not read the row: outputs that are NaN are formed again, over the kept
+    // neurons alone (and end at the first kept one that makes them NaN).
+    if constexpr (MODE == ROWS_FX) {
+        if (!nan) return;
+#pragma unroll 1
+        for (int x = 0; x < MI * NI * 4; ++x) {
+            const int r = r0 + (wn * NI + x / (4 * MI)) * 16 + br, n = m0 + (wm * MI + x / 4 % MI) * 16 + 4 * bk + x % 4;
+            if (r >= a.R || n >= a.M) continue;
+            float* o = a.out[z] + (size_t)r * a.M + n;
+            if (*o == *o) continue;
+            const uint8_t* mk = a.mask + (size_t)(r / B) * a.kmax;
+            const bf16 *xr = (const bf16*)a.x + (size_t)r * a.lda, *wc = (const bf16*)a.W[z] + n;
+            float v = 0.0f;
+#pragma unroll 1
+            for (int k = 0; k < a.K && v == v; ++k)
+                if (mk[k]) v += bf2f(xr[k]) * bf2f(wc[(size_t)k * G]);
+            *o = a.s * v + a.bias[z][n];
         }
     }
 }

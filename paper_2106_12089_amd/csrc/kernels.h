@@ -220,7 +220,7 @@ struct RowsArgs {
     // input gradient: out[0] = s * mask * sum over D directions of da[d] W[d]^T
     const void* da[2]; long das;        // [T] x fragment-major [B][G]
     int D, kmax, slices;                // (slices set at launch)
-    const uint8_t* mask;                // [T][kmax] rows of the output's neurons
+    const uint8_t* mask;                // [T][kmax] rows of the input's (input gradient: the output's) neurons
     const int* status;                  // sticky barrier status of the step, or null
     float* part;                        // partial products of the slices
     const void* W[2];                   // [K][G]

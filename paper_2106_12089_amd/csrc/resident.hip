@@ -49,6 +49,8 @@
 
 namespace lsd {
 
+typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+
 // LDS-only workgroup barrier: this wave's LDS accesses are done, its global
 // loads and stores stay in flight.
 __device__ __forceinline__ void lds_barrier() {
@@ -178,6 +180,24 @@ __device__ __forceinline__ uint32_t half_of(uint16_t x, int) { return x; }
 __device__ __forceinline__ uint32_t half_of(uint32_t x, int v) { return v ? x >> 16 : x & 0xffffu; }
 __device__ __forceinline__ uint32_t half_of(uint2 x, int v) { return half_of(v & 2 ? x.y : x.x, v & 1); }
 
+// The gate sums of unit u of row b over the kept neurons alone, from the exchanged block
+// src and the weights in memory.  A weight row that holds Inf or NaN makes a dropped
+// neuron's product with it NaN, where the method does not read the row: in a workgroup
+// that has met one in its weights, a sum that is NaN is formed again here (and ends at
+// the first kept neuron that makes all four gates NaN).
+__device__ __forceinline__ float4 kept_sum(const bf16* src, const bf16* U, const uint8_t* mask, int b, int u, int H) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 1
+    for (int k = 0; k < H; ++k) {
+        if (!mask[k]) continue;
+        const float h = bf2f(__hip_atomic_load(src + frag_off(b, k, (H + 31) / 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const bf16* p = U + (size_t)k * (4 * H) + u;
+        v.x += h * bf2f(p[0]); v.y += h * bf2f(p[H]); v.z += h * bf2f(p[2 * H]); v.w += h * bf2f(p[3 * H]);
+        if (v.x != v.x && v.y != v.y && v.z != v.z && v.w != v.w) break;
+    }
+    return v;
+}
+
 // ---------------------------------------------------------------------------
 // Forward (Eq. 1-6).  Unit tile = 4*NTL units = NTL column tiles of the four
 // gates of 4 units; rows = 16*MT.  Wave w holds the 32-neuron chunks w + 8c,
@@ -210,6 +230,7 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
     float4* red = (float4*)smem;                           // [8 waves][NF][RF_FP]
     bf16* sty = (bf16*)(smem + rf_red_bytes<NTL, MT>());   // [2][UT][SP] layer output of the tile, transposed
     __shared__ int len_s[MG];                              // lengths of the rows
+    __shared__ int bad_s[NW];                              // Inf or NaN among a wave's weights
     const int H = a.H, G = 4 * H, B = a.B, T_ = a.T;
     const int total = a.nslots * a.mgroups * a.ntiles;
     int g, tile;
@@ -233,6 +254,7 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
     // transposing reads.  (Gathering the fragments' 2-byte elements from memory
     // took 30-80 us per launch.)
     bf16x8_t ub[KC][NTL];
+    u16x2_t most = {0, 0};                                 // the largest magnitudes' bits: 0x7f80 and above are Inf and NaN
     {
         const bf16* U = (const bf16*)D.U;
         constexpr int WP = rf_wpitch(NTL);
@@ -274,11 +296,16 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
                 const bf16* p = st + (g8 + (cl >> 2)) * WP + 16 * j + 4 * (lane & 3);
                 const uint2 lo = lds_tr4(p), hi = lds_tr4(p + 4 * WP);
                 ub[c][j] = __builtin_bit_cast(bf16x8_t, u32x4_t{lo.x, lo.y, hi.x, hi.y});
+                for (uint32_t x : {lo.x, lo.y, hi.x, hi.y})
+                    most = __builtin_elementwise_max(most, __builtin_bit_cast(u16x2_t, x & 0x7fff7fffu));
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
+        const bool bad = __builtin_amdgcn_ballot_w64(most[0] >= 0x7f80 || most[1] >= 0x7f80) != 0;
+        if (lane == 0) bad_s[w] = bad;
         lds_barrier();                                     // (the parts overlap red of other waves)
     }
+    const bool spoilt = __builtin_amdgcn_ballot_w64(bad_s[lane & (NW - 1)] != 0) != 0;
     // this thread's (row, unit) pair q.  Derived anew from the (opaque) thread
     // index where a step needs it: kept in registers it would cost the large
     // tiles their room.  A pair outside the tile or the shape reads valid
@@ -311,10 +338,23 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
     constexpr uint32_t cstep = NW * 1024;                  // bytes from chunk c to c + 1 of a wave
     // (only a wave's last chunk can be past the last one)
     auto cofs = [&](int mt, int c) { return c + 1 < KC || w + NW * c < nch ? lofs[mt] + (uint32_t)c * cstep : OOB_OFF; };
+    auto red_sum = [&](int i) {
+        float4 v = red[i];
+#pragma unroll
+        for (int k = 1; k < NW; ++k) {
+            const float4 x = red[k * NF * RF_FP + i];
+            v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+        }
+        return v;
+    };
     // partial products of one exchanged block, into red: a row tile at a time
     // (its sums go to LDS under the products of the next), R loads in flight
-    auto product = [&](const bf16* src) {
-        constexpr int NA = KC * MT, R = NA < 8 ? NA : 8;
+    // (mask: the contraction's kept neurons)
+    auto product = [&](const bf16* src, const uint8_t* mask) {
+        // (8 in flight spill where the weights fill the registers: three layers of 1150,
+        // 70 steps: 375 us with 8, 360 with 4; two of 1500, 35 steps: 213 and 195; two
+        // of 1024 at 256 rows, 64 steps: 786 and 768)
+        constexpr int NA = KC * MT, RM = KC * NTL >= 28 ? 4 : 8, R = NA < RM ? NA : RM;
         const __amdgpu_buffer_rsrc_t r = buf_rsrc(src, (uint32_t)(hxs * 2));
         Raw8<bf16> fa[R];
 #pragma unroll
@@ -347,15 +387,18 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
                     make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
         }
         lds_barrier();
-    };
-    auto red_sum = [&](int i) {
-        float4 v = red[i];
-#pragma unroll
-        for (int k = 1; k < NW; ++k) {
-            const float4 x = red[k * NF * RF_FP + i];
-            v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+        if (__builtin_expect(spoilt, 0)) {
+            const int th = opaque_tid();
+#pragma unroll 1
+            for (int q = 0; q < PPT; ++q) {
+                const Pair r = pair_of(q, th);
+                if (!r.ok) continue;
+                const float4 v = red_sum(r.i);
+                if (v.x == v.x && v.y == v.y && v.z == v.z && v.w == v.w) continue;
+                red[r.i] = kept_sum(src, (const bf16*)D.U, mask, r.b, r.u, H);
+                for (int k = 1; k < NW; ++k) red[k * NF * RF_FP + r.i] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
         }
-        return v;
     };
     const uint32_t gxbytes = (uint32_t)((size_t)B * G * 4);
 
@@ -371,7 +414,7 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
         for (int s = 0; s < T_; ++s) {
             const int t = step_t(s);
             if (!res_wait(a.bar, gdep, a.ntiles, (unsigned)(s + 2), -1, 0, 0, a.err, a.timeout, STATUS_FWD)) break;
-            product((const bf16*)D.xin + (size_t)t * hxs);
+            product((const bf16*)D.xin + (size_t)t * hxs, a.d[D.dep].umask + (size_t)t * a.kmax);
             const __amdgpu_buffer_rsrc_t gr = buf_rsrc(D.gxp + (size_t)t * B * G, gxbytes);
             const int th = opaque_tid();
 #pragma unroll
@@ -453,7 +496,7 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
                 gxr[q][0] = v.x; gxr[q][1] = v.y; gxr[q][2] = v.z; gxr[q][3] = v.w;
             }
         }
-        product((const bf16*)D.hx + (size_t)(s & 1) * hxs);
+        product((const bf16*)D.hx + (size_t)(s & 1) * hxs, D.rmask + (size_t)t * a.kmax);
         bf16* hxn = (bf16*)D.hx + (size_t)((s + 1) & 1) * hxs;
         float og4[PPT][4], cnv[PPT], hnv[PPT];
         const int th = opaque_tid();
