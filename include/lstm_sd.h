@@ -137,7 +137,9 @@ typedef struct {
 int         lstm_sd_version(void);
 const char* lstm_sd_last_error(void);
 
-/* Size queries; return 0 (and set the error) for invalid dims. */
+/* Size queries; return 0 (and set the error) for invalid dims.  Sizes depend on
+ * the shape and the dtype alone: one set of buffers serves any dropout rates
+ * and both modes. */
 size_t lstm_sd_mask_bytes(const lstm_sd_dims* dims);
 size_t lstm_sd_reserve_bytes(const lstm_sd_dims* dims);
 size_t lstm_sd_workspace_bytes(const lstm_sd_dims* dims);

@@ -94,7 +94,8 @@ static float inv_keep(double p) { return p > 0.0 ? (float)(1.0 / (1.0 - p)) : 1.
 // products over rows fill the chip with 256 x 256 tiles (64 steps x batch 256 x hidden
 // 1024, p = 0.5: 349 against 368 us the products, 289 against 349 the gradients); the
 // dense mode skips nothing.
-static bool skip_pays(const Plan& P, int l) { return P.B >= 256 && P.compact && P.p_nr[l] > 0.0f; }
+constexpr int SKIP_MIN_B = 256;
+static bool skip_pays(const Plan& P, int l) { return P.B >= SKIP_MIN_B && P.compact && P.p_nr[l] > 0.0f; }
 static bool fx_rows(const Plan& P, int l) {
     const long tiles = (long)((P.T * P.B + 255) / 256) * ((P.G + 255) / 256) * P.D;
     return P.dtype == LSTM_SD_DTYPE_BF16 && !(skip_pays(P, l) && (P.p_nr[l] > 0.5f || tiles < 1024));
@@ -172,8 +173,9 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     q.r_gates = off; off = align_up(off + T * B * G * 4, A);
     q.r_c = off;     off = align_up(off + T * B * H * 4, A);
     const bool b16 = es == 2;
-    bool xt = !b16;                           // (bf16: transposed inputs feed the per-step products only)
-    for (int l = 0; l < q.L; ++l) xt = xt || !fx_rows(q, l);
+    // (bf16: transposed inputs feed the per-step products only, whose batches are large;
+    // sized by the shape alone, so that one buffer serves every rate and both modes)
+    const bool xt = !b16 || q.B >= SKIP_MIN_B;
     q.r_hrecT = off; off = align_up(off + (b16 ? T * B * (size_t)q.HP : T * H * BP) * es, A);
     q.r_dir_bytes = off;
     off = (size_t)q.L * D * q.r_dir_bytes;

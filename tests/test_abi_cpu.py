@@ -93,6 +93,18 @@ def test_null_pointers_and_small_buffers_rejected():
     assert lib.lstm_sd_mask_layout_get(ctypes.byref(d), None) == B.EINVAL
 
 
+@pytest.mark.parametrize("batch", [20, 255, 256, 300])
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_sizes_do_not_depend_on_rates_or_mode(batch, dtype):
+    """One set of buffers serves a schedule of dropout rates, evaluation and the dense mode."""
+    sizes = set()
+    for compact in (1, 0):
+        for p_nr, p_rh in ((0.0, 0.0), (0.3, 0.0), (0.5, 0.5), (0.65, 0.3), (0.9, 0.9)):
+            d = dims(input_dim=140, hidden=1024, batch=batch, seq_len=64, dtype=dtype, compact=compact, p_nr=p_nr, p_rh=p_rh)
+            sizes.add((B.lstm_sd_mask_bytes(d), B.lstm_sd_reserve_bytes(d), B.lstm_sd_workspace_bytes(d)))
+    assert len(sizes) == 1, sizes
+
+
 def test_forward_rejects_small_reserve_before_device_work():
     lib = B.load()
     d = dims(num_layers=1, input_dim=8, hidden=8, batch=2, seq_len=3)
