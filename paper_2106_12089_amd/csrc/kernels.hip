@@ -1817,7 +1817,7 @@ int kernel_timer_stop(double* total_ms, int64_t* launches) {
 template <typename... KArgs, typename... Args>
 static void launch_k(int kid, void (*kernel)(KArgs...), dim3 grid, dim3 block, size_t shm, hipStream_t st,
                      Args... args) {
-    if (g_timer_kid == kid) {
+    if (kid != KID_NONE && g_timer_kid == kid) {
         hipEvent_t e0 = timer_event(), e1 = timer_event();
         if (e0 && e1) {
             hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)shm, st, e0, e1, 0, args...);

@@ -2,7 +2,10 @@
 workspace, for callers that cannot allocate) against lstm_sd_forward with a
 caller workspace: the same outputs and the same reserve, on two calls in a
 row, the second on a smaller problem (the static workspace then holds the
-first call's values), and a backward fed by the static call's reserve."""
+first call's values), and a backward fed by the static call's reserve; and steps without
+host memory that grows from call to call."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -57,10 +60,41 @@ def test_static_forward_rejects_oversized_dims():
     d = B_.make_dims(cfg.num_layers, cfg.input_dim, cfg.hidden, cfg.batch, cfg.seq_len, cfg.num_dirs)
     assert B_.lstm_sd_workspace_bytes(d) > B_.STATIC_WORKSPACE_MAX
     lib = B_.load()
-    import ctypes
     fake = 4096   # never dereferenced: the size check fails first
     arr = (ctypes.c_void_p * 2)(fake, fake)
     w = B_.lstm_sd_weights(arr, arr, arr)
     rc = lib.lstm_sd_forward_static(ctypes.byref(d), ctypes.byref(w), *([fake] * 5), 1 << 40, fake, fake, fake,
                                     fake, 1 << 40, None)
     assert rc == B_.EUNSUPPORTED and "STATIC_WORKSPACE_MAX" in B_.lstm_sd_last_error()
+
+
+class _MallInfo(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_size_t) for n in ("arena", "ordblks", "smblks", "hblks", "hblkhd", "usmblks", "fsmblks",
+                                               "uordblks", "fordblks", "keepcost")]
+
+
+def test_steps_hold_no_more_memory_than_the_first():
+    """Calls outside a kernel timer create no events: 3000 steps leave the host heap in use
+    as it was."""
+    import dataclasses
+    from paper_2106_12089_amd.session import Session
+    cfg = dataclasses.replace(workloads.get_config("tiny"), name="alloc", dtype="bf16", loss="mse")
+    say("[gpu] host heap over 3000 steps")
+    s = Session(workloads.make_workload(cfg), 0.5, 0.5, 1)
+    info = ctypes.CDLL(None).mallinfo2
+    info.restype = _MallInfo
+
+    def run(n):
+        for i in range(n):
+            s.step(cfg.mask_seed, i)
+            if i % 50 == 0:
+                torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        m = info()
+        return m.uordblks + m.hblkhd
+
+    run(500)
+    before = run(100)
+    grown = run(3000) - before
+    say("   grown", grown)
+    assert grown < 200_000, grown   # (a pair of events to every launch without a name: 8 KB a step)
