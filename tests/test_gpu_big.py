@@ -1,13 +1,10 @@
-"""The large-batch kernels (the persistent forward with its U slice held in
-registers, the contraction split over the waves and summed through LDS; the
-input products, input gradients and weight gradients on 256-row tiles) on
-ragged shapes,
-forced with LSTM_SD_BIG=2 (it otherwise runs only where the row-group
-tiling of the other persistent forward does not fit, as at the stress
-shape): hidden sizes that are not multiples of the 32-neuron chunk or of the
-16-unit tile, batches that are not multiples of the 64-row group or of the
-16-row MFMA tile, both directions, per-row lengths, and both modes; the
-weight gradients on the default GEMM and on the row-sparse kernel."""
+"""Whole bf16 steps of large and ragged batches against the oracle: hidden sizes that are
+not multiples of the 32-neuron chunk or of the 16-unit tile, batches that are not
+multiples of a row group or of the 16-row MFMA tile, more row groups than one launch
+takes, 256 rows and more (input products and gradients over the kept neurons of a step),
+both directions, per-row lengths, and both modes; with the recurrences persistent and
+with the per-step kernels, which run where a recurrence does not fit the device; and the
+same bits from every repeat."""
 import dataclasses
 
 import numpy as np
@@ -43,13 +40,12 @@ def _run(cfg, wl, p_nr, p_rh, compact):
     dict(num_layers=1, num_dirs=2, input_dim=48, hidden=40, batch=1030, seq_len=3),
 ])
 @pytest.mark.parametrize("mode", [(0.5, 0.5, 1), (0.5, 0.5, 0), (0.3, 0.0, 1)])
-def test_big_forward_ragged(shape, mode, monkeypatch):
-    monkeypatch.setenv("LSTM_SD_BIG", "2")
+def test_big_ragged(shape, mode):
     base = workloads.get_config("tiny")
     cfg = dataclasses.replace(base, name="big", dtype="bf16", loss="mse", **shape)
     wl = workloads.make_workload(cfg)
     p_nr, p_rh, compact = mode
-    say(f"[gpu] big forward {shape} p_nr={p_nr} p_rh={p_rh} compact={compact}")
+    say(f"[gpu] big {shape} p_nr={p_nr} p_rh={p_rh} compact={compact}")
     gpu, ref = _run(cfg, wl, p_nr, p_rh, compact)
     errs = compare(gpu, ref)
     say("   errs", summary(errs))
@@ -65,17 +61,14 @@ def test_big_forward_ragged(shape, mode, monkeypatch):
     dict(num_layers=2, num_dirs=2, input_dim=200, hidden=72, batch=300, seq_len=3),
 ])
 @pytest.mark.parametrize("mode", [(0.5, 0.5, 1), (0.5, 0.5, 0)])
-def test_big_wgrad_rowsparse_kernel(shape, mode, monkeypatch):
-    """The large-batch row-sparse weight-gradient kernel (per-step gathered
-    rows; LSTM_SD_WGRAD_GEMM=0) in place of the default mask-multiplied
-    GEMM."""
-    monkeypatch.setenv("LSTM_SD_BIG", "2")
-    monkeypatch.setenv("LSTM_SD_WGRAD_GEMM", "0")
+def test_big_per_step_kernels(shape, mode, monkeypatch):
+    """The recurrences as one launch per step (LSTM_SD_PERSIST=0)."""
+    monkeypatch.setenv("LSTM_SD_PERSIST", "0")
     base = workloads.get_config("tiny")
     cfg = dataclasses.replace(base, name="big", dtype="bf16", loss="mse", **shape)
     wl = workloads.make_workload(cfg)
     p_nr, p_rh, compact = mode
-    say(f"[gpu] big row-sparse wgrad {shape} p_nr={p_nr} p_rh={p_rh} compact={compact}")
+    say(f"[gpu] big per step {shape} p_nr={p_nr} p_rh={p_rh} compact={compact}")
     gpu, ref = _run(cfg, wl, p_nr, p_rh, compact)
     errs = compare(gpu, ref)
     say("   errs", summary(errs))
@@ -84,14 +77,11 @@ def test_big_wgrad_rowsparse_kernel(shape, mode, monkeypatch):
 
 
 @pytest.mark.parametrize("mode", [(0.3, 0.0, 1), (0.5, 0.5, 1), (0.5, 0.5, 0)])
-def test_big_repeats_bit_identical(mode, monkeypatch):
+def test_big_repeats_bit_identical(mode):
     """The same step on the same masks gives the same bits every time: the
-    large-batch kernels' exchanges and the weight gradient's accumulator
-    (whose rows move between waves from step to step) leave no room for a
-    race.  A hidden size around the 32-row tile boundary at keep rate 0.7
-    puts rows in both tiles."""
+    exchanges of the recurrences and the products' accumulation orders leave
+    no room for a race."""
     from paper_2106_12089_amd.session import Session
-    monkeypatch.setenv("LSTM_SD_BIG", "2")
     base = workloads.get_config("tiny")
     cfg = dataclasses.replace(base, name="big", dtype="bf16", loss="mse", num_layers=2, num_dirs=1, input_dim=70,
                               hidden=45, batch=70, seq_len=5)

@@ -3,10 +3,10 @@ zero barrier time-out every grid-barrier wait gives up at once, so every
 workgroup leaves through the time-out path (no kernel spins or faults).  The
 step must then report the failure through lstm_sd_status, write NaN into
 every output it names, and a clean step on the same buffers afterwards must
-match the oracle again.  The seq2seq encoder (batch 64) takes the large-batch
-input products and gradients and the GEMM weight gradient; the stress shape
-(batch 256) the large-batch recurrences, whose clean step after the failure
-is checked bit for bit against a fresh session's."""
+match the oracle again.  Stacks in one launch (batch 20, 64), one bidirectional
+layer, and the stress shape (batch 256, a launch per layer), whose clean step
+after the failure is checked bit for bit against a fresh session's; and passes
+of several launches of which one fails."""
 import numpy as np
 import pytest
 

@@ -1,15 +1,8 @@
-"""The weight-gradient kernels with LDS-staged operands (bf16, batch up to
-32: the row-sparse scatter for slices of up to about 96 rows, the full
-kernel for identity keep lists, the dense mode and row-sparse problems
-whose kept fraction is high; the default wherever they apply) on ragged
-shapes: weight heights whose slices are 1, 16-17 or 95 rows, gate
-widths that end inside a 128-column block, batches below the 32-entry
-chunk (27: the last 8-entry piece of a row partly valid, 17 and 20: past
-the batch and never loaded), sequences shorter than its two-step lookahead, both directions, and
-rates that leave steps with no kept row (an 8-wide input at p = 0.9).  Each
-case runs a whole step against the oracle, with each row-sparse problem
-on either kernel (LSTM_SD_WGRAD_ROWSPARSE=1, 0) and on the unstaged ones
-(LSTM_SD_WGRAD_STAGED=0) as further checks, and repeats are bit-identical."""
+"""Whole bf16 steps against the oracle at shapes where the weight gradients can go wrong:
+weight heights and gate widths that end inside a tile, batches that do not divide a
+32-row chunk of (step, row) pairs (27, 17 and 20), single steps, both directions, a batch
+of 48, and rates that leave steps with no kept row (an 8-wide input at p = 0.9).  Rows of
+never-kept neurons are exact zeros, and repeats are bit-identical."""
 import dataclasses
 
 import numpy as np
@@ -58,13 +51,13 @@ CASES = [(sh, m + (1,)) for sh in SHAPES for m in [(0.5, 0.5), (0.9, 0.5), (0.3,
 
 
 @pytest.mark.parametrize("shape,mode", CASES)
-def test_wgrad_staged_ragged(shape, mode, monkeypatch):
+def test_wgrad_ragged(shape, mode):
     from oracle import masks as om
     base = workloads.get_config("tiny")
     cfg = dataclasses.replace(base, name="wgs", dtype="bf16", loss="mse", **shape)
     wl = workloads.make_workload(cfg)
     p_nr, p_rh, compact = mode
-    say(f"[gpu] staged wgrad {shape} p_nr={p_nr} p_rh={p_rh} compact={compact}")
+    say(f"[gpu] wgrad {shape} p_nr={p_nr} p_rh={p_rh} compact={compact}")
     gpu = _gpu(cfg, wl, p_nr, p_rh, compact)
     m_nr, m_rh = om.all_masks(cfg.mask_seed, 0, cfg.num_layers, cfg.num_dirs, cfg.seq_len, cfg.k_in,
                               cfg.hidden, p_nr, p_rh)
@@ -81,27 +74,13 @@ def test_wgrad_staged_ragged(shape, mode, monkeypatch):
             assert np.all(gpu["dW"][k][never] == 0.0)
             never_h = ~m_rh[l][d].any(axis=0)
             assert np.all(gpu["dU"][k][never_h] == 0.0)
-    # both kinds of kernel for the row-sparse problems, then the unstaged
-    # kernels, agree to the same bound
-    if compact:
-        for rs in ("1", "0"):
-            monkeypatch.setenv("LSTM_SD_WGRAD_ROWSPARSE", rs)
-            e = compare(_gpu(cfg, wl, p_nr, p_rh, compact), ref)
-            bad = {k: v for k, v in e.items() if not v <= TOL["bf16"]}
-            assert not bad, (rs, bad)
-        monkeypatch.delenv("LSTM_SD_WGRAD_ROWSPARSE")
-    monkeypatch.setenv("LSTM_SD_WGRAD_STAGED", "0")
-    other = _gpu(cfg, wl, p_nr, p_rh, compact)
-    errs2 = compare(other, ref)
-    bad2 = {k: v for k, v in errs2.items() if not v <= TOL["bf16"]}
-    assert not bad2, bad2
 
 
-def test_wgrad_staged_repeats_bit_identical():
+def test_wgrad_repeats_bit_identical():
     base = workloads.get_config("tiny")
     cfg = dataclasses.replace(base, name="wgs", dtype="bf16", loss="mse", **SHAPES[2])
     wl = workloads.make_workload(cfg)
-    say("[gpu] staged wgrad repeats")
+    say("[gpu] wgrad repeats")
     ref = None
     for it in range(4):
         cur = _flat(_gpu(cfg, wl, 0.5, 0.5))
@@ -114,12 +93,10 @@ def test_wgrad_staged_repeats_bit_identical():
 
 @pytest.mark.parametrize("mode", [(0.5, 0.5, 1), (0.5, 0.5, 0), (0.3, 0.0, 1)])
 @pytest.mark.parametrize("hidden", [60, 33])
-def test_wgrad_batch_above_32_both_kernels(mode, hidden, monkeypatch):
-    """A batch of 48 (bf16): the default mask-multiplied GEMM, and with
-    LSTM_SD_WGRAD_GEMM=0 the unstaged kernels (the row-sparse scatter and the
-    full kernel, two 32-row batch chunks); 4H = 240 or 132 gradient columns
-    (the last 16-column tile ragged: the bias gradient's columns past 4H are
-    not written)."""
+def test_wgrad_batch_above_32(mode, hidden):
+    """A batch of 48: a chunk of 32 rows in one step and over two; 4H = 240 or 132
+    gradient columns (the last 16-column tile ragged: the bias gradient's columns past
+    4H are not written)."""
     from oracle import masks as om
     base = workloads.get_config("tiny")
     cfg = dataclasses.replace(base, name="wgs", dtype="bf16", loss="mse", num_layers=2, num_dirs=1,
@@ -129,10 +106,8 @@ def test_wgrad_batch_above_32_both_kernels(mode, hidden, monkeypatch):
     m_nr, m_rh = om.all_masks(cfg.mask_seed, 0, cfg.num_layers, cfg.num_dirs, cfg.seq_len, cfg.k_in,
                               cfg.hidden, p_nr, p_rh)
     ref = oracle_step(wl, p_nr, p_rh, m_nr, m_rh)
-    for gemm in ("1", "0"):
-        monkeypatch.setenv("LSTM_SD_WGRAD_GEMM", gemm)
-        say(f"[gpu] batch 48 weight gradient gemm={gemm} p_nr={p_nr} p_rh={p_rh} compact={compact}")
-        errs = compare(_gpu(cfg, wl, p_nr, p_rh, compact), ref)
-        say("   errs", summary(errs))
-        bad = {k: v for k, v in errs.items() if not v <= TOL["bf16"]}
-        assert not bad, (gemm, bad)
+    say(f"[gpu] batch 48 weight gradient p_nr={p_nr} p_rh={p_rh} compact={compact}")
+    errs = compare(_gpu(cfg, wl, p_nr, p_rh, compact), ref)
+    say("   errs", summary(errs))
+    bad = {k: v for k, v in errs.items() if not v <= TOL["bf16"]}
+    assert not bad, bad
