@@ -61,19 +61,6 @@ double bwd_res_cost(int B, int H, int nslots);
 int kernel_timer_start(const char* name);
 int kernel_timer_stop(double* total_ms, int64_t* launches);
 
-// the persistent kernels of the fp32 path (bf16 runs with register-resident
-// weights, or per step where those do not fit the device)
-template <typename E>
-static hipError_t fwd_persist(PFwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1) {
-    if constexpr (std::is_same<E, float>::value) return launch_fwd_persist<float>(a, st, timer_on, e0, e1);
-    else return hipErrorInvalidValue;
-}
-template <typename E>
-static hipError_t bwd_persist(PBwdArgs& a, hipStream_t st, int timer_on, hipEvent_t e0, hipEvent_t e1) {
-    if constexpr (std::is_same<E, float>::value) return launch_bwd_persist<float>(a, st, timer_on, e0, e1);
-    else return hipErrorInvalidValue;
-}
-
 static thread_local std::string g_err;
 
 static int fail(int code, const std::string& msg) {
@@ -358,7 +345,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
     memset(&tr, 0, sizeof(tr));
     tr.src = x; tr.dst = R + P.r_xT; tr.B = B; tr.K = P.I; tr.BP = BP; tr.n1 = T;
     tr.src2 = h0; tr.dst2 = R + P.r_h0T; tr.K2 = H;
-    const bool b16 = std::is_same<E, bf16>::value;
+    constexpr bool b16 = std::is_same<E, bf16>::value;
     if (b16) {
         if (fx_rows(P, 0)) tr.dst = nullptr;
         tr.dst2 = nullptr;
@@ -499,13 +486,12 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
         }
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool timed = timer_pair(KID_FWDP_, &e0, &e1);
-        if (fwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) return true;
+        if (launch_fwd_persist<float>(pa, st, timed, e0, e1) == hipSuccess) return true;
         (void)hipGetLastError();              // does not fit
         if (timed) timer_unpair();
         return false;
     };
-    // The recurrences with register-resident weights (bf16, hidden size up to
-    // 1536): layers l0 .. l0+nl-1, a stack's with a worker slot between layers.
+    // The recurrences with register-resident weights (bf16): layers l0 .. l0+nl-1, a stack's with a worker slot between layers.
     auto res_launch = [&](int l0, int nl) -> bool {
         RFwdArgs ra;
         memset(&ra, 0, sizeof(ra));
@@ -564,7 +550,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
         return false;
     };
     bool fx0_done = false;
-    const bool res = std::is_same<E, bf16>::value && use_persistent() && fwd_res_cost(B, H, D) > 0.0;
+    const bool res = b16 && use_persistent() && fwd_res_cost(B, H, D) > 0.0;
     if (res && use_stacked() && D == 1 && L > 1 && L <= 4) {
         const double cs = fwd_res_cost(B, H, 2 * L - 1), c1 = fwd_res_cost(B, H, 1);
         if (cs > 0.0 && res_stack_pays(P, cs, c1)) {
@@ -573,7 +559,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
             fx0_done = true;
         }
     }
-    if (!std::is_same<E, bf16>::value && use_persistent() && use_stacked() && D == 1 && L > 1 && L <= 4) {
+    if (!b16 && use_persistent() && use_stacked() && D == 1 && L > 1 && L <= 4) {
         launch_fx_layer(0);
         if ((use_fwd_workers() && stacked(true)) || stacked(false)) return hip_check("forward launch");
         fx0_done = true;                      // neither fits: one layer at a time below
@@ -581,7 +567,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
     for (int l = 0; l < L; ++l) {
         if (!(l == 0 && fx0_done)) launch_fx_layer(l);
         if (res && res_launch(l, 1)) continue;
-        if (use_persistent()) {
+        if (!b16 && use_persistent()) {
             PFwdArgs pa;
             common_args(pa);
             pa.nslots = D;
@@ -591,7 +577,7 @@ static int forward_impl(const Plan& P, const lstm_sd_weights* w, const void* x, 
             }
             hipEvent_t e0 = nullptr, e1 = nullptr;
             const bool timed = timer_pair(KID_FWDP_, &e0, &e1);
-            if (fwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) continue;
+            if (launch_fwd_persist<float>(pa, st, timed, e0, e1) == hipSuccess) continue;
             (void)hipGetLastError();          // does not fit: per step
             if (timed) timer_unpair();
         }
@@ -699,7 +685,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
     // The recurrences with register-resident weights, as in the forward:
     // layers l1 down to l0 (a stack's with a worker slot between layers).  An
     // inner layer that starts a launch reads its input gradient full width.
-    bool res = std::is_same<E, bf16>::value && use_persistent() && bwd_res_cost(B, H, D) > 0.0;
+    bool res = b16 && use_persistent() && bwd_res_cost(B, H, D) > 0.0;
     auto res_launch = [&](int l1, int l0, const float* dy_above, int lddy) -> bool {
         RBwdArgs ra;
         memset(&ra, 0, sizeof(ra));
@@ -868,7 +854,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
             }
         }
     }
-    if (!std::is_same<E, bf16>::value && use_persistent() && use_stacked() && D == 1 && L > 1 && 2 * L - 1 <= 8) {
+    if (!b16 && use_persistent() && use_stacked() && D == 1 && L > 1 && 2 * L - 1 <= 8) {
         launch_bwd_init(nullptr, nullptr, nullptr, nullptr, 0, W + P.w_da, (int)es, G, P.mtiles, (long)L * T,
                         (long)P.das, sync_bar, sync_err, st);
         PBwdArgs pa;
@@ -897,7 +883,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
         }
         hipEvent_t e0 = nullptr, e1 = nullptr;
         const bool timed = timer_pair(KID_BWDP_, &e0, &e1);
-        if (bwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) {
+        if (launch_bwd_persist<float>(pa, st, timed, e0, e1) == hipSuccess) {
             if (dx) layer_dx(0, 0, (float*)(W + P.w_dxc));
             for (int l = L - 1; l >= 0; --l) layer_wgrad(l, l);
             flush_wgrad();
@@ -926,7 +912,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
                 res = false;                  // (decided at the first layer, for all of them)
             }
         }
-        if (use_persistent() && !persistent_done) {
+        if (!b16 && use_persistent()) {
             PBwdArgs pa;
             common_args(pa);
             pa.nslots = D;
@@ -941,7 +927,7 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
             }
             hipEvent_t e0 = nullptr, e1 = nullptr;
             const bool timed = timer_pair(KID_BWDP_, &e0, &e1);
-            if (bwd_persist<E>(pa, st, timed, e0, e1) == hipSuccess) {
+            if (launch_bwd_persist<float>(pa, st, timed, e0, e1) == hipSuccess) {
                 persistent_done = true;
             } else {
                 (void)hipGetLastError();      // does not fit: per step

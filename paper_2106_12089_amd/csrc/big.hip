@@ -579,7 +579,7 @@ void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 // while W is staged contraction-major for ROWS_FX and read by transposing LDS reads.
 // Two LDS buffers of KC chunks of 32 each, loads two buffers ahead of the staging, one
 // LDS-only barrier per buffer: the small tiles, a few workgroups to a CU, take the time
-// of a load and a barrier per buffer whatever its depth, so they run at KC 4.
+// of a load and a barrier per buffer whatever its depth, so they run at KC 2.
 // slices > 1 (ROWS_DX) splits the contraction over workgroups, each writing its
 // partial product; k_rows_reduce adds them in order.
 constexpr int ROWS_FX = 0, ROWS_DX = 1;

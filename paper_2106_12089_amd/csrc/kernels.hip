@@ -711,16 +711,13 @@ constexpr int WG_NB = 128;                 // gradient columns per workgroup
 constexpr int WG_CT = 2;                   // 16-column tiles per wave (each A fragment feeds WG_CT products)
 constexpr int WG_NWV = WG_NB / (16 * WG_CT); // waves per half workgroup
 constexpr int WG_LDC = WG_NB + 4;          // LDS accumulator row pitch (floats)
-template <typename T>
-struct WgTiles { static constexpr int N = 6; };   // 16-row tiles in registers at once
-template <>
-struct WgTiles<float> { static constexpr int N = 4; };
+constexpr int WG_TILES = 4;                // 16-row tiles in registers at once
 
 // Whether the two halves of a row-sparse weight-gradient workgroup split the
 // t-range (each then takes every kept row of the slice, into an accumulator
 // of its own): when one round of tiles holds the whole slice
 template <typename T>
-__host__ __device__ inline bool wgrad_tsplit(int K) { return (K + NXCD - 1) / NXCD <= 16 * (WgTiles<T>::N / 2); }
+__host__ __device__ inline bool wgrad_tsplit(int K) { return (K + NXCD - 1) / NXCD <= 16 * (WG_TILES / 2); }
 // LDS bytes of the row-sparse weight gradient for a K-row weight
 template <typename T>
 inline size_t wgrad_lds_bytes(int K) {
@@ -740,7 +737,7 @@ __device__ __forceinline__ void wg_slot(int& x, int& cb) {
 
 template <typename T, bool MULTI>
 __device__ __forceinline__ void wgrad_gather(const WgArgs& a, float* acc_lds) {
-    constexpr int MAXT = WgTiles<T>::N / 2;     // 16-row tiles of a round
+    constexpr int MAXT = WG_TILES / 2;     // 16-row tiles of a round
     constexpr int NW = Raw8<T>::NW;
     constexpr uint32_t ES = sizeof(T);
     // acc_lds: [rows of the slice + 1][WG_LDC], one per half when the halves split the t-range
@@ -1177,7 +1174,7 @@ __device__ __forceinline__ void wgrad_poison(const WgArgs& a) {
 
 // LDS of the full kernel's pass reduction
 template <typename T>
-constexpr size_t wgrad_full_lds_bytes() { return (size_t)WG_NWV * (WgTiles<T>::N / 2) * WG_CT * 4 * 64 * 4; }
+constexpr size_t wgrad_full_lds_bytes() { return (size_t)WG_NWV * (WG_TILES / 2) * WG_CT * 4 * 64 * 4; }
 
 // One launch for every weight gradient of a pass (grid z = problem): a
 // problem whose keep lists are all the identity takes the full kernel, the
@@ -1191,7 +1188,7 @@ __global__ void __launch_bounds__(128 * WG_NWV) k_wgrad(WgBatch bt) {
         wgrad_poison(a);
         return;
     }
-    if (a.full) wgrad_full<T, MASKED, WgTiles<T>::N / 2, MULTI>(a, acc_lds);
+    if (a.full) wgrad_full<T, MASKED, WG_TILES / 2, MULTI>(a, acc_lds);
     else wgrad_gather<T, MULTI>(a, acc_lds);
 }
 
@@ -2045,7 +2042,7 @@ void launch_wgrad(const WgBatch& b, hipStream_t st) {
             continue;
         }
         lds = std::max(lds, wgrad_lds_bytes<T>(p.K));
-        multi = multi || (p.K + NSEG - 1) / NSEG > 16 * (WgTiles<T>::N / 2);
+        multi = multi || (p.K + NSEG - 1) / NSEG > 16 * (WG_TILES / 2);
     }
     const dim3 blk(128 * WG_NWV);
     if (a.dense) {

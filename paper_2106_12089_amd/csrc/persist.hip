@@ -762,10 +762,7 @@ __global__ void __launch_bounds__(1024) k_bwd_persist(PBwdArgs a) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const uint32_t o = (uint32_t)frag_off(b, g * H + u, (G + 31) / 32) * (uint32_t)sizeof(T);
-                if constexpr (sizeof(T) == 2)
-                    __builtin_amdgcn_raw_buffer_store_b16(from_f32<T>(da4[q][g]), dw, o, 0, CPOL_SC1);
-                else
-                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(da4[q][g]), dw, o, 0, CPOL_SC1);
+                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(da4[q][g]), dw, o, 0, CPOL_SC1);
             }
         }
         if (final_pass) break;

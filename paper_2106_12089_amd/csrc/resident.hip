@@ -20,8 +20,8 @@
 //     its own, over its unit tiles only;
 //   - weights in registers give wide unit tiles (fewer workgroups per barrier
 //     and fewer reads of the exchanged block) and fit whole stacks on the chip
-//     whose slices exceed LDS: the layers then run as a pipeline, T + L - 1
-//     steps in place of L*T;
+//     whose slices exceed LDS: the layers then run as a pipeline, T + 2(L - 1)
+//     steps (a layer and its worker are a step apart each) in place of L*T;
 //   - a worker's product goes to the one workgroup of the layer that owns the
 //     same tile and rows, so that hand-over is a flag, not a barrier;
 //   - workgroup barriers wait for LDS only: the outputs that later kernels
@@ -875,16 +875,24 @@ static hipError_t launch_groups(void (*fn)(Args), Args& a, const Tiling& t, size
     return hipSuccess;
 }
 
-// Forward builds: (KC, NTL, MT) with KC*NTL <= 32 fragments (128 registers)
+// Forward builds: (KC, NTL, MT) with KC*NTL <= 32 fragments (128 registers), without
+// those that best_tiling prefers to no other on 256 compute units (narrow tiles of a wide
+// layer: their barriers have the most members)
+template <int KC, int N, int MT>
+constexpr bool rf_built = KC * N <= 32 && !(N == 2 && MT == 2 && KC > 2) &&
+                          !(N == 3 && (KC == 7 || (MT == 2 && (KC == 5 || KC == 8))));
+template <int KC, int N, int MT>
+static void (*fwd_res_one(size_t* lds))(RFwdArgs) {
+    if constexpr (rf_built<KC, N, MT>) {
+        *lds = rf_lds_bytes<N, MT>();
+        return k_fwd_res<KC, N, MT>;
+    }
+    return nullptr;
+}
 template <int KC>
 static void (*fwd_res_fn(int ntl, int mt, size_t* lds))(RFwdArgs) {
-#define LSD_F(N)                                                   \
-    if constexpr (KC * N <= 32) {                                  \
-        if (ntl == N) {                                            \
-            *lds = mt == 1 ? rf_lds_bytes<N, 1>() : rf_lds_bytes<N, 2>(); \
-            return mt == 1 ? k_fwd_res<KC, N, 1> : k_fwd_res<KC, N, 2>; \
-        }                                                          \
-    }
+#define LSD_F(N) \
+    if (ntl == N) return mt == 1 ? fwd_res_one<KC, N, 1>(lds) : fwd_res_one<KC, N, 2>(lds);
     LSD_F(2) LSD_F(3) LSD_F(4) LSD_F(5) LSD_F(6) LSD_F(8)
 #undef LSD_F
     return nullptr;
@@ -926,25 +934,29 @@ hipError_t launch_fwd_res(RFwdArgs& a, hipStream_t st, int timer_on, hipEvent_t 
 
 // Backward builds: KB chunks per wave (KL of them in LDS for 1 / 2 unit tiles), and
 // the chunks of loads in flight for (unit tiles, row tiles) = (1, 1), (1, 2), (2, 1),
-// (2, 2): as many as the registers hold, for an exchanged line from another XCD is
-// a microsecond away
+// (2, 2) (0: no such build): as many as the registers hold, for an exchanged line from
+// another XCD is a microsecond away.  Without those that best_tiling prefers to no other
+// on 256 compute units (two unit tiles of a narrow layer, two row tiles at 20 chunks)
 template <int KB, int KL1, int KL2, int R11, int R12, int R21, int R22>
 static void (*bwd_res_fn(int nb, int mt, int* kl, int* r))(RBwdArgs) {
     *kl = nb == 1 ? KL1 : KL2;
     *r = nb == 1 ? (mt == 1 ? R11 : R12) : (mt == 1 ? R21 : R22);
-    if (nb == 1) return mt == 1 ? k_bwd_res<KB, KL1, 1, 1, R11> : k_bwd_res<KB, KL1, 1, 2, R12>;
-    if constexpr (KB <= 24) return mt == 1 ? k_bwd_res<KB, KL2, 2, 1, R21> : k_bwd_res<KB, KL2, 2, 2, R22>;
+    if (nb == 1 && mt == 1) return k_bwd_res<KB, KL1, 1, 1, R11>;
+    if constexpr (R12 > 0)
+        if (nb == 1) return k_bwd_res<KB, KL1, 1, 2, R12>;
+    if constexpr (R21 > 0)
+        if (nb == 2) return mt == 1 ? k_bwd_res<KB, KL2, 2, 1, R21> : k_bwd_res<KB, KL2, 2, 2, R22>;
     return nullptr;
 }
 static void (*bwd_res_pick(int kb, int nb, int mt, int* kl, int* r))(RBwdArgs) {
-    if (kb <= 2) return bwd_res_fn<2, 0, 0, 2, 2, 2, 2>(nb, mt, kl, r);
+    if (kb <= 2) return bwd_res_fn<2, 0, 0, 2, 2, 0, 0>(nb, mt, kl, r);
     if (kb <= 4) return bwd_res_fn<4, 0, 0, 4, 4, 4, 4>(nb, mt, kl, r);
     if (kb <= 8) return bwd_res_fn<8, 0, 0, 8, 8, 8, 8>(nb, mt, kl, r);
     if (kb <= 11) return bwd_res_fn<11, 0, 0, 11, 11, 11, 8>(nb, mt, kl, r);
     if (kb <= 16) return bwd_res_fn<16, 0, 0, 16, 12, 16, 5>(nb, mt, kl, r);
-    if (kb <= 20) return bwd_res_fn<20, 0, 6, 20, 10, 16, 6>(nb, mt, kl, r);
+    if (kb <= 20) return bwd_res_fn<20, 0, 6, 20, 0, 16, 6>(nb, mt, kl, r);
     if (kb <= 24) return bwd_res_fn<24, 0, 6, 24, 8, 8, 4>(nb, mt, kl, r);
-    if (kb <= 32) return bwd_res_fn<32, 0, 0, 20, 6, 4, 4>(nb, mt, kl, r);
+    if (kb <= 32) return bwd_res_fn<32, 0, 0, 20, 6, 0, 0>(nb, mt, kl, r);
     return nullptr;
 }
 static Tiling bwd_res_tiling(int B, int H, int nslots) {
