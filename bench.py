@@ -8,7 +8,9 @@ language-model shape (batch 20, 35 steps, bf16 storage with fp32
 accumulation, structured dropout p = 0.5 on the non-recurrent inputs).
 Every other workload (LM-large, the Luong encoder, the BiLSTM tagger, the
 2-layer 1024-unit batch-256 stress shape, the AWD-LSTM shape) is measured in
-the same run under "configs".  Prints one JSON line.
+the same run under "configs".  Prints one JSON line, with a summary of the
+other workloads and without the tables of every kernel; --full FILE writes the
+whole record.
 
   value      effective TFLOP/s: algorithmic FLOPs of the step (products over
              the rows actually kept, three products per gate GEMM) / step time
@@ -51,6 +53,23 @@ PHASES = {"mask": ("mask_build",), "fp_x": ("fx",), "fp_rec": ("fwd_persist", "s
 CONFIG_RUNS = ("lm_large", "seq2seq_enc", "tagger", "stress", "awd_lstm")
 KERNEL_SRC_DIR = os.path.join(ROOT, "paper_2106_12089_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
+
+
+def short_record(out):
+    """The record as it is printed, in some KB (the whole one takes 30, more than logs
+    keep of a line): no tables of every kernel, the other workloads by their times,
+    rates and dominant kernel."""
+    tables = ("kernels", "phases_ms_dense", "phase_speedup")
+    short = {k: v for k, v in out.items() if k not in tables + ("configs",)}
+    if "nrrh" in out:
+        short["nrrh"] = {k: v for k, v in out["nrrh"].items() if k not in tables}
+    mode = ("ms_per_step", "tflops", "dense_ms_per_step", "speedup_vs_dense")
+    for name, c in out.get("configs", {}).items():
+        d = {m: {k: c[m][k] for k in mode if k in c[m]} for m in ("nr_st", "nr_rh_st") if c.get(m)}
+        if c.get("roofline"):
+            d["roofline"] = {k: c["roofline"].get(k) for k in ("kernel", "bound", "frac", "launch_avg_us")}
+        short.setdefault("configs", {})[name] = d
+    return short
 
 
 def kernel_src_hash():
@@ -750,6 +769,7 @@ def main(argv=None):
     ap.add_argument("--no-sweep", action="store_true", help="skip the p sweep of the tagger and stress workloads")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MIB",
                     help="also run a plain device copy of this many MiB (counter calibration)")
+    ap.add_argument("--full", metavar="FILE", help="write the whole record (per-kernel tables, every mode) as JSON")
     ap.add_argument("--summarize-counters", nargs=2, metavar=("FETCH_CSV", "WRITE_CSV"),
                     help="write profiles/traffic.json from two rocprofv3 --pmc runs and exit (no GPU)")
     ap.add_argument("--counter-command", default="", help="command recorded with the summaries")
@@ -868,7 +888,10 @@ def main(argv=None):
             print(f"[bench] config {name}", file=sys.stderr, flush=True)
             out["configs"][name] = config_block(name, args.steps, args.warmup, not args.no_cpu, args.no_dense,
                                                 not args.no_sweep)
-    print(json.dumps(out), flush=True)
+    if args.full:
+        with open(args.full, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(short_record(out)), flush=True)
     return 0
 
 

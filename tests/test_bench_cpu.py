@@ -42,3 +42,22 @@ def test_rates_per_layer():
 
 def test_one_gpu_only():
     assert bench.main(["--gpus", "2"]) == 2
+
+
+def test_printed_record_is_short_and_keeps_the_contract():
+    """The printed line fits a log's tail whatever the tables hold."""
+    import json
+    table = {f"kernel{i}": {"ms_per_step": 0.1234, "launches_per_step": 1.0, "avg_us": 123.456} for i in range(60)}
+    mode = dict(ms_per_step=0.3, tflops=64.0, dense_ms_per_step=0.3, speedup_vs_dense=1.0, kernels=table,
+                phases_ms=table, phases_ms_dense=table, phase_speedup=table)
+    roof = dict(kernel="bwd_persist", bound="hbm", frac=0.1, launch_avg_us=1.0, formula="x" * 400)
+    contract = dict(metric="m", value=1.0, unit="TFLOP/s", n_gpus=1, steps=20, warmup=5, ms_per_step=0.3,
+                    higher_is_better=True, scaling="weak", vs_baseline=None, dtype="bf16", data="synthetic", config={},
+                    roofline={"kernel": "bwd_persist"}, cpu_baseline={"value": 1.0})
+    out = dict(contract, kernels=table, phases_ms_dense=table, phase_speedup=table,
+               nrrh={k: v for k, v in mode.items() if k != "phases_ms"},
+               configs={n: dict(nr_st=mode, nr_rh_st=mode, roofline=roof, p_sweep=table) for n in bench.CONFIG_RUNS})
+    short = bench.short_record(out)
+    assert {k: short[k] for k in contract} == contract
+    assert len(json.dumps(short)) < 4000
+    assert short["configs"]["stress"]["nr_rh_st"]["ms_per_step"] == 0.3
