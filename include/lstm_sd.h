@@ -28,13 +28,18 @@
  *     layer's input (shared by both directions); the recurrent (RH) mask of
  *     (l, d) multiplies only the copy of h_prev that enters U.  The cell
  *     state is never dropped.
- *   - compact = 1 skips dropped rows/columns (the method); compact = 0 runs
- *     the same kernels over every row with the mask applied as a
- *     multiplier (the dense baseline).  Both give the same result up to
- *     floating-point summation order.  The weight gradients (bf16) are plain
- *     products over all steps of operands whose dropped columns are zeros, in
- *     both modes: on this device that is faster than the row-sparse form of
- *     Eq. 11, which fp32 uses.
+ *   - compact = 1 skips dropped rows/columns where that is the faster way (the
+ *     method); compact = 0 applies the mask as a multiplier throughout (the
+ *     dense baseline).  Both give the same result up to floating-point
+ *     summation order.  fp32 products run over the kept rows alone.  In bf16
+ *     the input products and input gradients do so at 256 batch rows and more
+ *     (above half of the neurons dropped, or where the shape is small); the
+ *     other bf16 products (smaller batches, the recurrences, the weight
+ *     gradients, the head) multiply the dropped neurons' zeros in both modes,
+ *     which on this device is faster than gathering the others.
+ *   - Weight rows of neurons that are dropped at every step do not reach the
+ *     outputs in bf16, whatever they hold (Inf, NaN): a forward product that
+ *     comes out NaN is formed again over the kept rows.
  *   - Optional per-row lengths [B] (int32, device): rows freeze h and c and
  *     output 0 from t = lengths[b] on; lengths outside [0, T] are clamped.
  *
@@ -269,9 +274,10 @@ int lstm_sd_embedding_backward(const lstm_sd_dims* dims, const int32_t* tokens, 
  * models drop the LSTM output before the FC layer (Sec. 4.1) and its
  * translation models the final encoder/decoder outputs, the projection being
  * sized by the vocabulary (Sec. 4.2).  A Case-III mask on the FC input
- * (Sec. 3.1) propagates as in Sec. 3.2 for one product: the forward product
- * reads only the kept input columns, the input gradient is written only in
- * the kept columns, and the weight gradient only in the rows kept at each t.
+ * (Sec. 3.1) propagates as in Sec. 3.2 for one product: only the kept input
+ * columns count in the forward product, the input gradient is zero in the
+ * dropped columns, and the weight gradient sums each row over the steps that
+ * keep it (fp32 gathers the kept columns; bf16 multiplies the others' zeros).
  *   z[t][b] = (s * m[t] * y[t][b]) W + c,   s = 1/(1-p_out)
  *   loss    = mean over rows that count of logsumexp(z) - z[target]
  * A row (t, b) counts when t < lengths[b] and its target is in [0, vocab)
