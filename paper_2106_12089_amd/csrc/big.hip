@@ -527,11 +527,22 @@ __global__ void __launch_bounds__(64 * WM * WN, 2) k_wgrad_rows(WrBatch bt) {
     }
 }
 
-// The tile of a pass.  256 x 256 (973 TFLOP/s at hidden 1024, batch 256, 64 steps:
-// 565 us a pass against 733 with 128 x 128) needs a long contraction to pay for its
-// one workgroup per CU and a count that fills the chip; at 22 to 44 chunks 128 x 128
-// is as fast or faster (hidden 1500: 83 against 100 us); below a workgroup of those
-// per CU, 64 x 128 (tagger 27 against 31 us).
+// Whether n tiles of 256 x 256, one to a compute unit at a time, fill at least `pct`
+// percent of the rounds they take on 256 of them.  Such a tile does the work of four of
+// 128 x 128 in two thirds to three quarters of their time, where its last round is full.
+static bool rounds_fill(long n, int pct) { return n * 100 >= pct * 256 * ((n + 255) / 256); }
+
+// The tile of a pass (us with 128 x 128 and with 256 x 256, by the share of the rounds
+// that the latter fills; contraction of 640 / 2560 / 8192 rows, 2000 to 16384 columns):
+//   0.56   51 /  65   147 / 182   425 / 536
+//   0.75   32 /  34   111 / 117   268 / 274   (2000 to 3840 rows in the middle)
+//   0.73   61 /  68   215 / 228   511 / 547   (two rounds)
+//   0.87   43 /  36   126 /  96   360 / 273
+//   1.00   45 /  38   131 /  98   373 / 283   (two rounds: 77 / 71, 217 / 188, 665 / 567)
+// and 565 against 733 at 16384 rows, hidden 1024: the line lies at 0.8.  64 x 128 below
+// one tile of 128 x 128 a compute unit: 16 against 19, 57 against 65 and 138 against 156
+// us at a quarter of one; 21 / 21, 57 / 59 and 174 / 163 at one.  WIDE builds are those
+// of 256 x 256 and 64 x 128, which are equal at 0.56 (532 and 536 us).
 void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     if (b.np == 0) return;
     auto fill = [&](int TM, int TN) {
@@ -549,14 +560,14 @@ void launch_wgrad_rows(WrBatch& b, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
         if (e0 && e1) hipExtLaunchKernelGGL(kern, grid, blk, (uint32_t)lds, st, e0, e1, 0, b);
         else kern<<<grid, blk, lds, st>>>(b);
     };
-    const int big = b.R >= 4096 ? 200 : 1 << 30, mid = 256;
+    const int mid = 256;
     if (wr_wide(b)) {
-        if (fill(256, 256) >= big) go(k_wgrad_rows<2, 4, 8, 4, true>, 512, WrShape<2, 4, 8, 4>::LDS);
+        if (rounds_fill(fill(256, 256), 50)) go(k_wgrad_rows<2, 4, 8, 4, true>, 512, WrShape<2, 4, 8, 4>::LDS);
         else {
             fill(64, 128);
             go(k_wgrad_rows<1, 4, 4, 2, true>, 256, WrShape<1, 4, 4, 2>::LDS);
         }
-    } else if (fill(256, 256) >= big) go(k_wgrad_rows<2, 4, 8, 4>, 512, WrShape<2, 4, 8, 4>::LDS);
+    } else if (rounds_fill(fill(256, 256), 80)) go(k_wgrad_rows<2, 4, 8, 4>, 512, WrShape<2, 4, 8, 4>::LDS);
     else if (fill(128, 128) >= mid) go(k_wgrad_rows<2, 2, 4, 4>, 256, WrShape<2, 2, 4, 4>::LDS);
     else {
         fill(64, 128);
@@ -853,30 +864,44 @@ static void rows_go(RowsArgs& a, int z, hipStream_t st, hipEvent_t e0, hipEvent_
 static long rows_tiles(const RowsArgs& a, int TM, int TN) {
     return (long)((a.R + TN - 1) / TN) * ((a.M + TM - 1) / TM);
 }
-// Tiles of the input products (us a pass, both layers or directions where there are
-// two).  256x256 from four a CU: 349 against 462 at 128x128 (16384 rows x 1024 x 4096,
-// two layers), 141 against 163 (3200 x 500 x 20000).  128x128 from one a CU: 35 against
-// 40 at 64x64 (700 x 1500 x 6000, two), 20 against 25 (1400 x 1150 x 4600, two).  64x64
-// below: 13.6 against 16.6 (700 x 650 x 2600, two).
+// Tiles of the input products (us at 64 x 64, 128 x 128 and 256 x 256 tiles; contraction
+// of 300, and of 1500 or 1000).
+// 128 x 128 from 160 of them on:
+//   120 tiles   9.5 / 12.7     20 / 26        200 tiles   13.6 / 14.0   33 / 27
+//   140 tiles   12 / 13        26 / 26        320 tiles   17 / 19       33 / 30
+// 256 x 256 where they fill 0.7 of their rounds:
+//   0.62 (320)  39 / 48        81 / 87        0.78 (200)  31 / 27       75 / 58
+//   0.66 (170)  25 / 27        59 / 59        0.86 (440)  52 / 52       131 / 116
+//   0.74 (380)  45 / 48       116 / 109       0.98 (500)  63 / 53       128 / 93
+// and 349 against 462 at 16384 rows x 1024 x 4096 (four full rounds, two layers).
 void launch_fx_rows(RowsArgs& a, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     a.M = a.G;
-    if (rows_tiles(a, 256, 256) * a.np >= 1024) rows_go<ROWS_FX, 2, 4, 8, 4, 1>(a, a.np, st, e0, e1);
-    else if (rows_tiles(a, 128, 128) * a.np >= 256) rows_go<ROWS_FX, 2, 2, 4, 4, 1>(a, a.np, st, e0, e1);
+    if (rounds_fill(rows_tiles(a, 256, 256) * a.np, 70)) rows_go<ROWS_FX, 2, 4, 8, 4, 1>(a, a.np, st, e0, e1);
+    else if (rows_tiles(a, 128, 128) * a.np >= 160) rows_go<ROWS_FX, 2, 2, 4, 4, 1>(a, a.np, st, e0, e1);
     else rows_go<ROWS_FX, 2, 2, 2, 2, 2>(a, a.np, st, e0, e1);
 }
-// Tiles of the input gradients.  256x256 from one a CU: 289 against 385 at 128x128
-// (16384 rows x 1024 outputs x 4096, two layers).  64x64 for contractions up to 5000:
-// 27 against 38 at 128x128 sliced (3200 x 500 x 2000), 34 against 51 (1400 x 1150 x
-// 4600).  128x128 with the contraction sliced to two workgroups a CU for the rest: 97
-// against 111 at 64x64 (700 x 1500 x 6000, two), 131 against 196 (3200 x 500 x 20000).
+// Tiles of the input gradients (us; contraction D*G of 1000 / 2600 / 4600 / 6000 / 12000
+// columns).
+// 256 x 256 where they fill 0.55 of their rounds, against 128 x 128:
+//   0.39   63 / 40    99 / 68   143 / 102   173 / 128   317 / 230
+//   0.54   66 / 57   101 / 101  146 / 153   188 / 193   321 / 353
+//   0.78   64 / 73   101 / 128  155 / 200   200 / 255   332 / 464
+// 128 x 128 from 160 of them on, against the better of 64 x 64 and slices:
+//   104    24 / 18    37 / 31    56 / 44     69 / 51    127 / 95
+//   160    24 / 25    39 / 40    57 / 68     69 / 78    132 / 124
+//   350    39 / 44    67 / 67   101 / 103   126 / 129   227 / 216
+// below that 64 x 64 for contractions up to 5000, 128 x 128 with the contraction sliced
+// to two workgroups a CU beyond (64 x 64 and slices at 20 and 80 tiles: 3000 columns 21 /
+// 27 and 34 / 41, 4600 28 / 30 and 46 / 42, 5400 33 / 31 and 54 / 46, 16000 85 / 57 and
+// 156 / 102).
 void launch_dx_rows(RowsArgs& a, size_t part_bytes, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     const long n256 = rows_tiles(a, 256, 256), n128 = rows_tiles(a, 128, 128);
     a.slices = 1;
-    if (n256 >= 208) return rows_go<ROWS_DX, 2, 4, 8, 4, 1>(a, 1, st, e0, e1);
-    if (n128 < 512 && (long)a.D * a.G <= 5000) return rows_go<ROWS_DX, 2, 2, 2, 2, 2>(a, 1, st, e0, e1);
+    if (rounds_fill(n256, 55)) return rows_go<ROWS_DX, 2, 4, 8, 4, 1>(a, 1, st, e0, e1);
+    if (n128 < 160 && (long)a.D * a.G <= 5000) return rows_go<ROWS_DX, 2, 2, 2, 2, 2>(a, 1, st, e0, e1);
     const long most = (long)std::min<size_t>(part_bytes / ((size_t)a.R * a.M * 4), 16);
     const long want = std::min(std::min((512 + n128 - 1) / n128, most), (long)a.D * ((a.G + 63) / 64) / 4);
-    if (n128 >= 256 || want < 2) return rows_go<ROWS_DX, 2, 4, 4, 2, 2>(a, 1, st, e0, e1);
+    if (n128 >= 160 || want < 2) return rows_go<ROWS_DX, 2, 4, 4, 2, 2>(a, 1, st, e0, e1);
     a.slices = (int)want;
     if (e0) (void)hipEventRecord(e0, st);
     rows_go<ROWS_DX, 2, 4, 4, 2, 2>(a, a.slices, st, nullptr, nullptr);

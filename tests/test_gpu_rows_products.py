@@ -23,7 +23,8 @@ pytestmark = pytest.mark.gpu
     (5, 13, 31, 5004),        # gradient sliced over workgroups, output rows not a multiple of 4
     (2, 70, 132, 6148),       # the same, rows a multiple of 4, two row tiles
     (33, 32, 40, 4100),       # product 128 x 128
-    (9, 127, 1999, 516),      # gradient 128 x 128
+    (9, 127, 1999, 516),      # gradient 64 x 64, 16 column tiles
+    (11, 127, 1999, 516),     # gradient 128 x 128
     (16, 128, 40, 32768),     # product 256 x 256
     (26, 255, 2045, 68),      # gradient 256 x 256
 ])
