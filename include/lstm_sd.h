@@ -32,11 +32,12 @@
  *     method); compact = 0 applies the mask as a multiplier throughout (the
  *     dense baseline).  Both give the same result up to floating-point
  *     summation order.  fp32 products run over the kept rows alone.  In bf16
- *     the input products and input gradients do so at 256 batch rows and more
- *     (above half of the neurons dropped, or where the shape is small); the
- *     other bf16 products (smaller batches, the recurrences, the weight
- *     gradients, the head) multiply the dropped neurons' zeros in both modes,
- *     which on this device is faster than gathering the others.
+ *     the input products and input gradients of wide layers (768 inputs and
+ *     more) do so at batches that nearly fill multiples of 256 rows and rates
+ *     of a half and more; the other bf16 products (other layers and batches,
+ *     the recurrences, the weight gradients, the head) multiply the dropped
+ *     neurons' zeros in both modes, which on this device is faster than
+ *     gathering the others.
  *   - Weight rows of neurons that are dropped at every step do not reach the
  *     outputs in bf16, whatever they hold (Inf, NaN): a forward product that
  *     comes out NaN is formed again over the kept rows.

@@ -71,25 +71,35 @@ static int fail(int code, const std::string& msg) {
 static float inv_keep(double p) { return p > 0.0 ? (float)(1.0 / (1.0 - p)) : 1.0f; }
 
 // Whether layer l's input product (bf16) runs as one product over all rows or as a
-// product per step over its kept neurons, and the same of its input gradient (us at
-// 20 steps, hidden 650 / 1024 / 1500, product + gradient, p = 0.5 and 0.65):
-//   batch  64:  44 /  80 / 158 over rows,  92 / 140 / 317 and  87 / 130 / 298 per step
-//   batch 128:  57 / 178 / 282 over rows,  96 / 223 / 328 and  92 / 213 / 309 per step
-//   batch 256: 107 / 384 / 427 over rows, 107 / 311 / 355 and 104 / 294 / 336 per step
-// so the line lies at 256 rows a step: from there the per-step kernels' 256-row tiles are
-// full and skipping pays.  It pays only above half the neurons dropped where the
-// products over rows fill the chip with 256 x 256 tiles (64 steps x batch 256 x hidden
-// 1024, p = 0.5: 349 against 368 us the products, 289 against 349 the gradients); the
-// dense mode skips nothing.
-constexpr int SKIP_MIN_B = 256;
-static bool skip_pays(const Plan& P, int l) { return P.B >= SKIP_MIN_B && P.compact && P.p_nr[l] > 0.0f; }
+// product per step over its kept neurons, and the same of its input gradient.  Skipping
+// pays where a step's rows fill the per-step kernels' tiles of 256, the layer is wide and
+// more than half of its inputs are dropped; at half, where the products over rows leave
+// their last round of 256 x 256 tiles part empty (us per step / over rows):
+//                        hidden 512             hidden 1024            hidden 1500
+//                        product    gradient    product    gradient    product    gradient
+//   p 0.6, 20 x 192      34 /  24   50 /  29    59 /  43   83 /  52    99 / 101  113 / 123
+//   p 0.6, 20 x 224      34 /  30   51 /  40    60 /  69   85 /  92   100 / 106  117 / 132
+//   p 0.6, 20 x 256      34 /  29   54 /  33    60 /  75   87 /  91   102 / 112  121 / 135
+//   p 0.6, 20 x 320      49 /  32   54 /  35    96 /  84   89 /  93   190 / 153  218 / 191
+//   p 0.6, 64 x 256      73 /  62   60 /  63   165 / 170  130 / 143   307 / 344  270 / 388
+//   p 0.6, 30 x 512      64 /  61   58 /  61   159 / 164  132 / 141   276 / 313  263 / 380
+//   p 0.5, 20 x 256      36 /  29   53 /  33    67 /  75   87 /  92   114 / 114  121 / 134
+//   p 0.5, 64 x 256      75 /  64   61 /  63   181 / 174  175 / 144   339 / 354  278 / 390
+//   p 0.3, 64 x 256      84 /  62   61 /  63   214 / 174  173 / 143   403 / 347  360 / 391
+// The dense mode skips nothing.
+constexpr int SKIP_MIN_B = 218;                            // (0.85 of a tile)
+static bool skip_pays(const Plan& P, int l, long tiles) {
+    const int p = (P.B + 255) / 256 * 256;                 // rows that the tiles take
+    return P.compact && P.kin(l) >= 768 && P.B >= SKIP_MIN_B && P.B * 100L >= 85L * p &&
+           (P.p_nr[l] > 0.5 || (P.p_nr[l] == 0.5 && tiles * 100 < 90 * ((tiles + 255) / 256 * 256)));
+}
 static bool fx_rows(const Plan& P, int l) {
     const long tiles = (long)((P.T * P.B + 255) / 256) * ((P.G + 255) / 256) * P.D;
-    return P.dtype == LSTM_SD_DTYPE_BF16 && !(skip_pays(P, l) && (P.p_nr[l] > 0.5f || tiles < 1024));
+    return P.dtype == LSTM_SD_DTYPE_BF16 && !skip_pays(P, l, tiles);
 }
 static bool dx_rows(const Plan& P, int l) {
     const long tiles = (long)((P.T * P.B + 255) / 256) * ((P.kin(l) + 255) / 256);
-    return P.dtype == LSTM_SD_DTYPE_BF16 && !(skip_pays(P, l) && (P.p_nr[l] > 0.5f || tiles < 208));
+    return P.dtype == LSTM_SD_DTYPE_BF16 && !skip_pays(P, l, tiles);
 }
 
 int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {

@@ -1,8 +1,7 @@
 """Whole bf16 steps of large and ragged batches against the oracle: hidden sizes that are
 not multiples of the 32-neuron chunk or of the 16-unit tile, batches that are not
 multiples of a row group or of the 16-row MFMA tile, more row groups than one launch
-takes, 256 rows and more (input products and gradients over the kept neurons of a step),
-both directions, per-row lengths, and both modes; with the recurrences persistent and
+takes, 256 rows and more, both directions, per-row lengths, and both modes; with the recurrences persistent and
 with the per-step kernels, which run where a recurrence does not fit the device; and the
 same bits from every repeat."""
 import dataclasses

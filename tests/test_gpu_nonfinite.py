@@ -31,7 +31,7 @@ def _spoil(host, dev, never):
 @pytest.mark.parametrize("shape,p_nr,persist", [
     (dict(num_layers=3, num_dirs=1, input_dim=60, hidden=45, batch=20, seq_len=3), 0.5, "1"),
     (dict(num_layers=2, num_dirs=2, input_dim=33, hidden=70, batch=37, seq_len=3), 0.5, "1"),
-    (dict(num_layers=2, num_dirs=1, input_dim=140, hidden=70, batch=256, seq_len=3), 0.7, "1"),
+    (dict(num_layers=2, num_dirs=1, input_dim=780, hidden=70, batch=256, seq_len=3), 0.7, "1"),
     (dict(num_layers=1, num_dirs=1, input_dim=130, hidden=520, batch=300, seq_len=3), 0.3, "1"),
     (dict(num_layers=2, num_dirs=1, input_dim=60, hidden=45, batch=20, seq_len=3), 0.5, "0"),
 ])

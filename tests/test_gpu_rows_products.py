@@ -2,9 +2,9 @@
 gradient -- against the oracle where their tiling can go wrong, through the vocabulary
 head (any number of columns) and through layers of both directions: contractions that
 fill no 32-column chunk or no step of two, row counts around a row tile, every tile
-(64, 128 and 256 wide), sliced contractions, and batches of 256 and more, where a layer
-takes them or the products that skip the dropped neurons by its rate.  The bound is that
-of the other bf16 parity tests."""
+(64, 128 and 256 wide), sliced contractions, and large batches, where a layer takes them
+or the products per step that skip the dropped neurons, by its rate, its width and how
+full its tiles are.  The bound is that of the other bf16 parity tests."""
 import dataclasses
 
 import pytest
@@ -42,6 +42,14 @@ def test_head_products(T, B, F, V, p, compact):
     (dict(num_layers=2, num_dirs=1, input_dim=140, hidden=70, batch=255, seq_len=2), 0.7),
     (dict(num_layers=2, num_dirs=1, input_dim=140, hidden=70, batch=256, seq_len=2), 0.7),
     (dict(num_layers=2, num_dirs=1, input_dim=140, hidden=70, batch=256, seq_len=2), 0.0),
+    # per step over the kept neurons from 768 inputs on: products and gradients of one layer and of
+    # both, at more and at half of them dropped; the last batch that fills its tiles and the first
+    # that does not
+    (dict(num_layers=2, num_dirs=1, input_dim=771, hidden=40, batch=218, seq_len=3), 0.7),
+    (dict(num_layers=2, num_dirs=1, input_dim=1001, hidden=40, batch=256, seq_len=2), 0.5),
+    (dict(num_layers=2, num_dirs=2, input_dim=61, hidden=390, batch=503, seq_len=2), 0.6),
+    (dict(num_layers=1, num_dirs=1, input_dim=768, hidden=33, batch=217, seq_len=2), 0.7),
+    (dict(num_layers=1, num_dirs=1, input_dim=768, hidden=33, batch=300, seq_len=2), 0.7),
     # (weights of a trained network's size: a larger recurrence multiplies every rounding over 64 steps)
     (dict(num_layers=1, num_dirs=1, input_dim=24, hidden=1030, batch=260, seq_len=64, weight_init="uniform",
           weight_scale=1030 ** -0.5), 0.5),
