@@ -887,8 +887,6 @@ static int backward_impl(const Plan& P, const lstm_sd_weights* w, const int32_t*
                 wk.s_nr = P.s_nr[l];
                 wk.nr_up = site_view(P, mbuf, P.site_nr(l));
                 wk.dxw_out = (float*)(W + P.w_dxw) + (size_t)(l - 1) * T * B * H;
-                wk.dh0 = dh0 + (size_t)l * B * H;         // unused by a worker (poisoning targets only)
-                wk.dc0 = dc0 + (size_t)l * B * H;
             }
         }
         hipEvent_t e0 = nullptr, e1 = nullptr;
