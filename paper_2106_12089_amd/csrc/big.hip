@@ -866,9 +866,11 @@ static long rows_tiles(const RowsArgs& a, int TM, int TN) {
 }
 // Tiles of the input products (us at 64 x 64, 128 x 128 and 256 x 256 tiles; contraction
 // of 300, and of 1500 or 1000).
-// 128 x 128 from 160 of them on:
-//   120 tiles   9.5 / 12.7     20 / 26        200 tiles   13.6 / 14.0   33 / 27
-//   140 tiles   12 / 13        26 / 26        320 tiles   17 / 19       33 / 30
+// 128 x 128 from 160 of them on, from 512 where the contraction is short (of 700 at 200
+// tiles: 22 / 18 us):
+//   120 tiles   9.5 / 12.7     20 / 26        320 tiles   17 / 19       33 / 30
+//   140 tiles   12 / 13        26 / 26        640 tiles   28 / 26       65 / 48
+//   200 tiles   13.6 / 14.0    33 / 27       1260 tiles   49 / 39      123 / 81
 // 256 x 256 where they fill 0.7 of their rounds:
 //   0.62 (320)  39 / 48        81 / 87        0.78 (200)  31 / 27       75 / 58
 //   0.66 (170)  25 / 27        59 / 59        0.86 (440)  52 / 52       131 / 116
@@ -877,7 +879,7 @@ static long rows_tiles(const RowsArgs& a, int TM, int TN) {
 void launch_fx_rows(RowsArgs& a, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
     a.M = a.G;
     if (rounds_fill(rows_tiles(a, 256, 256) * a.np, 70)) rows_go<ROWS_FX, 2, 4, 8, 4, 1>(a, a.np, st, e0, e1);
-    else if (rows_tiles(a, 128, 128) * a.np >= 160) rows_go<ROWS_FX, 2, 2, 4, 4, 1>(a, a.np, st, e0, e1);
+    else if (rows_tiles(a, 128, 128) * a.np >= (a.K >= 400 ? 160 : 512)) rows_go<ROWS_FX, 2, 2, 4, 4, 1>(a, a.np, st, e0, e1);
     else rows_go<ROWS_FX, 2, 2, 2, 2, 2>(a, a.np, st, e0, e1);
 }
 // Tiles of the input gradients (us; contraction D*G of 1000 / 2600 / 4600 / 6000 / 12000

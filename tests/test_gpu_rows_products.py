@@ -22,7 +22,9 @@ pytestmark = pytest.mark.gpu
     (3, 43, 65, 132),         # 64 x 64, two row tiles and a row
     (5, 13, 31, 5004),        # gradient sliced over workgroups, output rows not a multiple of 4
     (2, 70, 132, 6148),       # the same, rows a multiple of 4, two row tiles
-    (33, 32, 40, 4100),       # product 128 x 128
+    (33, 32, 40, 4100),       # product 64 x 64, a short contraction
+    (20, 32, 401, 4100),      # product 128 x 128
+    (33, 64, 40, 4100),       # the same, a short contraction
     (9, 127, 1999, 516),      # gradient 64 x 64, 16 column tiles
     (11, 127, 1999, 516),     # gradient 128 x 128
     (16, 128, 40, 32768),     # product 256 x 256
