@@ -28,8 +28,8 @@
 //     read and the next step's inputs stay in flight over the grid barrier.
 // Measured per launch, before (weights in LDS, or a large batch in two phases) and
 // with this: two stacked layers of 650 at 20 rows, 35 steps: forward 172 -> 112,
-// backward 200 -> 124 us; three of 1150, 70 steps: 865 -> 360, 1300 -> 552 us; one
-// layer of 1024 at 256 rows, 64 steps: 488 -> 386, 943 -> 452 us.
+// backward 200 -> 122 us; three of 1150, 70 steps: 865 -> 380, 1300 -> 570 us (5%
+// between runs); one layer of 1024 at 256 rows, 64 steps: 488 -> 387, 943 -> 452 us.
 // Dropped neurons are zeros in the exchanged block (the masks are known to the
 // producer), in compact and dense mode alike: a step's products are a small
 // part of its time, and a register slice cannot be gathered by row.
