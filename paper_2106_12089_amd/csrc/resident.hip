@@ -495,6 +495,13 @@ __global__ void __launch_bounds__(512) k_fwd_res(RFwdArgs a) {
                 const float4 v = load_coherent4(gr, (uint32_t)(r.b * H + r.u) * 16u);
                 gxr[q][0] = v.x; gxr[q][1] = v.y; gxr[q][2] = v.z; gxr[q][3] = v.w;
             }
+        } else {
+            // (inputs loaded a step ago: waited for here.  Left to their use behind the
+            // product, two directions of 256 units, 32 rows took 56 us for 20 steps and
+            // 716 for 320; waited for here 52 and 657)
+#pragma unroll
+            for (int q = 0; q < PPT; ++q)
+                asm volatile("" : "+v"(gxr[q][0]), "+v"(gxr[q][1]), "+v"(gxr[q][2]), "+v"(gxr[q][3]));
         }
         product((const bf16*)D.hx + (size_t)(s & 1) * hxs, D.rmask + (size_t)t * a.kmax);
         bf16* hxn = (bf16*)D.hx + (size_t)((s + 1) & 1) * hxs;
