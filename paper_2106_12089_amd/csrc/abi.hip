@@ -87,10 +87,12 @@ static float inv_keep(double p) { return p > 0.0 ? (float)(1.0 / (1.0 - p)) : 1.
 //   p 0.5, 64 x 256      75 /  64   61 /  63   181 / 174  175 / 144   339 / 354  278 / 390
 //   p 0.3, 64 x 256      84 /  62   61 /  63   214 / 174  173 / 143   403 / 347  360 / 391
 // The dense mode skips nothing.
-constexpr int SKIP_MIN_B = 218;                            // (0.85 of a tile)
-static bool skip_pays(const Plan& P, int l, long tiles) {
+static bool skip_shape(const Plan& P, int l) {
     const int p = (P.B + 255) / 256 * 256;                 // rows that the tiles take
-    return P.compact && P.kin(l) >= 768 && P.B >= SKIP_MIN_B && P.B * 100L >= 85L * p &&
+    return P.kin(l) >= 768 && P.B * 100L >= 85L * p;
+}
+static bool skip_pays(const Plan& P, int l, long tiles) {
+    return P.compact && skip_shape(P, l) &&
            (P.p_nr[l] > 0.5 || (P.p_nr[l] == 0.5 && tiles * 100 < 90 * ((tiles + 255) / 256 * 256)));
 }
 static bool fx_rows(const Plan& P, int l) {
@@ -170,9 +172,10 @@ int make_plan(const lstm_sd_dims* d, Plan* p, const char** why) {
     q.r_gates = off; off = align_up(off + T * B * G * 4, A);
     q.r_c = off;     off = align_up(off + T * B * H * 4, A);
     const bool b16 = es == 2;
-    // (bf16: transposed inputs feed the per-step products only, whose batches are large;
-    // sized by the shape alone, so that one buffer serves every rate and both modes)
-    const bool xt = !b16 || q.B >= SKIP_MIN_B;
+    // (bf16: transposed inputs feed the per-step products only; sized by the shape
+    // alone, so that one buffer serves every rate and both modes)
+    bool xt = !b16;
+    for (int l = 0; l < q.L; ++l) xt = xt || skip_shape(q, l);
     q.r_hrecT = off; off = align_up(off + (b16 ? T * B * (size_t)q.HP : T * H * BP) * es, A);
     q.r_dir_bytes = off;
     off = (size_t)q.L * D * q.r_dir_bytes;
