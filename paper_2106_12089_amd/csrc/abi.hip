@@ -89,7 +89,8 @@ static float inv_keep(double p) { return p > 0.0 ? (float)(1.0 / (1.0 - p)) : 1.
 // The transposed inputs that skipping reads cost a pass part of that (20 us a layer at
 // 64 x 256 and 1024).  Whole passes, skipping against over rows: from 1280 wide 0.99 to 1.06
 // times as fast, most at p >= 0.7; 1024 wide 0.98 to 1.03, a loss only at p 0.6 and 64 x 256 or
-// 30 x 512; 800 wide 0.98 to 1.02 at 256 and 512 rows, but 0.94 at 224.
+// 30 x 512; 768 to 900 wide 0.98 to 1.02 at 64 steps, 256 or 512 rows, but 0.91 to 0.96 at
+// 20 x 218 and 20 x 224.
 // The dense mode skips nothing.
 static bool skip_shape(const Plan& P, int l) {
     const int p = (P.B + 255) / 256 * 256;                 // rows that the tiles take
